@@ -36,6 +36,20 @@ int check_device() {
   return cached[dev] > 0 ? LBM_OK : fail(LBM_EUNSUPPORTED, "device %d is not gfx950", dev);
 }
 
+int device_cus() {
+  static int cached[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (cached[dev] == 0) {
+    int v = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        v <= 0)
+      v = 256;
+    cached[dev] = v;
+  }
+  return cached[dev];
+}
+
 int launch_check(const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess)

@@ -42,27 +42,41 @@ __device__ __forceinline__ void pull9_walls(const T *__restrict__ src, int nx, i
   g[8] = above ? rp[(size_t)8 * nx + xm] : r0[(size_t)6 * nx + x];
 }
 
-// Guo's source term of direction i for the force (fx, 0) at velocity (u, v):
-// w_i [3 (e_i - u) + 9 (e_i . u) e_i] . F.
+// The moments with Guo's velocity, u = (sum_i e_i f_i + F / 2) / rho, for the
+// body force rho * gx along x.
 template <typename T>
-__device__ __forceinline__ T guo_source(int i, T fx, T u, T v) {
-  const T eu = T(cx(i)) * u + T(cy(i)) * v;
-  return wgt<T>(i) * fx * (T(3) * (T(cx(i)) - u) + T(9) * eu * T(cx(i)));
+__device__ __forceinline__ Moments<T> with_force(Moments<T> M, T gx) {
+#pragma clang fp contract(off)
+  M.u = M.u + T(0.5) * gx;
+  M.uu = fma_of(M.v, M.v, M.u * M.u);
+  M.diag = fma_of(M.jy, M.inv, M.u);
+  M.anti = fma_of(M.jy, M.inv, -M.u);
+  return M;
+}
+
+// Guo's source term of direction i for the force (fx, 0) at the velocity of
+// M, w_i [3 (e_i - u) + 9 (e_i . u) e_i] . F, without the products with a zero
+// component and with the fused multiply-adds written out (as geq_of).
+template <typename T>
+__device__ __forceinline__ T guo_source(int i, T fx, const Moments<T> &M) {
+#pragma clang fp contract(off)
+  const T wf = wgt<T>(i) * fx;
+  if (cx(i) == 0) return wf * (T(-3) * M.u);
+  // e_x (e_i . u)
+  const T ex = cy(i) == 0 ? M.u : (cx(i) * cy(i) > 0 ? M.diag : -M.anti);
+  return wf * fma_of(T(9), ex, T(3) * (T(cx(i)) - M.u));
 }
 
 // BGK collision with Guo's body-force term, force rho * gx along x.
 template <typename T>
 __device__ __forceinline__ void forced_collide(T (&g)[9], T omega, T gx) {
-  T drho, rho, u, v, uu;
-  node_moments(g, drho, rho, u, v, uu);
-  u += T(0.5) * gx;
-  uu = u * u + v * v;
-  const T fx = rho * gx;
-  const T src_scale = T(1) - T(0.5) * omega;
+#pragma clang fp contract(off)
+  const Moments<T> M = with_force(node_moments(g), gx);
+  const T fx = M.rho * gx;
+  const T src_scale = fma_of(T(-0.5), omega, T(1));
 #pragma unroll
   for (int i = 0; i < 9; ++i)
-    g[i] = g[i] + omega * (geq_shifted<T>(i, drho, rho, u, v, uu) - g[i]) +
-           src_scale * guo_source<T>(i, fx, u, v);
+    g[i] = fma_of(src_scale, guo_source<T>(i, fx, M), relax<T>(g[i], geq_of<T>(i, M), omega));
 }
 
 }  // namespace lbm

@@ -45,9 +45,8 @@ __global__ __launch_bounds__(kChannelThreads) void channel_profile_kernel(
     double f[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) f[i] = (double)r[(size_t)i * nx + x];
-    double drho, rho, u, v, uu;
-    node_moments(f, drho, rho, u, v, uu);
-    acc += u - 0.5 * (double)gx;
+    const Moments<double> M = node_moments(f);
+    acc += M.u - 0.5 * (double)gx;
   }
   red[threadIdx.x] = acc;
   __syncthreads();

@@ -264,15 +264,14 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
       float(&g)[9] = gc[half];
       float(&Gi)[9] = Gc[half];
       float(&z)[NOUT] = zc[half];
-      float drho, rho, u, v, uu;
-      lbm::node_moments(g, drho, rho, u, v, uu);
+      const lbm::Moments<float> M = lbm::node_moments(g);
       const float s = 1.0f / (1.0f + expf(-z[0]));
       const float tadj = 0.5f + s;
       const float tb = tauc[half];
       float dta = 0.0f, m0 = 0.0f, mx = 0.0f, my = 0.0f;
 #pragma unroll
       for (int i = 0; i < 9; ++i) {
-        dta += Gi[i] * (g[i] - lbm::geq_shifted<float>(i, drho, rho, u, v, uu));
+        dta += Gi[i] * (g[i] - lbm::geq_of(i, M));
         m0 += Gi[i];
         mx += float(cx(i)) * Gi[i];
         my += float(cy(i)) * Gi[i];

@@ -23,6 +23,7 @@
 #include <cstdint>
 
 #include "gnn_layout.hpp"
+#include "lbm_common.hpp"
 
 namespace gnn {
 
@@ -98,6 +99,27 @@ __device__ __forceinline__ float gelu_grad(float x) {
 __device__ __forceinline__ f32x4 gelu4(f32x4 v) {
   return f32x4{gelu(v.x), gelu(v.y), gelu(v.z), gelu(v.w)};
 }
+
+// ------------------------------------------------------------ collision ---
+
+// The projected correction of Eq. 3: (P v)_i = v_i - m0 / 9 - e_ix mx / 6 -
+// e_iy my / 6 for v = z[1..9] with the moments (m0, mx, my).  Sums and
+// projections are written over the velocity set, with no products by 0 and +-1.
+struct Projection {
+  float m0, mx, my;
+  __device__ __forceinline__ explicit Projection(const float (&z)[NOUT]) {
+#pragma clang fp contract(off)
+    m0 = (((((((z[1] + z[2]) + z[3]) + z[4]) + z[5]) + z[6]) + z[7]) + z[8]) + z[9];
+    mx = ((((z[2] - z[4]) + z[6]) - z[7]) - z[8]) + z[9];
+    my = ((((z[3] - z[5]) + z[6]) + z[7]) - z[8]) - z[9];
+  }
+  __device__ __forceinline__ float operator()(int i, const float (&z)[NOUT]) const {
+    float d = __builtin_fmaf(m0, -1.0f / 9.0f, z[1 + i]);
+    if (lbm::cx(i)) d = __builtin_fmaf(mx, lbm::cx(i) > 0 ? -1.0f / 6.0f : 1.0f / 6.0f, d);
+    if (lbm::cy(i)) d = __builtin_fmaf(my, lbm::cy(i) > 0 ? -1.0f / 6.0f : 1.0f / 6.0f, d);
+    return d;
+  }
+};
 
 // ------------------------------------------------------------------------
 // Packed weights.  gnn_prep_kernel converts the FP32 blob into BF16

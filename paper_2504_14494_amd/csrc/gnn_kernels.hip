@@ -273,11 +273,10 @@ __global__ __launch_bounds__(kThreads, SAVE ? 3 : 4) void gnn_encode_kernel(
       const unsigned drawn = cw.draw();
       float gp[9];
       node_pops<PULL>(lat, nx, ny, x < nx ? x : nx - 1, y, gp);
-      float drho, rho, u, v, uu;
-      lbm::node_moments(gp, drho, rho, u, v, uu);
+      const lbm::Moments<float> M = lbm::node_moments(gp);
       cw.take(drawn);
-      const float raw[NFEAT] = {gp[0], gp[1], gp[2], gp[3], gp[4], gp[5],
-                                gp[6], gp[7], gp[8], drho, u,     v};
+      const float raw[NFEAT] = {gp[0], gp[1], gp[2], gp[3],  gp[4], gp[5],
+                                gp[6], gp[7], gp[8], M.drho, M.u,   M.v};
       float ft[NFEAT];
 #pragma unroll
       for (int k = 0; k < NFEAT; ++k) ft[k] = (raw[k] - mu[k]) * isg[k];
@@ -356,27 +355,14 @@ struct HeadArgs {
 template <int I0 = 0, int I1 = 9>
 __device__ __forceinline__ void gnn_collide(float (&g)[9], const float (&z)[NOUT], float tau,
                                            float sdelta) {
-  float drho, rho, u, v, uu;
-  lbm::node_moments(g, drho, rho, u, v, uu);
+  const lbm::Moments<float> M = lbm::node_moments(g);
   float sig = 1.0f / (1.0f + expf(-z[0]));
   float tau_adj = 0.5f + sig;
   float omega = 1.0f / (tau * tau_adj);
-  float m0 = 0.0f, mx = 0.0f, my = 0.0f;
+  const Projection P(z);
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    m0 += z[1 + i];
-    mx += float(cx(i)) * z[1 + i];
-    my += float(cy(i)) * z[1 + i];
-  }
-  m0 *= (1.0f / 9.0f);
-  mx *= (1.0f / 6.0f);
-  my *= (1.0f / 6.0f);
-#pragma unroll
-  for (int i = I0; i < I1; ++i) {
-    float relaxed = g[i] + omega * (lbm::geq_shifted<float>(i, drho, rho, u, v, uu) - g[i]);
-    float df = z[1 + i] - m0 - float(cx(i)) * mx - float(cy(i)) * my;
-    g[i] = relaxed + sdelta * df;
-  }
+  for (int i = I0; i < I1; ++i)
+    g[i] = __builtin_fmaf(sdelta, P(i, z), lbm::relax(g[i], lbm::geq_of(i, M), omega));
 }
 
 // One round over 16 x 8 receiver tiles drawn from a counter, two 4-wave
@@ -998,6 +984,7 @@ __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
 
 using namespace gnn;
 using lbm::check_device;
+using lbm::device_cus;
 using lbm::fail;
 using lbm::launch_check;
 
@@ -1015,20 +1002,6 @@ static int encode_blocks_per_cu() {
     cached = v;
   }
   return cached;
-}
-
-static int device_cus() {
-  static int cached[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cached[dev] == 0) {
-    int v = 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        v <= 0)
-      v = 256;
-    cached[dev] = v;
-  }
-  return cached[dev];
 }
 
 static inline void *at(void *base, size_t off) { return (uint8_t *)base + off; }

@@ -51,12 +51,55 @@ struct EqCoef {
   __host__ __device__ static constexpr T D(int i) { return i == 0 ? D0 : (i < 5 ? D1 : D5); }
 };
 
-// Shifted equilibrium of direction i from drho = rho - 1, rho, u, v.
+__host__ __device__ __forceinline__ float fma_of(float a, float b, float c) {
+  return __builtin_fmaf(a, b, c);
+}
+__host__ __device__ __forceinline__ double fma_of(double a, double b, double c) {
+  return __builtin_fma(a, b, c);
+}
+
+// Shifted equilibrium of direction i from drho = rho - 1, rho, u, v, with
+// uu = u.u (initial states).
 template <typename T>
 __host__ __device__ __forceinline__ T geq_shifted(int i, T drho, T rho, T u, T v, T uu) {
   T eu = T(cx(i)) * u + T(cy(i)) * v;
   return EqCoef<T>::A(i) * drho +
          rho * (EqCoef<T>::B(i) * eu + EqCoef<T>::C(i) * eu * eu - EqCoef<T>::D(i) * uu);
+}
+
+// Moments of a node as the collisions use them: drho = rho - 1, rho, its
+// reciprocal, the momentum j = rho u, the velocity, u.u, and the velocity along
+// the two diagonals, u + v and v - u.
+template <typename T>
+struct Moments {
+  T drho, rho, inv, jx, jy, u, v, uu, diag, anti;
+};
+
+// Shifted equilibrium of direction i, as geq_shifted.  Opposite directions
+// share e.u up to its sign and C (e.u)^2, and no product with a zero component
+// is formed (the compiler must keep one: it is NaN for an infinite factor): 82
+// VALU instructions for the collision of a node, 108 when every direction
+// was written out.  The fused multiply-adds are explicit, so that every kernel
+// that inlines this rounds alike: steps of different kernels agree bitwise.
+template <typename T>
+__device__ __forceinline__ T geq_of(int i, const Moments<T> &M) {
+#pragma clang fp contract(off)
+  using E = EqCoef<T>;
+  if (i == 0) return fma_of(M.drho, E::A(0), M.rho * -(E::D(0) * M.uu));
+  const T e = i == 1 || i == 3   ? M.u
+              : i == 2 || i == 4 ? M.v
+              : i == 5 || i == 7 ? M.diag
+                                 : M.anti;
+  const T b = i == 3 || i == 4 || i == 7 || i == 8 ? -E::B(i) : E::B(i);
+  return fma_of(M.rho, fma_of(-E::D(i), M.uu, fma_of(b, e, e * (E::C(i) * e))),
+                E::A(i) * M.drho);
+}
+
+// g relaxed toward geq at rate omega.
+template <typename T>
+__device__ __forceinline__ T relax(T g, T geq, T omega) {
+#pragma clang fp contract(off)
+  return fma_of(omega, geq - g, g);
 }
 
 // Index of population i at node (x, y) of a row-interleaved lattice
@@ -87,20 +130,39 @@ __device__ __forceinline__ void pull9(const T *__restrict__ src, int nx, int ny,
   g[8] = rp[(size_t)8 * nx + xm];
 }
 
-// Density deviation, density, velocity and |u|^2 of one node from its
-// shifted populations (rho = 1 + sum g, rho u = sum e g).  The summation
-// order pairs opposite directions so that a state at rest sums exactly.
+// 1 / x.  FP32: the hardware reciprocal (1 ulp) and one Newton step, three
+// instructions for the eleven of an IEEE division; equal to 1.0f / x for every
+// x in [2^-20, 2^20] (checked over all of them), which is where a density
+// is.  An infinite or zero x gives NaN, as the collision that consumes it does.
+__device__ __forceinline__ float recip(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return __builtin_fmaf(__builtin_fmaf(-x, r, 1.0f), r, r);
+}
+// FP64: two Newton steps from the hardware's estimate, to within an ulp.
+__device__ __forceinline__ double recip(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+}
+
+// Moments of one node from its shifted populations (rho = 1 + sum g,
+// j = sum e g).  The summation order pairs opposite directions so that a
+// state at rest sums exactly.
 template <typename T>
-__device__ __forceinline__ void node_moments(const T (&g)[9], T &drho, T &rho, T &u, T &v,
-                                             T &uu) {
-  drho = ((g[0] + (g[1] + g[3])) + (g[2] + g[4])) + ((g[5] + g[7]) + (g[6] + g[8]));
-  T jx = (g[1] - g[3]) + ((g[5] - g[7]) + (g[8] - g[6]));
-  T jy = (g[2] - g[4]) + ((g[5] - g[7]) + (g[6] - g[8]));
-  rho = T(1) + drho;
-  T inv = T(1) / rho;
-  u = jx * inv;
-  v = jy * inv;
-  uu = u * u + v * v;
+__device__ __forceinline__ Moments<T> node_moments(const T (&g)[9]) {
+#pragma clang fp contract(off)
+  Moments<T> M;
+  M.drho = ((g[0] + (g[1] + g[3])) + (g[2] + g[4])) + ((g[5] + g[7]) + (g[6] + g[8]));
+  M.jx = (g[1] - g[3]) + ((g[5] - g[7]) + (g[8] - g[6]));
+  M.jy = (g[2] - g[4]) + ((g[5] - g[7]) + (g[6] - g[8]));
+  M.rho = T(1) + M.drho;
+  M.inv = recip(M.rho);
+  M.u = M.jx * M.inv;
+  M.v = M.jy * M.inv;
+  M.uu = fma_of(M.v, M.v, M.u * M.u);
+  M.diag = fma_of(M.jx, M.inv, M.v);
+  M.anti = fma_of(-M.jx, M.inv, M.v);
+  return M;
 }
 
 // BGK collision of one node in shifted variables (Eq. 1 with the
@@ -108,10 +170,24 @@ __device__ __forceinline__ void node_moments(const T (&g)[9], T &drho, T &rho, T
 // streamed) and is overwritten by the post-collision ones; omega = 1 / tau.
 template <typename T>
 __device__ __forceinline__ void bgk_collide(T (&g)[9], T omega) {
-  T drho, rho, u, v, uu;
-  node_moments(g, drho, rho, u, v, uu);
+  const Moments<T> M = node_moments(g);
 #pragma unroll
-  for (int i = 0; i < 9; ++i) g[i] = g[i] + omega * (geq_shifted<T>(i, drho, rho, u, v, uu) - g[i]);
+  for (int i = 0; i < 9; ++i) g[i] = relax<T>(g[i], geq_of<T>(i, M), omega);
+}
+
+// Lane l of a wave takes lane l - 1's v (the value at x - 1), lane 0 takes
+// `halo` (DPP wave_shr:1).
+__device__ __forceinline__ float wave_from_left(float v, float halo) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, halo),
+                                                               __builtin_bit_cast(int, v), 0x138,
+                                                               0xF, 0xF, false));
+}
+// Lane l takes lane l + 1's v (the value at x + 1), lane 63 takes `halo`
+// (DPP wave_shl:1).
+__device__ __forceinline__ float wave_from_right(float v, float halo) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, halo),
+                                                               __builtin_bit_cast(int, v), 0x130,
+                                                               0xF, 0xF, false));
 }
 
 // True if the byte ranges [a, a + bytes) and [b, b + bytes) intersect.
@@ -124,6 +200,8 @@ inline bool overlap(const void *a, const void *b, size_t bytes) {
 int fail(int code, const char *fmt, ...);
 // Checks that the current device is gfx950 (cached per device).
 int check_device();
+// Compute units of the current device (cached per device).
+int device_cus();
 // Maps the last HIP launch error to LBM_EDEVICE.
 int launch_check(const char *what);
 

@@ -87,21 +87,6 @@ __global__ __launch_bounds__(kBgkThreads) void bgk_pull_kernel(const T *__restri
   for (int i = 0; i < 9; ++i) __builtin_nontemporal_store(g[i], d + (size_t)i * nx);
 }
 
-// Lane l of a wave takes lane l - 1's v (the value at x - 1), lane 0 takes
-// `halo` (DPP wave_shr:1).
-__device__ __forceinline__ float wave_from_left(float v, float halo) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, halo),
-                                                               __builtin_bit_cast(int, v), 0x138,
-                                                               0xF, 0xF, false));
-}
-// Lane l takes lane l + 1's v (the value at x + 1), lane 63 takes `halo`
-// (DPP wave_shl:1).
-__device__ __forceinline__ float wave_from_right(float v, float halo) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, halo),
-                                                               __builtin_bit_cast(int, v), 0x130,
-                                                               0xF, 0xF, false));
-}
-
 // The same step in FP32, by waves of 64 consecutive nodes of a row.  The
 // six populations that move along x are not gathered from x -/+ 1: every
 // lane loads its own column, so each of the nine loads of a wave covers two

@@ -50,53 +50,47 @@ __device__ __forceinline__ u32x4 relu_frag(f32x4 lo, f32x4 hi) {
   return u32x4{relu_bf16x2(r.x), relu_bf16x2(r.y), relu_bf16x2(r.z), relu_bf16x2(r.w)};
 }
 
-// Density deviation, density and velocity of a node, as lbm::node_moments
-// (same sums, same order) but with the hardware reciprocal of rho (about
-// 1 ulp) instead of an IEEE division.
-__device__ __forceinline__ void moments(const float (&g)[9], float &drho, float &rho, float &u,
-                                        float &v) {
-  drho = ((g[0] + (g[1] + g[3])) + (g[2] + g[4])) + ((g[5] + g[7]) + (g[6] + g[8]));
-  const float jx = (g[1] - g[3]) + ((g[5] - g[7]) + (g[8] - g[6]));
-  const float jy = (g[2] - g[4]) + ((g[5] - g[7]) + (g[6] - g[8]));
-  rho = 1.0f + drho;
-  const float inv = __builtin_amdgcn_rcpf(rho);
-  u = jx * inv;
-  v = jy * inv;
+// Moments of a node, as lbm::node_moments (same sums, same order) but with
+// the hardware reciprocal of rho (about 1 ulp); what only the collision needs
+// is left to it.
+__device__ __forceinline__ lbm::Moments<float> moments(const float (&g)[9]) {
+#pragma clang fp contract(off)
+  lbm::Moments<float> M = {};
+  M.drho = ((g[0] + (g[1] + g[3])) + (g[2] + g[4])) + ((g[5] + g[7]) + (g[6] + g[8]));
+  M.jx = (g[1] - g[3]) + ((g[5] - g[7]) + (g[8] - g[6]));
+  M.jy = (g[2] - g[4]) + ((g[5] - g[7]) + (g[6] - g[8]));
+  M.rho = 1.0f + M.drho;
+  M.inv = __builtin_amdgcn_rcpf(M.rho);
+  M.u = M.jx * M.inv;
+  M.v = M.jy * M.inv;
+  return M;
 }
 
-// Eq. 3 with the projected correction at one node, given its moments (the
-// velocity without the force).  The sigmoid and the relaxation rate use the
+// Eq. 3 with the projected correction at one node, given its moments (with
+// Guo's velocity where there is a force).  The sigmoid and the relaxation rate use the
 // hardware exp2 and reciprocal (about 1 ulp each); z0 = 0 still gives
 // tau_adj = 1 exactly (2^0 = 1, 1/2 = 0.5).  FORCED: under the channel's body
 // force rho * gx, f^eq is taken at Guo's velocity and Guo's source is added at
 // the effective rate omega = 1 / (tau tau_adj).
 template <bool FORCED>
 __device__ __forceinline__ void collide(float (&g)[9], const float (&z)[NOUT], float tau,
-                                        float sdelta, float gx, float drho, float rho, float u,
-                                        float v) {
-  if constexpr (FORCED) u += 0.5f * gx;
-  const float uu = u * u + v * v;
+                                        float sdelta, float gx, lbm::Moments<float> M) {
+#pragma clang fp contract(off)
+  M.uu = FORCED ? __builtin_fmaf(M.v, M.v, M.u * M.u) : __builtin_fmaf(M.u, M.u, M.v * M.v);
+  M.diag = M.u + M.v;
+  M.anti = M.v - M.u;
   constexpr float kLog2e = 1.4426950408889634f;
   float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-z[0] * kLog2e));
   float tau_adj = 0.5f + sig;
   float omega = __builtin_amdgcn_rcpf(tau * tau_adj);
-  float m0 = 0.0f, mx = 0.0f, my = 0.0f;
+  const float fx = M.rho * gx, src_scale = __builtin_fmaf(-0.5f, omega, 1.0f);
+  const Projection P(z);
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
-    m0 += z[1 + i];
-    mx += float(cx(i)) * z[1 + i];
-    my += float(cy(i)) * z[1 + i];
-  }
-  m0 *= (1.0f / 9.0f);
-  mx *= (1.0f / 6.0f);
-  my *= (1.0f / 6.0f);
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    float relaxed = g[i] + omega * (lbm::geq_shifted<float>(i, drho, rho, u, v, uu) - g[i]);
+    float relaxed = lbm::relax(g[i], lbm::geq_of(i, M), omega);
     if constexpr (FORCED)
-      relaxed += (1.0f - 0.5f * omega) * lbm::guo_source<float>(i, rho * gx, u, v);
-    float df = z[1 + i] - m0 - float(cx(i)) * mx - float(cy(i)) * my;
-    g[i] = relaxed + sdelta * df;
+      relaxed = __builtin_fmaf(src_scale, lbm::guo_source<float>(i, fx, M), relaxed);
+    g[i] = __builtin_fmaf(sdelta, P(i, z), relaxed);
   }
 }
 
@@ -176,7 +170,7 @@ __global__ __launch_bounds__(kThreads, SAVE ? kBlocksPerCuSave : kBlocksPerCu) v
     const bool valid = x < nx;
     const unsigned drawn = cw.draw();
     float gp[9];
-    float drho, rho, u, v;  // kept for the collision
+    lbm::Moments<float> M;  // kept for the collision
     {
       // rows y - 1, y, y + 1 (uniform) and columns x - 1, x, x + 1 (per lane)
       const int xv = valid ? x : nx - 1;
@@ -211,11 +205,11 @@ __global__ __launch_bounds__(kThreads, SAVE ? kBlocksPerCuSave : kBlocksPerCu) v
       }
     }
     {
-      moments(gp, drho, rho, u, v);
+      M = moments(gp);
       cw.take(drawn);
-      const float uf = WALLS ? u + 0.5f * gx : u;  // Guo's velocity on the channel
-      const float raw[NFEAT] = {gp[0], gp[1], gp[2], gp[3], gp[4], gp[5],
-                                gp[6], gp[7], gp[8], drho, uf,    v};
+      if (WALLS) M.u = __builtin_fmaf(M.jx, M.inv, 0.5f * gx);  // Guo's velocity
+      const float raw[NFEAT] = {gp[0], gp[1], gp[2], gp[3],  gp[4], gp[5],
+                                gp[6], gp[7], gp[8], M.drho, M.u,   M.v};
       float ft[NFEAT];
 #pragma unroll
       for (int k = 0; k < NFEAT; ++k) ft[k] = fmaf(raw[k], isg[k], nmi[k]);
@@ -305,7 +299,7 @@ __global__ __launch_bounds__(kThreads, SAVE ? kBlocksPerCuSave : kBlocksPerCu) v
         for (int k = 0; k < NOUT; ++k) z[k] = zz[k];
       }
       const float tau = tau_arr ? tau_arr[b] : tau_s;  // b < batch while cw.more()
-      collide<WALLS>(gp, z, tau, sdelta, gx, drho, rho, u, v);
+      collide<WALLS>(gp, z, tau, sdelta, gx, M);
       float *d = dst + (size_t)b * ny * row + (size_t)y * row + x;
       // node mass in FP32 (rounding ~1e-9 per node, ~1e-13 of the lattice
       // mass), accumulated over the nodes in exact fixed point (a total that
@@ -377,15 +371,6 @@ using lbm::launch_check;
 
 static inline void *at_(void *base, size_t off) { return (uint8_t *)base + off; }
 
-static int simple_device_cus() {
-  int dev = 0, v = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 256;
-  if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      v <= 0)
-    return 256;
-  return v;
-}
-
 // pull: the fused step (else the forward of pre-collision states); walls: the
 // channel step (with pull), body force rho * gx along x.
 static int launch_simple(bool pull, bool walls, float gx, const float *src, float *dst,
@@ -400,7 +385,7 @@ static int launch_simple(bool pull, bool walls, float gx, const float *src, floa
   const long long chunks = (long long)batch * ny * ((nx + 63) / 64);
   long long blocks = (chunks + simple::kWaves - 1) / simple::kWaves;
   // the resident blocks; their waves draw the chunks from a counter
-  long long cap = (long long)simple_device_cus() *
+  long long cap = (long long)lbm::device_cus() *
                   (saved && !pull ? simple::kBlocksPerCuSave : simple::kBlocksPerCu);
   if (cap > kMaxGnnBlocks) cap = kMaxGnnBlocks;
   const int nb = (int)(blocks < cap ? blocks : cap);
