@@ -91,6 +91,18 @@ int lbm_step_bgk(const float *g_src, float *g_dst, int nx, int ny, float tau,
 int lbm_step_bgk_f64(const double *g_src, double *g_dst, int nx, int ny,
                      double tau, void *stream);
 
+/* nsteps steps of lbm_step_bgk in one pass over the lattice, bitwise the
+ * state that as many single steps leave (the states in between exist on the
+ * chip only).  2 <= nsteps <= lbm_steps_max(nx, ny, f64, walls), the most steps
+ * that one call takes for this lattice: f64 1 for FP64 populations, walls 1 for
+ * the channel (lbm_steps_channel, below).  Other arguments and errors as
+ * lbm_step_bgk. */
+int lbm_steps_max(int nx, int ny, int f64, int walls);
+int lbm_steps_bgk(const float *g_src, float *g_dst, int nx, int ny, float tau,
+                  int nsteps, void *stream);
+int lbm_steps_bgk_f64(const double *g_src, double *g_dst, int nx, int ny,
+                      double tau, int nsteps, void *stream);
+
 /* Streaming alone, the left-hand side of Eq. 1 without the collision:
  * g_dst_i(x) = g_src_i(x - e_i), periodic, on `batch` lattices stored one
  * after another ([batch][ny][9][nx]).  Turns a post-collision state into the
@@ -160,6 +172,12 @@ int lbm_step_channel(const float *g_src, float *g_dst, int nx, int ny, float tau
                      float gx, void *stream);
 int lbm_step_channel_f64(const double *g_src, double *g_dst, int nx, int ny,
                          double tau, double gx, void *stream);
+
+/* nsteps steps of lbm_step_channel in one pass, as lbm_steps_bgk. */
+int lbm_steps_channel(const float *g_src, float *g_dst, int nx, int ny,
+                      float tau, float gx, int nsteps, void *stream);
+int lbm_steps_channel_f64(const double *g_src, double *g_dst, int nx, int ny,
+                          double tau, double gx, int nsteps, void *stream);
 
 /* x-averaged velocity profile of a channel state as lbm_step_channel leaves
  * it (post-collision populations f*, whose momentum includes the step's

@@ -25,6 +25,8 @@ EXPORTS = [
     "lbm_last_error", "lbm_init", "lbm_init_f64", "lbm_step_bgk", "lbm_step_bgk_f64",
     "lbm_stream", "lbm_init_ce", "lbm_init_ce_f64",
     "lbm_step_channel", "lbm_step_channel_f64", "lbm_channel_profile",
+    "lbm_steps_max", "lbm_steps_bgk", "lbm_steps_bgk_f64", "lbm_steps_channel",
+    "lbm_steps_channel_f64",
     "lbm_moments", "lbm_restrict", "lbm_copy", "gnn_param_count", "gnn_blob_len",
     "lbm_step_gnn", "lbm_step_gnn_noalloc", "gnn_forward", "gnn_backward", "gnn_mse",
     "gnn_mse_weighted", "gnn_adam",
@@ -71,6 +73,11 @@ def load(path: str = LIB_PATH):
         "lbm_stream": ([vp, vp, i, i, i, vp], i),
         "lbm_step_channel": ([vp, vp, i, i, f, f, vp], i),
         "lbm_step_channel_f64": ([vp, vp, i, i, d, d, vp], i),
+        "lbm_steps_max": ([i, i, i, i], i),
+        "lbm_steps_bgk": ([vp, vp, i, i, f, i, vp], i),
+        "lbm_steps_bgk_f64": ([vp, vp, i, i, d, i, vp], i),
+        "lbm_steps_channel": ([vp, vp, i, i, f, f, i, vp], i),
+        "lbm_steps_channel_f64": ([vp, vp, i, i, d, d, i, vp], i),
         "lbm_channel_profile": ([vp, i, i, f, vp, vp], i),
         "lbm_init_ce": ([vp, i, i, vp, vp, vp, f, vp], i),
         "lbm_init_ce_f64": ([vp, i, i, vp, vp, vp, d, vp], i),

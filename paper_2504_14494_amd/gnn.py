@@ -287,7 +287,7 @@ class GnnLattice(Lattice):
                 tmp.mass.copy_(self.fallback.mass)
             step(self.a.clone(), torch.empty_like(self.a), tmp)
         return self._run(("gnn", float(tau), bool(gate)) + self._graph_key(gate),
-                         lambda s, d: step(s, d, fb), warm, n, graph)
+                         lambda s, d, k: step(s, d, fb), warm, n, graph)
 
     def step_gnn_channel(self, tau: float, gx: float, n: int = 1, gate: bool = True,
                          graph: bool = False):
@@ -309,7 +309,7 @@ class GnnLattice(Lattice):
                 tmp.mass.copy_(self.fallback.mass)
             step(self.a.clone(), torch.empty_like(self.a), tmp)
         return self._run(("gnn_channel", float(tau), float(gx), bool(gate)) + self._graph_key(gate),
-                         lambda s, d: step(s, d, fb), warm, n, graph)
+                         lambda s, d, k: step(s, d, fb), warm, n, graph)
 
 
 def backward_ws_bytes(batch: int, nx: int, ny: int, rounds: int = 2) -> int:

@@ -17,7 +17,8 @@ from ._lib import LbmFallback, LbmTgv, check
 
 __all__ = [
     "lbm_init", "lbm_init_ce", "lbm_step_bgk", "lbm_stream", "lbm_moments", "lbm_restrict", "lbm_copy",
-    "lbm_step_channel", "lbm_channel_profile",
+    "lbm_step_channel", "lbm_channel_profile", "lbm_steps_max", "lbm_steps_bgk",
+    "lbm_steps_channel",
     "lbm_workspace_bytes", "Workspace", "Lattice",
 ]
 
@@ -130,6 +131,35 @@ def lbm_step_channel(src: torch.Tensor, dst: torch.Tensor, tau: float, gx: float
     return dst
 
 
+def lbm_steps_max(nx: int, ny: int, dtype=torch.float32, walls: bool = False) -> int:
+    """The most steps that one call of lbm_steps_bgk (walls: lbm_steps_channel)
+    takes for this lattice."""
+    return int(_lib.load().lbm_steps_max(nx, ny, int(dtype == torch.float64), int(walls)))
+
+
+def _steps(name, src, dst, args, nsteps):
+    _need(src, src.dtype, "src")
+    _need(dst, src.dtype, "dst")
+    nx, ny = _pop_dims(src)
+    if src.shape != dst.shape:
+        raise ValueError("src and dst shapes differ")
+    if src.dtype not in (torch.float32, torch.float64):
+        raise TypeError("populations must be float32 or float64")
+    fn = getattr(_lib.load(), name if src.dtype == torch.float32 else name + "_f64")
+    check(fn(_ptr(src), _ptr(dst), nx, ny, *args, int(nsteps), _stream()), name)
+    return dst
+
+
+def lbm_steps_bgk(src: torch.Tensor, dst: torch.Tensor, tau: float, nsteps: int):
+    """nsteps (2 to lbm_steps_max) steps of lbm_step_bgk in one pass."""
+    return _steps("lbm_steps_bgk", src, dst, (float(tau),), nsteps)
+
+
+def lbm_steps_channel(src: torch.Tensor, dst: torch.Tensor, tau: float, gx: float, nsteps: int):
+    """nsteps (2 to lbm_steps_max) steps of lbm_step_channel in one pass."""
+    return _steps("lbm_steps_channel", src, dst, (float(tau), float(gx)), nsteps)
+
+
 def lbm_channel_profile(g: torch.Tensor, gx: float) -> torch.Tensor:
     """x-averaged fluid velocity u_x(y) of a channel state as
     lbm_step_channel leaves it (post-collision), FP64 [ny]."""
@@ -201,17 +231,25 @@ def lbm_copy(src: torch.Tensor, dst: torch.Tensor):
     return dst
 
 
+def _shares(n: int, parts: int):
+    """n split into `parts` whole shares that differ by at most one."""
+    return [n // parts + (1 if j < n % parts else 0) for j in range(parts)] if parts else []
+
+
 class Lattice:
     """A/B population buffers of one periodic D2Q9 lattice on the GPU.
 
-    Stepping methods take `graph=True` to run whole chunks of steps as one
-    captured HIP graph (torch.cuda.CUDAGraph over the library's launches on
-    the current stream), which removes the per-launch host cost that
-    dominates small lattices.  The graph holds the buffer addresses, so one
-    is captured per (step kind, parameters, buffer holding the state) and
-    replayed; results are bitwise those of the eager steps."""
+    Plain and channel steps are taken several at a time (lbm_steps_max of the
+    lattice), which writes only the last state.  Stepping methods take
+    `graph=True` to run whole chunks of steps as one captured HIP graph
+    (torch.cuda.CUDAGraph over the library's launches on the current stream),
+    which removes the per-launch host cost that dominates small lattices; a
+    lattice whose steps one launch takes by the thousand needs none.  The
+    graph holds the buffer addresses, so one is captured per (step kind,
+    parameters, buffer holding the state) and replayed.  Results are bitwise
+    those of single eager steps."""
 
-    GRAPH_CHUNK = 64   # steps per captured graph (even: the state returns to `a`)
+    GRAPH_CHUNK = 64   # steps per captured graph
 
     def __init__(self, nx: int, ny: int, dtype=torch.float32, device="cuda"):
         self.nx, self.ny = nx, ny
@@ -219,10 +257,13 @@ class Lattice:
         self.b = torch.empty_like(self.a)
         self.steps = 0
         self._graphs = {}
+        self._most = lbm_steps_max(nx, ny, dtype)
+        self._most_walls = lbm_steps_max(nx, ny, dtype, walls=True)
 
-    def _capture(self, one_step, warmup):
+    def _capture(self, advance, warmup, most):
         """HIP graph of GRAPH_CHUNK steps from self.a, ping-ponging with
-        self.b.  `warmup()` runs one step on scratch copies first, on the
+        self.b over an even number of launches, so that the state returns to
+        self.a.  `warmup()` runs one step on scratch copies first, on the
         side stream, so that library state and workspaces exist before the
         capture and the lattice itself does not advance."""
         side = torch.cuda.Stream()
@@ -231,11 +272,13 @@ class Lattice:
             warmup()
         torch.cuda.current_stream().wait_stream(side)
         torch.cuda.synchronize()
+        launches = -(-self.GRAPH_CHUNK // most)
+        launches += launches % 2
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g):
             src, dst = self.a, self.b
-            for _ in range(self.GRAPH_CHUNK):
-                one_step(src, dst)
+            for k in _shares(self.GRAPH_CHUNK, launches):
+                advance(src, dst, k)
                 src, dst = dst, src
         return g
 
@@ -245,23 +288,23 @@ class Lattice:
         cannot leave it pointing at freed memory."""
         return [self.a, self.b]
 
-    def _run(self, key, one_step, warmup, n: int, graph: bool):
+    def _run(self, key, advance, warmup, n: int, graph: bool, most: int = 1):
         """n steps: whole chunks from a captured graph when `graph`, the rest
-        eagerly (one_step(src, dst) advances src into dst)."""
-        if graph and n >= self.GRAPH_CHUNK:
+        eagerly.  advance(src, dst, k) takes src k steps on into dst, k <= most."""
+        if graph and n >= self.GRAPH_CHUNK and 2 * most <= self.GRAPH_CHUNK:
             k = (key, self.a.data_ptr())
             if k not in self._graphs:
-                g = self._capture(one_step, warmup)
+                g = self._capture(advance, warmup, most)
                 self._graphs[k] = (g, list(self._graph_buffers()))
             g = self._graphs[k][0]
             for _ in range(n // self.GRAPH_CHUNK):
                 g.replay()
             self.steps += (n // self.GRAPH_CHUNK) * self.GRAPH_CHUNK
             n %= self.GRAPH_CHUNK
-        for _ in range(n):
-            one_step(self.a, self.b)
+        for k in _shares(n, -(-n // most)) if n > 1 else (1,) * n:
+            advance(self.a, self.b, k)
             self.a, self.b = self.b, self.a
-            self.steps += 1
+            self.steps += k
         return self
 
     @property
@@ -288,20 +331,27 @@ class Lattice:
         return self
 
     def step_bgk(self, tau: float, n: int = 1, graph: bool = False):
-        def one(src, dst):
-            lbm_step_bgk(src, dst, tau)
+        def advance(src, dst, k):
+            if k == 1:
+                lbm_step_bgk(src, dst, tau)
+            else:
+                lbm_steps_bgk(src, dst, tau, k)
 
         def warm():
-            one(self.a.clone(), torch.empty_like(self.a))
-        return self._run(("bgk", float(tau)), one, warm, n, graph)
+            advance(self.a.clone(), torch.empty_like(self.a), 1)
+        return self._run(("bgk", float(tau)), advance, warm, n, graph, self._most)
 
     def step_channel(self, tau: float, gx: float, n: int = 1, graph: bool = False):
-        def one(src, dst):
-            lbm_step_channel(src, dst, tau, gx)
+        def advance(src, dst, k):
+            if k == 1:
+                lbm_step_channel(src, dst, tau, gx)
+            else:
+                lbm_steps_channel(src, dst, tau, gx, k)
 
         def warm():
-            one(self.a.clone(), torch.empty_like(self.a))
-        return self._run(("channel", float(tau), float(gx)), one, warm, n, graph)
+            advance(self.a.clone(), torch.empty_like(self.a), 1)
+        return self._run(("channel", float(tau), float(gx)), advance, warm, n, graph,
+                         self._most_walls)
 
     def moments(self, analytic=None, fields=False):
         return lbm_moments(self.a, analytic, fields)
