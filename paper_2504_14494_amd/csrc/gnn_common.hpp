@@ -211,26 +211,28 @@ constexpr int kQueueStride = 32;  // words between two part counters (128 bytes)
 struct ChunkQueue {
   int c, xc, y, b;  // current chunk, c >= nchunks when done
   int cxn, ny, nchunks;
-  int base, len, cur, end, first_dyn;
+  int base, len, cur, end, first_dyn, batch;
   unsigned *ctr;
   int nxt;     // first chunk (in the part) of the next batch, once taken
   bool fresh;  // the current chunk starts its batch: its draw is to be issued and taken
-  __device__ __forceinline__ ChunkQueue(int batch, int nx, int ny_, int waves_per_block,
+  __device__ __forceinline__ ChunkQueue(int lattices, int nx, int ny_, int waves_per_block,
                                         int wave, unsigned *counters) {
     const int w = __builtin_amdgcn_readfirstlane(wave);
     cxn = (nx + 63) >> 6;
     ny = ny_;
-    nchunks = batch * ny * cxn;
+    nchunks = lattices * ny * cxn;
     const int G = (int)gridDim.x, parts = G < kQueueParts ? G : kQueueParts;
     const int p = (int)blockIdx.x % parts;
     const int L = (nchunks + parts - 1) / parts;
     base = p * L;
     len = nchunks - base < L ? nchunks - base : L;
     const int part_waves = ((G - 1 - p) / parts + 1) * waves_per_block;
-    first_dyn = part_waves * kQueueBatch;
+    const int share = len / part_waves;
+    batch = share >= kQueueBatch ? kQueueBatch : (share > 1 ? share : 1);
+    first_dyn = part_waves * batch;
     ctr = counters + p * kQueueStride;
     nxt = len;
-    cur = ((int)blockIdx.x / parts * waves_per_block + w) * kQueueBatch;
+    cur = ((int)blockIdx.x / parts * waves_per_block + w) * batch;
     begin_batch();
   }
   __device__ __forceinline__ void at(int local) {
@@ -244,7 +246,7 @@ struct ChunkQueue {
       c = nchunks;
       return;
     }
-    end = cur + kQueueBatch < len ? cur + kQueueBatch : len;
+    end = cur + batch < len ? cur + batch : len;
     at(cur);
     fresh = true;
   }
@@ -261,7 +263,7 @@ struct ChunkQueue {
       // the one-lane atomic wave-wide and waits for its result at once
       int z = 0;
       asm volatile("" : "+v"(z));
-      d = atomicAdd(ctr + z, (unsigned)kQueueBatch);
+      d = atomicAdd(ctr + z, (unsigned)batch);
     }
     return d;
   }
