@@ -186,8 +186,11 @@ __device__ __forceinline__ f32x4 load_bias(const f32x4 *__restrict__ bias, int b
   return bias[(size_t)b * 64 + lane];
 }
 
-// Packs the FP32 blob into `pack` (frag_layout(R).total bytes) on stream s.
-int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, hipStream_t s);
+// Packs the FP32 blob into `pack` (frag_layout(R).total bytes) on stream s, and
+// readies the control words of a step (ctrl, or NULL): counters zeroed, the
+// gate's reference mass (mass, or NULL without the gate) copied.
+int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, const double *mass,
+                hipStream_t s);
 
 // Chunks of 64 consecutive nodes of a lattice row, chunk c = (b ny + y) cxn
 // + xc over `batch` lattices of nx x ny (batch nx ny < 2^31 keeps every index
@@ -294,26 +297,25 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 // ------------------------------------------------------------------ gate ---
 
-// The per-step fallback gate, as seen by the kernel that produces the
-// corrected step's per-workgroup FP64 mass and flag partials.  Control words
-// (in the caller's workspace): ctrl[0] = the step's decision, ctrl[1] =
-// workgroups of the producing kernel done, ctrl[2] = workgroups of the
-// fallback kernel done.  gnn_prep_kernel, which starts every step, zeroes
-// the two counts, the tile counters of the message-passing rounds,
+// The per-step fallback gate.  The kernel that produces the corrected step
+// leaves one mass partial and one flag per workgroup; the gate kernel that
+// follows it sums them (every workgroup for itself: the sums are exact, so all
+// decide alike) and redoes the step with plain BGK if it must.  The launch in
+// between is what makes the partials visible: an arrival count in the
+// producing kernel, with the device-wide fences it needs across the XCDs, took
+// 7.6 us of a step.  Control words (in the caller's workspace), readied by
+// gnn_prep_kernel, which starts every step: ctrl[kCtrlFallback] = workgroups of
+// the gate kernel done with a fallback (0), ctrl[kCtrlMass ..] = the FP64 mass of
+// the previous state, the tile counters of the message-passing rounds (0),
 // ctrl[kCtrlTileQueue + r], and the chunk counters of the encoder or of the
-// fused per-node step, ctrl[kCtrlChunkQueue + 32 p].  arrive == NULL means the step runs without the
-// gate.
+// fused per-node step (0), ctrl[kCtrlChunkQueue + 32 p].
+constexpr int kCtrlFallback = 2;
 constexpr int kCtrlTileQueue = 4;
+constexpr int kCtrlMass = 8;         // two words, 8-byte aligned
 constexpr int kCtrlChunkQueue = 32;  // kQueueParts counters, 128 bytes apart
-static_assert(kCtrlTileQueue + MAX_ROUNDS <= kCtrlChunkQueue, "control words");
+static_assert(kCtrlTileQueue + MAX_ROUNDS <= kCtrlMass && kCtrlMass + 2 <= kCtrlChunkQueue,
+              "control words");
 static_assert(kCtrlChunkQueue + kQueueParts * kQueueStride <= kCtrlWords, "control words fit their bytes");
-struct GateArgs {
-  unsigned *ctrl;        // control words above, or NULL (no gate)
-  double threshold;      // relative mass drift allowed per step
-  unsigned *flags;       // OR-ed: 1 = negative / non-finite population, 2 = drift
-  unsigned *n_fallback;  // steps that fell back, or NULL
-  double *mass;          // total mass of the previous state (FP64), in/out
-};
 
 // Mass partials in exact fixed point: a signed 128-bit integer in units of
 // 2^-80 (hi * 2^64 + lo).  Integer addition is associative, so a total does
@@ -373,65 +375,48 @@ __device__ __forceinline__ double q80_value(Q80 q) {
   return (double)q.hi * (1.0 / 65536.0) + (double)q.lo * 0x1p-80;
 }
 
-// Partial sums of either kind, added and read out in the gate below.
-__device__ __forceinline__ double part_add(double a, double b) { return a + b; }
-__device__ __forceinline__ Q80 part_add(Q80 a, Q80 b) { return q80_add(a, b); }
-__device__ __forceinline__ double part_value(double a) { return a; }
-__device__ __forceinline__ double part_value(Q80 a) { return q80_value(a); }
-template <typename P>
-__device__ __forceinline__ P part_zero() { return P{}; }
+// Sum over the lanes of a wave, in every lane.
+__device__ __forceinline__ Q80 q80_wave_sum(Q80 m) {
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) {
+    Q80 o;
+    o.lo = __shfl_xor(m.lo, s);
+    o.hi = __shfl_xor(m.hi, s);
+    m = q80_add(m, o);
+  }
+  return m;
+}
 
-// Called by all kThreads threads of every workgroup of the producing kernel,
-// after its thread 0 stored the workgroup's partials.  The workgroup that
-// finishes last sums every partial in index order (a fixed order: the same
-// decision for the same state) and decides: bit 1 = a negative or non-finite
-// population, bit 2 = relative change of total mass not <= threshold.  A
-// kept step records its new mass here; a tripped one records the flags and
-// the fallback count, and the fallback kernel then writes the mass of what it
-// stored.  sm and sf are shared scratch of kThreads entries each; every
-// thread takes part in the barriers, so no thread may have left before.
-template <int kThreads, typename P>
-__device__ void gate_decide_last(const GateArgs &g, const P *pmass, const unsigned *pflag,
-                                 int nparts, double nodes, P *sm, unsigned *sf) {
+// Sums over a workgroup through one LDS entry per wave (integer atomics in LDS
+// took 8 us here: the lanes of a wave take turns at an address).
+struct PartialSlot {
+  Q80 mass;
+  unsigned flag;
+};
+// (then a barrier)
+__device__ __forceinline__ void put_partial(PartialSlot *slots, Q80 mass, unsigned flag) {
+  const Q80 m = q80_wave_sum(mass);
+  const bool any = __ballot(flag != 0u) != 0ull;
+  if ((threadIdx.x & 63) == 0) slots[threadIdx.x >> 6] = PartialSlot{m, any ? 1u : 0u};
+}
+__device__ __forceinline__ PartialSlot sum_partials(const PartialSlot *slots, int first, int n) {
+  PartialSlot s = slots[first];
+  for (int k = first + 1; k < first + n; ++k) {
+    s.mass = q80_add(s.mass, slots[k].mass);
+    s.flag |= slots[k].flag;
+  }
+  return s;
+}
+
+// Leaves a workgroup's partial: called by all its threads, a slot per wave in LDS.
+__device__ __forceinline__ void store_partial(PartialSlot *slots, Q80 mass, unsigned flag,
+                                              Q80 *pmass, unsigned *pflag) {
+  put_partial(slots, mass, flag);
+  __syncthreads();
   if (threadIdx.x == 0) {
-    __threadfence();  // this workgroup's partials before its arrival
-    const unsigned done = atomicAdd(&g.ctrl[1], 1u);
-    sf[0] = done == gridDim.x - 1 ? 1u : 0u;
-  }
-  __syncthreads();
-  const bool last = sf[0] != 0u;
-  __syncthreads();
-  if (!last) return;
-  __threadfence();  // every other workgroup's partials are visible
-  P m = part_zero<P>();
-  unsigned f = 0;
-  for (int k = threadIdx.x; k < nparts; k += kThreads) {
-    m = part_add(m, pmass[k]);
-    f |= pflag[k];
-  }
-  sm[threadIdx.x] = m;
-  sf[threadIdx.x] = f;
-  __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      sm[threadIdx.x] = part_add(sm[threadIdx.x], sm[threadIdx.x + s]);
-      sf[threadIdx.x] |= sf[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double mnew = nodes + part_value(sm[0]);
-    const double mold = *g.mass;
-    unsigned fl = sf[0] ? 1u : 0u;
-    const double rel = fabs(mnew - mold) / mold;
-    if (!(rel <= g.threshold)) fl |= 2u;
-    g.ctrl[0] = fl;
-    if (fl) {
-      *g.flags |= fl;
-      if (g.n_fallback) *g.n_fallback += 1u;
-    } else {
-      *g.mass = mnew;
-    }
+    const PartialSlot s = sum_partials(slots, 0, (int)blockDim.x >> 6);
+    pmass[blockIdx.x] = s.mass;
+    pflag[blockIdx.x] = s.flag;
   }
 }
 

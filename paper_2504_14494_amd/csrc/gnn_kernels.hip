@@ -161,12 +161,13 @@ __device__ __forceinline__ long long bias_index(const BlobLayout &L, const FragL
 __global__ __launch_bounds__(64) void gnn_prep_kernel(const float *__restrict__ blob, int R,
                                                       BlobLayout L, FragLayout F,
                                                       uint8_t *__restrict__ pack,
-                                                      unsigned *__restrict__ ctrl) {
+                                                      unsigned *__restrict__ ctrl,
+                                                      const double *__restrict__ mass) {
   int lane = threadIdx.x, f = blockIdx.x;
-  // the fallback gate's arrival counts start every step at zero
+  // the fallback's arrival count starts every step at zero
   if (ctrl && f == 0 && lane == 0) {
-    ctrl[1] = 0u;
-    ctrl[2] = 0u;
+    ctrl[kCtrlFallback] = 0u;
+    if (mass) *(double *)(ctrl + kCtrlMass) = *mass;
   }
   // and so do the tile counters of the rounds and the chunk counters
   if (ctrl && f == 0 && lane < MAX_ROUNDS) ctrl[kCtrlTileQueue + lane] = 0u;
@@ -345,9 +346,8 @@ struct HeadArgs {
   float tau;              // tau when tau_arr is NULL
   float *head_out;        // [N][10] head outputs or NULL
   float *save_z;          // [N][12] head outputs kept for the backward pass
-  double *pmass;          // [gridDim.x] FP64 sum of g* over the nodes of a workgroup
+  Q80 *pmass;             // [gridDim.x] sum of g* over the nodes of a workgroup
   unsigned *pflag;        // [gridDim.x] 1 if a population came out negative / non-finite
-  GateArgs gate;          // the fallback gate (gate.ctrl NULL: none)
 };
 
 // Corrected collision of one node (Eq. 3 with the projected correction),
@@ -391,7 +391,6 @@ constexpr int kHaloBytes = kStageLoads * 64 * 16;
 static_assert(kNodeBytes == 9 * 16, "a node is nine 16-byte slots");
 static_assert(kRowsPerWave * kRoundWaves == TILE_Y, "tile rows split over the waves");
 static_assert(TILE_X * TILE_Y * NOUT * 4 <= kHaloBytes, "head outputs fit in a halo buffer");
-static_assert((16 + 4) * kRoundThreads <= kHaloBytes, "reduction fits in a halo buffer");
 // Divisions of the staging loop by multiply and shift (full-rate 24-bit
 // multiplies): slot / 9 for every slot of a halo buffer and node / HALO_X for
 // every node, checked here over the whole range.
@@ -893,47 +892,332 @@ __global__ __launch_bounds__(kRoundThreads, 2) void gnn_round_kernel(
 
   if constexpr (HEAD) {
     __syncthreads();  // last tile's head outputs consumed
-    Q80 *red_m = (Q80 *)hs_a;
-    unsigned *red_f = (unsigned *)(hs_a + sizeof(Q80) * kRoundThreads);
-    red_m[threadIdx.x] = mass_acc;
-    red_f[threadIdx.x] = flag_acc;
-    __syncthreads();
-    for (int s = kRoundThreads / 2; s > 0; s >>= 1) {
-      if ((int)threadIdx.x < s) {
-        red_m[threadIdx.x] = q80_add(red_m[threadIdx.x], red_m[threadIdx.x + s]);
-        red_f[threadIdx.x] |= red_f[threadIdx.x + s];
+    store_partial((PartialSlot *)hs_a, mass_acc, flag_acc, args.pmass, args.pflag);
+  }
+}
+
+// ------------------------------------------------- small lattices, fused ---
+
+// The whole corrected collision of a small lattice in one kernel: a workgroup
+// takes 16 x 4 nodes and recomputes the ring that its rounds read, so the
+// encoder, the R rounds, the head and the collision follow one another in LDS
+// with a barrier between them, where the large-lattice kernels go through
+// memory and a launch each.  Same arithmetic in the same order as those, so
+// bitwise the same results.  What bounds it is the chain of phases: at 128^2
+// there is one workgroup per CU (eight waves, two per SIMD), its GELUs
+// alone are 6 us (10, 7 and 4 groups of 16 nodes in the three phases of R = 2),
+// and it runs 16: 2.6 until the weights and populations are there, 2 in the
+// encoder, 7 and 4 in the rounds.  A gated step of 128^2 in a captured graph:
+// 46 us with encoder, rounds and gate arrival, 24 with this kernel.
+constexpr int kSmallThreads = 512;
+constexpr int kSmallWaves = kSmallThreads / 64;
+constexpr int kSmallY = 4;                 // tile rows (TILE_X columns)
+constexpr int kSmallRounds = 2;            // weights of more rounds do not fit the LDS
+
+template <int R>
+struct SmallTile {
+  // frame of nodes in LDS: the tile and R rings around it
+  static constexpr int W = TILE_X + 2 * R, H = kSmallY + 2 * R, kNodes = W * H;
+  // receivers of round r: the tile and R - 1 - r rings
+  static constexpr int width(int r) { return TILE_X + 2 * (R - 1 - r); }
+  static constexpr int rows(int r) { return kSmallY + 2 * (R - 1 - r); }
+  // the packed fragments and biases a forward pass reads lie in one run each
+  static constexpr int kFrags = 12 + 36 * R + 2;  // W1 W2 (WA WB WC WN)^R WH
+  static constexpr int kBias = 9 + 8 * R;         // b1 b2 (be bn)^R bh
+};
+
+template <int R, bool PULL>
+__global__ __launch_bounds__(kSmallThreads, 2) void gnn_small_kernel(
+    int batch, int nx, int ny, const uint8_t *__restrict__ pack, FragLayout F, HeadArgs args) {
+  using G = SmallTile<R>;
+  __shared__ u32x4 w_s[G::kFrags * 64];
+  __shared__ f32x4 b_s[G::kBias * 4];  // per channel group (16 lanes share one)
+  __shared__ __attribute__((aligned(16))) uint8_t h_s[2][G::kNodes * kNodeBytes];
+  __shared__ __attribute__((aligned(16))) uint32_t slot_s[G::kNodes * 8];
+  __shared__ PartialSlot part_s[kSmallWaves];
+  static_assert(TILE_X * kSmallY * NOUT <= G::kNodes * 8, "head outputs fit in the slots");
+  static_assert(TILE_X * kSmallY == 64, "one wave holds the tile");
+  static_assert((G::width(0) * G::rows(0) + 15) / 16 <= kSmallWaves, "a group per wave");
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int n = lane & 15, q = lane >> 4;
+  const u32x4 *frags = (const u32x4 *)(pack + F.frag_off) + (size_t)F.W1 * 64;
+  const f32x4 *bias = (const f32x4 *)(pack + F.bias_off) + (size_t)F.B1 * 64;
+  const float *cst = (const float *)(pack + F.const_off);
+
+  const int txn = (nx + TILE_X - 1) / TILE_X, tyn = (ny + kSmallY - 1) / kSmallY;
+  const int tile = blockIdx.x, tx = tile % txn, ty = tile / txn % tyn, b = tile / txn / tyn;
+  const int x0 = tx * TILE_X, y0 = ty * kSmallY;
+  const float *lat = args.src + (size_t)b * ny * 9 * nx;
+
+  // The populations of the frame's nodes, one node per lane, and the weights
+  // are all requested before the first wait.
+  const int fy = (int)threadIdx.x / G::W, fx = (int)threadIdx.x - fy * G::W;
+  const bool framed = (int)threadIdx.x < G::kNodes;
+  float gp[9] = {};
+  if (framed) node_pops<PULL>(lat, nx, ny, wrapi(x0 - R + fx, nx), wrapi(y0 - R + fy, ny), gp);
+  constexpr int kLoads = (G::kFrags + kSmallWaves - 1) / kSmallWaves;
+  u32x4 wl[kLoads];
+#pragma unroll
+  for (int k = 0; k < kLoads; ++k) {
+    const int f = k * kSmallWaves + wave;
+    wl[k] = frags[(size_t)(f < G::kFrags ? f : 0) * 64 + lane];
+  }
+  f32x4 bl = {};
+  if (threadIdx.x < G::kBias * 4)
+    bl = bias[(size_t)(threadIdx.x >> 2) * 64 + 16 * (threadIdx.x & 3)];
+  const float sdelta = cst[C_SDELTA];
+  if (framed) {
+    const lbm::Moments<float> M = lbm::node_moments(gp);
+    const float raw[NFEAT] = {gp[0], gp[1], gp[2], gp[3],  gp[4], gp[5],
+                              gp[6], gp[7], gp[8], M.drho, M.u,   M.v};
+    float ft[NFEAT];
+#pragma unroll
+    for (int j = 0; j < NFEAT; ++j)
+      ft[j] = (raw[j] - cst[C_MU + j]) * (1.0f / cst[C_SIGMA + j]);
+    u32x4 *o = (u32x4 *)(slot_s + threadIdx.x * 8);
+    o[0] = u32x4{pack_bf16(ft[0], ft[1]), pack_bf16(ft[2], ft[3]), pack_bf16(ft[4], ft[5]),
+                 pack_bf16(ft[6], ft[7])};
+    o[1] = u32x4{pack_bf16(ft[8], ft[9]), pack_bf16(ft[10], ft[11]), 0u, 0u};
+  }
+#pragma unroll
+  for (int k = 0; k < kLoads; ++k) {
+    const int f = k * kSmallWaves + wave;
+    if (f < G::kFrags) w_s[f * 64 + lane] = wl[k];
+  }
+  if (threadIdx.x < G::kBias * 4) b_s[threadIdx.x] = bl;
+  __syncthreads();
+
+  const u32x4 *w = w_s + lane;
+  const f32x4 *bs = b_s + q;
+
+  // encoder: 16 nodes at a time, states into h_s[0]
+  for (int grp = wave; grp < (G::kNodes + 15) / 16; grp += kSmallWaves) {
+    const int k = 16 * grp + n < G::kNodes ? 16 * grp + n : G::kNodes - 1;
+    const u32x4 xb = q < 2 ? *(const u32x4 *)(slot_s + k * 8 + 4 * q) : u32x4{0u, 0u, 0u, 0u};
+    f32x4 a[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) a[t] = gelu4(mfma(w[t * 64], xb, bs[t * 4]));
+    const u32x4 e1[2] = {frag_from_acc(a[0], a[1]), frag_from_acc(a[2], a[3])};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const f32x4 acc = mfma(w[(4 + 2 * t) * 64], e1[0], bs[(4 + t) * 4]);
+      a[t] = gelu4(mfma(w[(5 + 2 * t) * 64], e1[1], acc));
+    }
+    u32x4 *dst = (u32x4 *)(h_s[0] + k * kNodeBytes);
+    dst[q] = frag_from_acc(a[0], a[1]);  // (lanes past the frame repeat its last node)
+    dst[4 + q] = frag_from_acc(a[2], a[3]);
+  }
+  __syncthreads();
+
+  // The tile's populations, for the collision: waves 4 and 5 have no
+  // receivers in the last round and split them (0-4 and 5-8).
+  const int xo = x0 + (lane & 15), yo = y0 + (lane >> 4);
+  const bool inside = xo < nx && yo < ny;
+
+  // One copy of the code for all rounds: a workgroup passes here once per
+  // round, and a second copy would come cold from the instruction cache.
+#pragma unroll 1
+  for (int r = 0; r < R; ++r) {
+    const bool last = r == R - 1;
+    const uint8_t *hin = h_s[r & 1];
+    uint8_t *hout = h_s[(r + 1) & 1];
+    const u32x4 *wr = w + (12 + 36 * r) * 64;  // WA 0, WB 8, WC 16, WN 20
+    const f32x4 *be = bs + (8 + 8 * r) * 4, *bn = be + 16;
+    const int wo = G::width(r), no = wo * G::rows(r);
+    if (last && (wave == 4 || wave == 5))
+      node_pops<PULL>(lat, nx, ny, inside ? xo : x0, inside ? yo : y0, gp);
+    if (16 * wave < no) {
+      const int k = 16 * wave + n < no ? 16 * wave + n : no - 1;
+      const int ry = k / wo, rx = k - ry * wo;
+      // the receiver's place in the frame; chunk q of its lower-left
+      // neighbour, from which every neighbour's is at a constant offset
+      const int at = (ry + r + 1) * G::W + rx + r + 1;
+      const uint8_t *nb = hin + (at - G::W - 1) * kNodeBytes + q * 16;
+      auto frag_at = [&](int dx, int dy, int s) {
+        return *(const u32x4 *)(nb + ((dy + 1) * G::W + dx + 1) * kNodeBytes + s * 64);
+      };
+      const u32x4 hn[2] = {frag_at(0, 0, 0), frag_at(0, 0, 1)};
+      u32x4 wb[4][2];
+      uint32_t wc[4];  // only lanes q == 0 hold a non-zero (first) dword
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        wb[t][0] = wr[(8 + 2 * t) * 64];
+        wb[t][1] = wr[(9 + 2 * t) * 64];
+        wc[t] = wr[(16 + t) * 64].x;
       }
-      __syncthreads();
+      f32x4 an[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        an[t] = mfma(wr[2 * t * 64], hn[0], be[t * 4]);
+        an[t] = mfma(wr[(2 * t + 1) * 64], hn[1], an[t]);
+      }
+      u32x4 hj[2][2];
+      hj[1][0] = frag_at(cx(1), cy(1), 0);
+      hj[1][1] = frag_at(cx(1), cy(1), 1);
+      hj[0][0] = frag_at(cx(2), cy(2), 0);
+      hj[0][1] = frag_at(cx(2), cy(2), 1);
+      f32x4 agg[4] = {};
+      const uint32_t q0 = q == 0 ? 0xffffffffu : 0u;
+      auto message = [&](int d, const u32x4(&h)[2], f32x4(&acc)[4]) {
+        const u32x4 ed = {q0 & (bf16_unit(cx(d)) | (bf16_unit(cy(d)) << 16)), 0u, 0u, 0u};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          acc[t] = mfma(u32x4{wc[t], 0u, 0u, 0u}, ed, an[t]);
+          acc[t] = mfma(wb[t][0], h[0], acc[t]);
+          acc[t] = mfma(wb[t][1], h[1], acc[t]);
+        }
+      };
+      // the edge pipeline of gnn_round_kernel
+      f32x4 acc[2][4];
+      message(1, hj[1], acc[0]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int d = 1; d < 9; ++d) {
+        if (d + 2 <= 8) {
+          hj[d & 1][0] = frag_at(cx(d + 2), cy(d + 2), 0);
+          hj[d & 1][1] = frag_at(cx(d + 2), cy(d + 2), 1);
+        }
+        if (d < 8) message(d + 1, hj[(d + 1) & 1], acc[d & 1]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) agg[t] += gelu4(acc[(d - 1) & 1][t]);
+        if (d + 2 <= 8) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        if (d < 8) {
+#pragma unroll
+          for (int i = 0; i < 12; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const u32x4 ab[2] = {frag_from_acc(agg[0], agg[1]), frag_from_acc(agg[2], agg[3])};
+      f32x4 p[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        p[t] = mfma(wr[(20 + 4 * t) * 64], hn[0], bn[t * 4]);
+        p[t] = mfma(wr[(21 + 4 * t) * 64], hn[1], p[t]);
+        p[t] = mfma(wr[(22 + 4 * t) * 64], ab[0], p[t]);
+        p[t] = mfma(wr[(23 + 4 * t) * 64], ab[1], p[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) p[t] = gelu4(p[t]);
+      const u32x4 hb[2] = {frag_from_acc(p[0], p[1]), frag_from_acc(p[2], p[3])};
+      if (!last) {
+        u32x4 *dst = (u32x4 *)(hout + at * kNodeBytes);
+        dst[q] = hb[0];
+        dst[4 + q] = hb[1];
+      } else {
+        const f32x4 z = mfma(w[(G::kFrags - 1) * 64], hb[1],
+                             mfma(w[(G::kFrags - 2) * 64], hb[0], bs[(G::kBias - 1) * 4]));
+        const float zz[4] = {z.x, z.y, z.z, z.w};
+        float *zb = (float *)slot_s;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (4 * q + e < NOUT) zb[k * NOUT + 4 * q + e] = zz[e];
+      }
     }
-    Q80 *pmass = (Q80 *)args.pmass;
+    __syncthreads();
+  }
+
+  if (wave == 4 || wave == 5) {
+    float z[NOUT];
+#pragma unroll
+    for (int k = 0; k < NOUT; ++k) z[k] = ((const float *)slot_s)[lane * NOUT + k];
+    const float tau = args.tau_arr ? args.tau_arr[b] : args.tau;
+    const bool lo = wave == 4;
+    if (lo)
+      gnn_collide<0, 5>(gp, z, tau, sdelta);
+    else
+      gnn_collide<5, 9>(gp, z, tau, sdelta);
+    double msum = 0.0;
+    unsigned bad = 0;
+    if (inside) {
+      float *d = args.dst + (size_t)b * ny * 9 * nx + (size_t)yo * 9 * nx + xo;
+      auto finish = [&](int i) {
+        d[(size_t)i * nx] = gp[i];
+        const float f = gp[i] + lbm::wgt<float>(i);
+        bad |= (f >= 0.0f && f < INFINITY) ? 0u : 1u;
+        msum += (double)gp[i];
+      };
+      if (lo) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) finish(i);
+        if (args.head_out) {
+          const size_t node = ((size_t)b * ny + yo) * nx + xo;
+          for (int k = 0; k < NOUT; ++k) args.head_out[node * NOUT + k] = z[k];
+        }
+      } else {
+#pragma unroll
+        for (int i = 5; i < 9; ++i) finish(i);
+      }
+    }
+    if (PULL) put_partial(part_s, q80_of(msum), bad);
+  }
+  if constexpr (PULL) {
+    __syncthreads();
     if (threadIdx.x == 0) {
-      pmass[blockIdx.x] = red_m[0];
-      args.pflag[blockIdx.x] = red_f[0];
-    }
-    if constexpr (PULL) {
-      if (args.gate.ctrl)
-        gate_decide_last<kRoundThreads>(args.gate, pmass, args.pflag, (int)gridDim.x,
-                                        (double)batch * nx * ny, red_m, red_f);
+      const PartialSlot s = sum_partials(part_s, 4, 2);
+      args.pmass[blockIdx.x] = s.mass;
+      args.pflag[blockIdx.x] = s.flag;
     }
   }
 }
 
 // ------------------------------------------------------------ fallback ---
 
-// Plain BGK step from the unchanged source when the gate tripped (same
-// arithmetic as bgk_pull_kernel, grid-stride; for the channel, the same as
-// channel_pull_kernel: walls and forcing); exits at once otherwise.  The
-// workgroup that finishes last sums the FP64 partials of what was stored in
-// index order and records it as the new total mass.
+// The gate: every workgroup sums the producing kernel's partials and decides
+// (bit 1 = a negative or non-finite population, bit 2 = relative change of
+// total mass not <= threshold).  A kept step records its new mass.  A tripped one
+// records the flags and the fallback count and is redone as a plain BGK step
+// from the unchanged source (same arithmetic as bgk_pull_kernel, grid-stride;
+// for the channel, as channel_pull_kernel: walls and forcing); the workgroup
+// that finishes last sums the FP64 partials of what was stored in index order and
+// records it as the new total mass.
+struct GateArgs {
+  const Q80 *pmass;       // partials of the producing kernel
+  const unsigned *pflag;
+  int nparts;
+  double threshold;
+  unsigned *flags, *n_fallback;
+  double *mass;
+};
+
 __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
     const float *__restrict__ src, float *__restrict__ dst, int nx, int ny, float omega,
     int walls, float gx, unsigned *__restrict__ ctrl, double *__restrict__ pmass2,
-    double *__restrict__ mass) {
+    GateArgs gate) {
   __shared__ double sm[kThreads];
+  __shared__ PartialSlot part_s[kWaves];
   __shared__ unsigned last_s;
-  if (ctrl[0] == 0) return;
-  double m = 0.0;
   const size_t nodes = (size_t)nx * ny;
+  {
+    Q80 m{0ull, 0ll};
+    unsigned f = 0;
+    for (int k = threadIdx.x; k < gate.nparts; k += kThreads) {
+      m = q80_add(m, gate.pmass[k]);
+      f |= gate.pflag[k];
+    }
+    const double mold = *(const double *)(ctrl + kCtrlMass);
+    put_partial(part_s, m, f);
+    __syncthreads();
+    const PartialSlot sum = sum_partials(part_s, 0, kWaves);
+    const double mnew = (double)nodes + q80_value(sum.mass);
+    unsigned fl = sum.flag;
+    const double rel = fabs(mnew - mold) / mold;
+    if (!(rel <= gate.threshold)) fl |= 2u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if (fl) {
+        *gate.flags |= fl;
+        if (gate.n_fallback) *gate.n_fallback += 1u;
+      } else {
+        *gate.mass = mnew;
+      }
+    }
+    if (!fl) return;
+  }
+  double m = 0.0;
   for (size_t k = (size_t)blockIdx.x * kThreads + threadIdx.x; k < nodes;
        k += (size_t)gridDim.x * kThreads) {
     int x = (int)(k % nx), y = (int)(k / nx);
@@ -961,7 +1245,7 @@ __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
   if (threadIdx.x == 0) {
     pmass2[blockIdx.x] = sm[0];
     __threadfence();  // the partial before the arrival
-    const unsigned done = atomicAdd(&ctrl[2], 1u);
+    const unsigned done = atomicAdd(&ctrl[kCtrlFallback], 1u);
     last_s = done == gridDim.x - 1 ? 1u : 0u;
   }
   __syncthreads();
@@ -975,7 +1259,7 @@ __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
     if ((int)threadIdx.x < s) sm[threadIdx.x] += sm[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *mass = (double)nodes + sm[0];
+  if (threadIdx.x == 0) *gate.mass = (double)nodes + sm[0];
 }
 
 }  // namespace gnn
@@ -1017,27 +1301,29 @@ extern "C" size_t gnn_blob_len(int n_rounds) {
 
 namespace gnn {
 
-int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, hipStream_t s) {
+int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, const double *mass,
+                hipStream_t s) {
   const BlobLayout L = blob_layout(R);
   const FragLayout F = frag_layout(R);
   if (F.total > kPackBytes) return fail(LBM_EINVAL, "packed weights exceed their scratch");
   hipLaunchKernelGGL(gnn_prep_kernel, dim3(F.nfrag + F.nbias + 1), dim3(64), 0, s, params, R, L,
-                     F, pack, ctrl);
+                     F, pack, ctrl, mass);
   return launch_check("gnn_prep_kernel");
 }
 
 // Launches weight packing, encoder and rounds.  src: populations the
 // collision starts from (post-collision state of the previous step when
-// PULL, else pre-collision); the last round writes dst and the partials.
+// PULL, else pre-collision); the last kernel writes dst and *nparts mass and
+// flag partials.
 int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, int ny,
                    const float *tau_arr, float tau, const float *params, int R, float *head_out,
-                   void *saved, void *ws, const lbm_fallback *fb, hipStream_t s) {
+                   void *saved, void *ws, const lbm_fallback *fb, int *nparts, hipStream_t s) {
   const long long nodes = (long long)batch * nx * ny;
   const FragLayout F = frag_layout(R);
   const ForwardScratch W = forward_scratch(nodes);
   uint8_t *pack = (uint8_t *)at(ws, W.pack);
   unsigned *ctrl = (unsigned *)at(ws, W.ctrl);
-  if (int rc = launch_prep(params, R, pack, ctrl, s)) return rc;
+  if (int rc = launch_prep(params, R, pack, ctrl, fb ? fb->mass : nullptr, s)) return rc;
 
   const int cus = device_cus();
   const bool save = saved != nullptr;
@@ -1047,6 +1333,34 @@ int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, i
     if (save) return (uint16_t *)at(saved, S.h + (size_t)r * align256((size_t)nodes * HID * 2));
     return (uint16_t *)at(ws, (r & 1) ? W.hB : W.hA);
   };
+
+  // Small lattices take one fused kernel, up to two workgroups per CU one after
+  // the other: gated steps took 24 us at 128^2 (256 tiles; encoder and rounds
+  // launched on their own 46), 39 at 160 x 160 (400 tiles; 43) and 55 at 192^2
+  // (576 tiles; 54).
+  const long long small_tiles =
+      (long long)batch * ((nx + TILE_X - 1) / TILE_X) * ((ny + kSmallY - 1) / kSmallY);
+  if (R <= kSmallRounds && !save && small_tiles <= 2 * device_cus()) {
+    HeadArgs ha{};
+    ha.src = src;
+    ha.dst = dst;
+    ha.tau_arr = tau_arr;
+    ha.tau = tau;
+    ha.head_out = head_out;
+    ha.pmass = (Q80 *)at(ws, W.pmass);
+    ha.pflag = (unsigned *)at(ws, W.pflag);
+    *nparts = (int)small_tiles;
+    const dim3 grid((unsigned)small_tiles), block(kSmallThreads);
+    if (pull && R == 1)
+      hipLaunchKernelGGL((gnn_small_kernel<1, true>), grid, block, 0, s, batch, nx, ny, pack, F, ha);
+    else if (pull)
+      hipLaunchKernelGGL((gnn_small_kernel<2, true>), grid, block, 0, s, batch, nx, ny, pack, F, ha);
+    else if (R == 1)
+      hipLaunchKernelGGL((gnn_small_kernel<1, false>), grid, block, 0, s, batch, nx, ny, pack, F, ha);
+    else
+      hipLaunchKernelGGL((gnn_small_kernel<2, false>), grid, block, 0, s, batch, nx, ny, pack, F, ha);
+    return launch_check("gnn_small_kernel");
+  }
 
   // the encoder's grid: the workgroups that fit on the device at once (four
   // per CU for inference, three when saving activations); their waves draw
@@ -1075,6 +1389,7 @@ int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, i
   long long cap = (long long)cus * 2;
   if (cap > kMaxGnnBlocks) cap = kMaxGnnBlocks;
   int rb = (int)(ntiles < cap ? ntiles : cap);
+  *nparts = rb;
   HeadArgs none{};
   HeadArgs ha{};
   ha.src = src;
@@ -1083,9 +1398,8 @@ int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, i
   ha.tau = tau;
   ha.head_out = head_out;
   ha.save_z = save ? (float *)at(saved, S.z) : nullptr;
-  ha.pmass = (double *)at(ws, W.pmass);
+  ha.pmass = (Q80 *)at(ws, W.pmass);
   ha.pflag = (unsigned *)at(ws, W.pflag);
-  if (fb && pull) ha.gate = GateArgs{ctrl, fb->drift_threshold, fb->flags, fb->n_fallback, fb->mass};
   for (int r = 0; r < R; ++r) {
     const bool head = r == R - 1;
     uint16_t *hin = hbuf(r);
@@ -1118,15 +1432,19 @@ int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, i
 
 namespace gnn {
 
-// The fallback kernel of the per-step gate, after a corrected step whose last
-// workgroup took the decision into ctrl[0]: recompute with plain BGK if
-// tripped (the kernel exits at once otherwise) and record the new mass.
+// The gate of a corrected step whose producing kernel left `nparts` partials.
 int launch_gate(const float *g_src, float *g_dst, int nx, int ny, float tau, int walls,
-                float gx, const lbm_fallback *fb, void *pmass2, void *ctrl, hipStream_t s) {
-  long long fbn = ((long long)nx * ny + kThreads - 1) / kThreads;
-  int fbb = (int)(fbn < kMaxGnnBlocks ? fbn : kMaxGnnBlocks);
-  hipLaunchKernelGGL(gate_fallback_kernel, dim3(fbb), dim3(kThreads), 0, s, g_src, g_dst, nx, ny,
-                     1.0f / tau, walls, gx, (unsigned *)ctrl, (double *)pmass2, fb->mass);
+                float gx, const lbm_fallback *fb, const void *pmass, const void *pflag,
+                int nparts, void *pmass2, void *ctrl, hipStream_t s) {
+  // four workgroups per CU: each of them reads every partial, and a fallback
+  // walks the lattice in strides of the grid
+  const long long fbn = ((long long)nx * ny + kThreads - 1) / kThreads;
+  const long long cap = 4LL * device_cus() < kMaxGnnBlocks ? 4LL * device_cus() : kMaxGnnBlocks;
+  const GateArgs gate{(const Q80 *)pmass, (const unsigned *)pflag, nparts,
+                      fb->drift_threshold, fb->flags, fb->n_fallback, fb->mass};
+  hipLaunchKernelGGL(gate_fallback_kernel, dim3((unsigned)(fbn < cap ? fbn : cap)),
+                     dim3(kThreads), 0, s, g_src, g_dst, nx, ny, 1.0f / tau, walls, gx,
+                     (unsigned *)ctrl, (double *)pmass2, gate);
   return launch_check("gate_fallback_kernel");
 }
 
@@ -1158,20 +1476,23 @@ extern "C" int gnn_forward(const float *g_pre, float *g_post, int batch, int nx,
   if (saved && saved_bytes < saved_need)
     return fail(LBM_EWORKSPACE, "gnn_forward: saved buffer needs %zu bytes", saved_need);
   if (int rc = check_device()) return rc;
+  int nparts;
   return launch_forward(false, g_pre, g_post, batch, nx, ny, tau, 0.0f, params, n_rounds,
-                        head_out, saved, workspace, nullptr, (hipStream_t)stream);
+                        head_out, saved, workspace, nullptr, &nparts, (hipStream_t)stream);
 }
 
 // lbm_step_gnn on a given scratch of forward_scratch(nx * ny) bytes or more.
 static int step_gnn(const float *g_src, float *g_dst, int nx, int ny, float tau,
                     const float *params, int n_rounds, const lbm_fallback *fb, void *workspace,
                     hipStream_t s) {
+  int nparts;
   if (int rc = launch_forward(true, g_src, g_dst, 1, nx, ny, nullptr, tau, params, n_rounds,
-                              nullptr, nullptr, workspace, fb, s))
+                              nullptr, nullptr, workspace, fb, &nparts, s))
     return rc;
   if (!fb) return LBM_OK;
   const ForwardScratch W = forward_scratch((long long)nx * ny);
-  return launch_gate(g_src, g_dst, nx, ny, tau, 0, 0.0f, fb, at(workspace, W.pmass2),
+  return launch_gate(g_src, g_dst, nx, ny, tau, 0, 0.0f, fb, at(workspace, W.pmass),
+                     at(workspace, W.pflag), nparts, at(workspace, W.pmass2),
                      at(workspace, W.ctrl), s);
 }
 

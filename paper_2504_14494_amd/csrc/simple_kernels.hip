@@ -11,8 +11,7 @@
 // Sizes follow the corrected collision's encoder and head: 12 -> 64 -> 64
 // (ReLU) -> 10.  The parameter blob is the zero-round layout:
 //   W1[64][12] b1[64] W2[64][64] b2[64] Wh[10][64] bh[10] | mu[12] sigma[12] s_delta
-// The weight fragments (gnn_prep_kernel), the gate's decision
-// (gate_decide_last) and its fallback kernel are shared with the
+// The weight fragments (gnn_prep_kernel) and the gate kernel are shared with the
 // message-passing step; the collision epilogue is this
 // file's own, with the same arithmetic except the hardware exp2 and
 // reciprocal in the sigmoid and the relaxation rate.
@@ -23,7 +22,8 @@
 namespace gnn {
 
 // Shared with gnn_kernels.hip.
-int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, hipStream_t s);
+int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, const double *mass,
+                hipStream_t s);
 
 namespace simple {
 
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kThreads, SAVE ? kBlocksPerCuSave : kBlocksPerCu) v
     const float *__restrict__ src, float *__restrict__ dst, int batch, int nx, int ny,
     const float *__restrict__ tau_arr, float tau_s, float gx, const uint8_t *__restrict__ pack,
     FragLayout F, float *__restrict__ head_out, Q80 *__restrict__ pmass,
-    unsigned *__restrict__ pflag, SimpleSave sv, GateArgs gate, unsigned *__restrict__ chunkq) {
+    unsigned *__restrict__ pflag, SimpleSave sv, unsigned *__restrict__ chunkq) {
   __shared__ u32x4 w_s[14 * 64];   // W1 (4), W2 (8), Wh (2) fragments
   __shared__ f32x4 b_s[9 * 4];     // b1 (4), b2 (4), bh (1), per channel group
   __shared__ __attribute__((aligned(16))) uint32_t slot_s[kWaves][64 * kSlot];
@@ -330,37 +330,17 @@ __global__ __launch_bounds__(kThreads, SAVE ? kBlocksPerCuSave : kBlocksPerCu) v
     wave_lds_sync();
   }
 
-  // every wave is done with its slots: the reduction reuses them
+  // every wave is done with its slots: the sum reuses them
   __syncthreads();
-  Q80 *red_m = (Q80 *)&slot_s[0][0];
-  unsigned *red_f = &slot_s[0][0] + 4 * kThreads;
-  static_assert(5 * kThreads <= kWaves * 64 * kSlot, "reduction fits in the slots");
-  red_m[threadIdx.x] = mass_acc;
-  red_f[threadIdx.x] = flag_acc;
-  __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      red_m[threadIdx.x] = q80_add(red_m[threadIdx.x], red_m[threadIdx.x + s]);
-      red_f[threadIdx.x] |= red_f[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    pmass[blockIdx.x] = red_m[0];
-    pflag[blockIdx.x] = red_f[0];
-  }
-  if constexpr (PULL) {
-    if (gate.ctrl)
-      gate_decide_last<kThreads>(gate, pmass, pflag, (int)gridDim.x, (double)nx * ny, red_m,
-                                 red_f);
-  }
+  store_partial((PartialSlot *)&slot_s[0][0], mass_acc, flag_acc, pmass, pflag);
 }
 
 }  // namespace simple
 
 // The gate's fallback kernel, shared with the message-passing step (gnn_kernels.hip).
 int launch_gate(const float *g_src, float *g_dst, int nx, int ny, float tau, int walls,
-                float gx, const lbm_fallback *fb, void *pmass2, void *ctrl, hipStream_t s);
+                float gx, const lbm_fallback *fb, const void *pmass, const void *pflag,
+                int nparts, void *pmass2, void *ctrl, hipStream_t s);
 
 }  // namespace gnn
 
@@ -376,12 +356,12 @@ static inline void *at_(void *base, size_t off) { return (uint8_t *)base + off; 
 static int launch_simple(bool pull, bool walls, float gx, const float *src, float *dst,
                          int batch, int nx, int ny, const float *tau_arr, float tau,
                          const float *params, float *head_out, void *saved, void *ws,
-                         const lbm_fallback *fb, hipStream_t s) {
+                         const lbm_fallback *fb, int *nparts, hipStream_t s) {
   const FragLayout F = frag_layout(0);
   const SimpleScratch W = simple_scratch();
   uint8_t *pack = (uint8_t *)at_(ws, W.pack);
   unsigned *ctrl = (unsigned *)at_(ws, W.ctrl);
-  if (int rc = launch_prep(params, 0, pack, ctrl, s)) return rc;
+  if (int rc = launch_prep(params, 0, pack, ctrl, fb ? fb->mass : nullptr, s)) return rc;
   const long long chunks = (long long)batch * ny * ((nx + 63) / 64);
   long long blocks = (chunks + simple::kWaves - 1) / simple::kWaves;
   // the resident blocks; their waves draw the chunks from a counter
@@ -389,10 +369,9 @@ static int launch_simple(bool pull, bool walls, float gx, const float *src, floa
                   (saved && !pull ? simple::kBlocksPerCuSave : simple::kBlocksPerCu);
   if (cap > kMaxGnnBlocks) cap = kMaxGnnBlocks;
   const int nb = (int)(blocks < cap ? blocks : cap);
+  *nparts = nb;
   Q80 *pm = (Q80 *)at_(ws, W.pmass);
   unsigned *pf = (unsigned *)at_(ws, W.pflag);
-  GateArgs gate{};
-  if (fb && pull) gate = GateArgs{ctrl, fb->drift_threshold, fb->flags, fb->n_fallback, fb->mass};
   simple::SimpleSave sv{};
   if (saved) {
     const SavedLayout SL = saved_layout((long long)batch * nx * ny, 0);
@@ -404,19 +383,19 @@ static int launch_simple(bool pull, bool walls, float gx, const float *src, floa
   if (pull && walls)
     hipLaunchKernelGGL((simple::simple_step_kernel<true, false, true>), dim3(nb),
                        dim3(simple::kThreads), 0, s, src, dst, batch, nx, ny, tau_arr, tau, gx,
-                       pack, F, head_out, pm, pf, sv, gate, ctrl + kCtrlChunkQueue);
+                       pack, F, head_out, pm, pf, sv, ctrl + kCtrlChunkQueue);
   else if (pull)
     hipLaunchKernelGGL((simple::simple_step_kernel<true, false, false>), dim3(nb),
                        dim3(simple::kThreads), 0, s, src, dst, batch, nx, ny, tau_arr, tau, 0.0f,
-                       pack, F, head_out, pm, pf, sv, gate, ctrl + kCtrlChunkQueue);
+                       pack, F, head_out, pm, pf, sv, ctrl + kCtrlChunkQueue);
   else if (saved)
     hipLaunchKernelGGL((simple::simple_step_kernel<false, true, false>), dim3(nb),
                        dim3(simple::kThreads), 0, s, src, dst, batch, nx, ny, tau_arr, tau, 0.0f,
-                       pack, F, head_out, pm, pf, sv, gate, ctrl + kCtrlChunkQueue);
+                       pack, F, head_out, pm, pf, sv, ctrl + kCtrlChunkQueue);
   else
     hipLaunchKernelGGL((simple::simple_step_kernel<false, false, false>), dim3(nb),
                        dim3(simple::kThreads), 0, s, src, dst, batch, nx, ny, tau_arr, tau, 0.0f,
-                       pack, F, head_out, pm, pf, sv, gate, ctrl + kCtrlChunkQueue);
+                       pack, F, head_out, pm, pf, sv, ctrl + kCtrlChunkQueue);
   return launch_check("simple_step_kernel");
 }
 
@@ -442,8 +421,9 @@ extern "C" int simple_forward(const float *g_pre, float *g_post, int batch, int 
   if (saved && saved_bytes < saved_need)
     return fail(LBM_EWORKSPACE, "simple_forward: saved buffer needs %zu bytes", saved_need);
   if (int rc = check_device()) return rc;
+  int nparts;
   return launch_simple(false, false, 0.0f, g_pre, g_post, batch, nx, ny, tau, 0.0f, params,
-                       head_out, saved, workspace, nullptr, (hipStream_t)stream);
+                       head_out, saved, workspace, nullptr, &nparts, (hipStream_t)stream);
 }
 
 // The fused step, periodic (walls = 0) or the channel (walls = 1, force gx).
@@ -463,12 +443,14 @@ static int step_simple(const char *who, const float *g_src, float *g_dst, int nx
     return fail(LBM_EWORKSPACE, "%s: workspace needs %zu bytes", who, simple_scratch().total);
   if (int rc = check_device()) return rc;
   hipStream_t s = (hipStream_t)stream;
+  int nparts;
   if (int rc = launch_simple(true, walls, gx, g_src, g_dst, 1, nx, ny, nullptr, tau, params,
-                             nullptr, nullptr, workspace, fb, s))
+                             nullptr, nullptr, workspace, fb, &nparts, s))
     return rc;
   if (!fb) return LBM_OK;
   const SimpleScratch W = simple_scratch();
-  return launch_gate(g_src, g_dst, nx, ny, tau, walls ? 1 : 0, gx, fb, at_(workspace, W.pmass2),
+  return launch_gate(g_src, g_dst, nx, ny, tau, walls ? 1 : 0, gx, fb, at_(workspace, W.pmass),
+                     at_(workspace, W.pflag), nparts, at_(workspace, W.pmass2),
                      at_(workspace, W.ctrl), s);
 }
 
