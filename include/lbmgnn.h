@@ -319,9 +319,10 @@ int lbm_step_simple_channel(const float *g_src, float *g_dst, int nx, int ny,
 /* The same collision alone (no streaming) on a batch of pre-collision states
  * [batch][ny][9][nx], tau: device float[batch]; head_out NULL or
  * [batch][ny][nx][10].  saved: NULL for inference, else a device buffer of
- * >= lbm_workspace_bytes(LBM_WS_GNN_SAVED, batch, nx, ny, 0) bytes that
- * receives what gnn_backward (n_rounds = 0) needs: the BF16 features, both
- * hidden layers (fragment order) and the FP32 head outputs per node. */
+ * >= lbm_workspace_bytes(LBM_WS_GNN_SAVED, batch, nx, ny, 0) bytes, to be handed
+ * to gnn_backward (n_rounds = 0).  It receives z_0 per node; this network's
+ * activations are cheaper to recompute than to store, so the backward pass
+ * forms them again from g_pre. */
 int simple_forward(const float *g_pre, float *g_post, int batch, int nx, int ny,
                    const float *tau, const float *params, float *head_out,
                    void *saved, size_t saved_bytes, void *workspace,

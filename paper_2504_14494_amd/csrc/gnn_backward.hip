@@ -2,7 +2,7 @@
 // training step (paper: Training Methodology, loss of Eq. 4): gradient of a
 // scalar loss with respect to every trainable parameter, the MSE loss and an
 // Adam update.  n_rounds >= 1 is the message-passing network (GELU);
-// n_rounds = 0 the per-node network of Fig. 2 (ReLU): head, then encoder.
+// n_rounds = 0 the per-node network of Fig. 2 (ReLU, simple_backward.hip).
 //
 // The forward saved, per node, the BF16 values the MFMAs consumed: features
 // x, first encoder layer e1, node states h_0..h_R and summed messages a_1..a_R,
@@ -26,175 +26,13 @@
 // the nodes it visits, and writes one FP32 partial per wave; a last kernel
 // sums the partials of the fixed grid in a fixed order, so the gradient is
 // bitwise reproducible.
-#include "gnn_common.hpp"
-#include "lbm_common.hpp"
+#include "bwd_common.hpp"
 
 namespace gnn {
 
-using lbm::cx;
-using lbm::cy;
-
-constexpr int kBT = 256;            // threads per block
-constexpr int kPitch = 40;          // BF16 per staged row: 32 nodes + padding
-
-// ------------------------------------------------------------ helpers ---
-
-struct Pos {
-  int b, y, x;          // x clamped into the lattice for loads
-  bool valid;
-  size_t node;
-};
-
-__device__ __forceinline__ Pos group_pos(long long grp, long long ngroups, int n, int nx, int ny,
-                                         long long gxn) {
-  Pos P;
-  bool in = grp < ngroups;
-  long long g = in ? grp : 0;
-  int xg = (int)(g % gxn);
-  long long by = g / gxn;
-  P.y = (int)(by % ny);
-  P.b = (int)(by / ny);
-  int x = xg * 16 + n;
-  P.valid = in && x < nx;
-  P.x = x < nx ? x : x % nx;
-  P.node = ((size_t)P.b * ny + P.y) * nx + P.x;
-  return P;
-}
-
-// FP32 per-node vectors in accumulator order: lane (n, q) owns the 64 bytes
-// at q * 16 floats (row tiles t = 0..3, 4 values each).
-__device__ __forceinline__ void load_acc(const float *buf, size_t node, int q, f32x4 (&v)[4]) {
-  const f32x4 *p = (const f32x4 *)(buf + node * HID) + q * 4;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) v[t] = p[t];
-}
-__device__ __forceinline__ void store_acc(float *buf, size_t node, int q, const f32x4 (&v)[4]) {
-  f32x4 *p = (f32x4 *)(buf + node * HID) + q * 4;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) p[t] = v[t];
-}
-__device__ __forceinline__ void add_acc(float *buf, size_t node, int q, const f32x4 (&v)[4]) {
-  f32x4 *p = (f32x4 *)(buf + node * HID) + q * 4;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) p[t] = p[t] + v[t];
-}
-
-// BF16 node state fragments (fragment order, see gnn_common.hpp).
-__device__ __forceinline__ void load_frags(const uint16_t *h, size_t node, int q, u32x4 (&f)[2]) {
-  const u32x4 *p = (const u32x4 *)(h + node * HID);
-  f[0] = p[q];
-  f[1] = p[4 + q];
-}
-
-__device__ __forceinline__ f32x4 unpack_lo(u32x4 v) {
-  return f32x4{bf16_to_f32(v.x & 0xffffu), bf16_to_f32(v.x >> 16), bf16_to_f32(v.y & 0xffffu),
-               bf16_to_f32(v.y >> 16)};
-}
-__device__ __forceinline__ f32x4 unpack_hi(u32x4 v) {
-  return f32x4{bf16_to_f32(v.z & 0xffffu), bf16_to_f32(v.z >> 16), bf16_to_f32(v.w & 0xffffu),
-               bf16_to_f32(v.w >> 16)};
-}
-
-__device__ __forceinline__ uint16_t bf16_bits(float v) {
-  __bf16 b = (__bf16)v;
-  return __builtin_bit_cast(uint16_t, b);
-}
-
-// Staging of one value per (channel row, node column), BF16, channel-major.
-// Accumulator-layout vectors: lane (n, q) holds channels 16 t + 4 q + e.
-__device__ __forceinline__ void stage_acc(uint16_t *rows, const f32x4 (&v)[4], int q, int col,
-                                          int row0 = 0) {
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    rows[(row0 + 16 * t + 4 * q + 0) * kPitch + col] = bf16_bits(v[t].x);
-    rows[(row0 + 16 * t + 4 * q + 1) * kPitch + col] = bf16_bits(v[t].y);
-    rows[(row0 + 16 * t + 4 * q + 2) * kPitch + col] = bf16_bits(v[t].z);
-    rows[(row0 + 16 * t + 4 * q + 3) * kPitch + col] = bf16_bits(v[t].w);
-  }
-}
-// Fragment-order vectors: element j of k-step s is channel c(s, q, j).
-__device__ __forceinline__ void stage_frag(uint16_t *rows, const u32x4 (&f)[2], int q, int col,
-                                           int row0 = 0) {
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const uint32_t w[4] = {f[s].x, f[s].y, f[s].z, f[s].w};
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      rows[(row0 + frag_channel(s, q, j)) * kPitch + col] =
-          (uint16_t)((j & 1) ? (w[j >> 1] >> 16) : (w[j >> 1] & 0xffffu));
-  }
-}
-__device__ __forceinline__ void stage_zero(uint16_t *rows, int nrows, int lane) {
-  for (int k = lane; k < nrows * kPitch / 2; k += 64) ((uint32_t *)rows)[k] = 0u;
-}
-
-// acc[mt][ct] += D^T-slice x A over the 32 staged nodes: rows of d are the
-// output channels (16 mt + ...), rows of a the input channels (16 ct + ...).
-template <int MT, int CT>
-__device__ __forceinline__ void dw_mma(f32x4 (&acc)[MT][CT], const uint16_t *d,
-                                       const uint16_t *a, int lane) {
-  const int r = lane & 15, q = lane >> 4;
-  u32x4 A[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) A[mt] = *(const u32x4 *)(d + (16 * mt + r) * kPitch + 8 * q);
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    u32x4 B = *(const u32x4 *)(a + (16 * ct + r) * kPitch + 8 * q);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt][ct] = mfma(A[mt], B, acc[mt][ct]);
-  }
-}
-
-// Writes a dW accumulator block to this wave's partial: element
-// (row 16 mt + 4 q + e, column col0 + 16 ct + (lane & 15)) of a row-major
-// [rows][ld] matrix at `base`.
-template <int MT, int CT>
-__device__ __forceinline__ void write_dw(float *part, size_t base, int ld, int col0, int nrows,
-                                         int ncols, const f32x4 (&acc)[MT][CT], int lane) {
-  const int c = lane & 15, q = lane >> 4;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      const float v[4] = {acc[mt][ct].x, acc[mt][ct].y, acc[mt][ct].z, acc[mt][ct].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        int row = 16 * mt + 4 * q + e, col = 16 * ct + c;
-        if (row < nrows && col < ncols) part[base + (size_t)row * ld + col0 + col] = v[e];
-      }
-    }
-}
-
-// Sums, over the 16 node lanes, per-lane accumulator-layout vectors (channel
-// 16 t + 4 q + e) and writes the 64 channel totals to part[base + stride * ch].
-__device__ __forceinline__ void write_vec(float *part, size_t base, int stride,
-                                          const f32x4 (&v)[4], float *red, int lane) {
-  const int q = lane >> 4;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    red[lane * 17 + 4 * t + 0] = v[t].x;
-    red[lane * 17 + 4 * t + 1] = v[t].y;
-    red[lane * 17 + 4 * t + 2] = v[t].z;
-    red[lane * 17 + 4 * t + 3] = v[t].w;
-  }
-  wave_lds_sync();
-  const int k = lane & 15;
-  float s = 0.0f;
-  for (int n = 0; n < 16; ++n) s += red[(16 * q + n) * 17 + k];
-  const int ch = 16 * (k >> 2) + 4 * q + (k & 3);
-  part[base + (size_t)stride * ch] = s;
-  wave_lds_sync();
-}
-
-// s_waitcnt vmcnt(0) with expcnt and lgkmcnt left at their maximum.
-constexpr int kBwdWaitVmcnt0 = 0x0F70;
-
-template <int DR, int AR>
-struct Stage {
-  uint16_t d[DR * kPitch];
-  uint16_t a[AR * kPitch];
-  float red[64 * 17];
-};
+// simple_backward.hip
+int launch_simple_backward(const float *G, const float *g_pre, const float *tau, const float *z0,
+                           int batch, int nx, int ny, const uint8_t *pack, float *part, hipStream_t s);
 
 // ------------------------------------------------------------ the head ---
 
@@ -221,7 +59,7 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
   // One wave per SIMD: the next chunk's inputs (both groups) are loaded while
   // this chunk is computed; one explicit wait before the chunk's first store
   // covers them.
-  float g_nx[2][9], G_nx[2][9], z_nx[2][NOUT], tau_nx[2];
+  float g_nx[2][9], G_nx[2][9], z_nx[2], tau_nx[2];
   u32x4 hf_nx[2][2];
   auto prefetch = [&](long long cc) {
 #pragma unroll
@@ -233,8 +71,7 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
         g_nx[hh][i] = gpre[lat + lbm::pidx(nx, P.y, i, P.x)];
         G_nx[hh][i] = G[lat + lbm::pidx(nx, P.y, i, P.x)];
       }
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) z_nx[hh][k] = save_z[P.node * 12 + k];
+      z_nx[hh] = save_z[P.node * 12];
       tau_nx[hh] = tau[P.b];
       load_frags(hR, P.node, q, hf_nx[hh]);
     }
@@ -242,7 +79,7 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
   if (w < nchunks) prefetch(w);
   __builtin_amdgcn_s_waitcnt(kBwdWaitVmcnt0);
   for (long long c = w; c < nchunks; c += kBwdWaves) {
-    float gc[2][9], Gc[2][9], zc[2][NOUT], tauc[2];
+    float gc[2][9], Gc[2][9], zc[2], tauc[2];
     u32x4 hfc[2][2];
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
@@ -251,8 +88,7 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
         gc[hh][i] = g_nx[hh][i];
         Gc[hh][i] = G_nx[hh][i];
       }
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) zc[hh][k] = z_nx[hh][k];
+      zc[hh] = z_nx[hh];
       tauc[hh] = tau_nx[hh];
       hfc[hh][0] = hf_nx[hh][0];
       hfc[hh][1] = hf_nx[hh][1];
@@ -263,25 +99,9 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
       Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
       float(&g)[9] = gc[half];
       float(&Gi)[9] = Gc[half];
-      float(&z)[NOUT] = zc[half];
-      const lbm::Moments<float> M = lbm::node_moments(g);
-      const float s = 1.0f / (1.0f + expf(-z[0]));
-      const float tadj = 0.5f + s;
-      const float tb = tauc[half];
-      float dta = 0.0f, m0 = 0.0f, mx = 0.0f, my = 0.0f;
-#pragma unroll
-      for (int i = 0; i < 9; ++i) {
-        dta += Gi[i] * (g[i] - lbm::geq_of(i, M));
-        m0 += Gi[i];
-        mx += float(cx(i)) * Gi[i];
-        my += float(cy(i)) * Gi[i];
-      }
       float dz[NOUT];
-      dz[0] = dta / (tb * tadj * tadj) * s * (1.0f - s);
-#pragma unroll
-      for (int i = 0; i < 9; ++i)
-        dz[1 + i] = sdelta * (Gi[i] - m0 * (1.0f / 9.0f) - float(cx(i)) * mx * (1.0f / 6.0f) -
-                              float(cy(i)) * my * (1.0f / 6.0f));
+      head_gradient(g, Gi, sdelta, dz);
+      dz[0] = tau_gradient(dz[0], zc[half], tauc[half]);
       if (!P.valid)
 #pragma unroll
         for (int k = 0; k < NOUT; ++k) dz[k] = 0.0f;
@@ -755,19 +575,10 @@ __global__ __launch_bounds__(kBT) void bwd_edge_send_kernel(
 
 // ------------------------------------------------------------- encoder ---
 
-// Derivative of the activation at the recomputed pre-activation: GELU (tanh
-// form) for the message-passing network, ReLU (1 for p > 0, else 0) for the
-// per-node network of Fig. 2.
-template <int ACT>
-__device__ __forceinline__ f32x4 act_grad4(f32x4 p) {
-  if constexpr (ACT == 0)
-    return f32x4{gelu_grad(p.x), gelu_grad(p.y), gelu_grad(p.z), gelu_grad(p.w)};
-  else
-    return f32x4{p.x > 0.0f ? 1.0f : 0.0f, p.y > 0.0f ? 1.0f : 0.0f, p.z > 0.0f ? 1.0f : 0.0f,
-                 p.w > 0.0f ? 1.0f : 0.0f};
+__device__ __forceinline__ f32x4 gelu_grad4(f32x4 p) {
+  return f32x4{gelu_grad(p.x), gelu_grad(p.y), gelu_grad(p.z), gelu_grad(p.w)};
 }
 
-template <int ACT>
 __global__ __launch_bounds__(kBT) void bwd_encoder_kernel(
     const float *__restrict__ dh0, const uint16_t *__restrict__ sx, const uint16_t *__restrict__ se1,
     int batch, int nx, int ny, const uint8_t *__restrict__ pack, FragLayout F, BlobLayout L,
@@ -828,7 +639,7 @@ __global__ __launch_bounds__(kBT) void bwd_encoder_kernel(
       for (int t = 0; t < 4; ++t) {
         f32x4 p = mfma(w2[t][0], e1[0], b2[t]);
         p = mfma(w2[t][1], e1[1], p);
-        dp2[t] = P.valid ? G[t] * act_grad4<ACT>(p) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        dp2[t] = P.valid ? G[t] * gelu_grad4(p) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         s2[t] += dp2[t];
       }
       const u32x4 dpb[2] = {frag_from_acc(dp2[0], dp2[1]), frag_from_acc(dp2[2], dp2[3])};
@@ -838,21 +649,14 @@ __global__ __launch_bounds__(kBT) void bwd_encoder_kernel(
         f32x4 de1 = mfma(w2t_s[(2 * t) * 64 + wo], dpb[0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
         de1 = mfma(w2t_s[(2 * t + 1) * 64 + wo], dpb[1], de1);
         f32x4 p1 = mfma(w1_s[t * 64 + wo], xb, b1[t]);
-        dp1[t] = de1 * act_grad4<ACT>(p1);
+        dp1[t] = de1 * gelu_grad4(p1);
         s1[t] += dp1[t];
       }
       const int col = 16 * half + n;
       stage_acc(S.d, dp2, q, col);
       stage_frag(S.a, e1, q, col);
       stage_acc(D1, dp1, q, col);
-      // feature rows k = 8 q + j (12 used; rows 12..15 hold zero features)
-      if (q < 2) {
-        const uint32_t wv[4] = {xb.x, xb.y, xb.z, xb.w};
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          X1[(8 * q + j) * kPitch + col] =
-              (uint16_t)((j & 1) ? (wv[j >> 1] >> 16) : (wv[j >> 1] & 0xffffu));
-      }
+      stage_rows16(X1, xb, q, col);
     }
     wave_lds_sync();
     dw_mma<4, 4>(acc2, S.d, S.a, lane);
@@ -879,6 +683,38 @@ __global__ __launch_bounds__(kReduceThreads) void bwd_reduce_kernel(
 #pragma unroll 32
   for (int w = 0; w < kBwdWaves; ++w) s += part[(size_t)w * nparam + p];
   grad[p] = s;
+}
+
+// The same sum for a network of few parameters, whose 88 waves above wait
+// for memory 32 times (22 us for the 5,642 parameters of the per-node network):
+// a block takes 32 parameters, brings all of their partials to LDS with 64 loads
+// in flight per thread, and 32 lanes add them in wave order (13).  With
+// more parameters than CUs x 32 the blocks come in several rounds and the
+// kernel above is the better one (38,922: 41 us, 64 and more here).
+constexpr int kFewParams = 32;
+__global__ __launch_bounds__(kBT) void bwd_reduce_few_kernel(const float *__restrict__ part,
+                                                             size_t nparam,
+                                                             float *__restrict__ grad) {
+  __shared__ float v_s[kBwdWaves * kFewParams];
+  const int k = threadIdx.x % kFewParams, w0 = threadIdx.x / kFewParams;
+  constexpr int kStride = kBT / kFewParams, kPer = 64;
+  const size_t p = (size_t)blockIdx.x * kFewParams + k;
+  const size_t pc = p < nparam ? p : nparam - 1;
+#pragma unroll 1
+  for (int r = w0; r < kBwdWaves; r += kPer * kStride) {
+    float v[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) v[j] = part[(size_t)(r + j * kStride) * nparam + pc];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) v_s[(r + j * kStride) * kFewParams + k] = v[j];
+  }
+  static_assert(kBwdWaves % (kPer * kStride) == 0, "whole turns");
+  __syncthreads();
+  if (threadIdx.x >= kFewParams) return;
+  float s = 0.0f;
+#pragma unroll 32
+  for (int w = 0; w < kBwdWaves; ++w) s += v_s[w * kFewParams + k];
+  if (p < nparam) grad[p] = s;
 }
 
 // ------------------------------------------------------------ MSE, Adam ---
@@ -1018,37 +854,42 @@ extern "C" int gnn_backward(const float *dL_dgpost, const float *g_pre, const vo
   auto hsaved = [&](int r) { return (const uint16_t *)at(saved, SL.h + (size_t)r * hstride); };
   auto asaved = [&](int r) { return (const uint16_t *)at(saved, SL.agg + (size_t)r * hstride); };
 
-  int cur = 0;
-  hipLaunchKernelGGL(bwd_head_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dL_dgpost, g_pre, tau,
-                     (const float *)at(saved, SL.z), hsaved(R), batch, nx, ny, pack, F, L,
-                     dh[cur], part);
-  if (int rc = launch_check("bwd_head_kernel")) return rc;
-  for (int r = R - 1; r >= 0; --r) {
-    float *din = dh[cur], *dout = dh[cur ^ 1];
-    hipLaunchKernelGGL(bwd_node_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, din, hsaved(r),
-                       asaved(r), batch, nx, ny, r, pack, F, L, dout, dagg, part);
-    if (int rc = launch_check("bwd_node_kernel")) return rc;
-    hipLaunchKernelGGL(bwd_edge_recv_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dagg, hsaved(r),
-                       batch, nx, ny, r, pack, F, L, dq, part);
-    if (int rc = launch_check("bwd_edge_recv_kernel")) return rc;
-    hipLaunchKernelGGL(bwd_edge_send_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dq, hsaved(r),
-                       batch, nx, ny, r, pack, F, L, dagg, dout, part);
-    if (int rc = launch_check("bwd_edge_send_kernel")) return rc;
-    cur ^= 1;
+  if (R == 0) {  // the per-node network, one kernel
+    if (int rc = launch_simple_backward(dL_dgpost, g_pre, tau, (const float *)saved, batch,
+                                        nx, ny, pack, part, s))
+      return rc;
+  } else {
+    int cur = 0;
+    hipLaunchKernelGGL(bwd_head_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dL_dgpost, g_pre, tau,
+                       (const float *)at(saved, SL.z), hsaved(R), batch, nx, ny, pack, F, L,
+                       dh[cur], part);
+    if (int rc = launch_check("bwd_head_kernel")) return rc;
+    for (int r = R - 1; r >= 0; --r) {
+      float *din = dh[cur], *dout = dh[cur ^ 1];
+      hipLaunchKernelGGL(bwd_node_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, din, hsaved(r),
+                         asaved(r), batch, nx, ny, r, pack, F, L, dout, dagg, part);
+      if (int rc = launch_check("bwd_node_kernel")) return rc;
+      hipLaunchKernelGGL(bwd_edge_recv_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dagg, hsaved(r),
+                         batch, nx, ny, r, pack, F, L, dq, part);
+      if (int rc = launch_check("bwd_edge_recv_kernel")) return rc;
+      hipLaunchKernelGGL(bwd_edge_send_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dq, hsaved(r),
+                         batch, nx, ny, r, pack, F, L, dagg, dout, part);
+      if (int rc = launch_check("bwd_edge_send_kernel")) return rc;
+      cur ^= 1;
+    }
+    hipLaunchKernelGGL(bwd_encoder_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dh[cur],
+                       (const uint16_t *)at(saved, SL.x), (const uint16_t *)at(saved, SL.e1),
+                       batch, nx, ny, pack, F, L, part);
+    if (int rc = launch_check("bwd_encoder_kernel")) return rc;
   }
-  // n_rounds = 0 is the per-node network of Fig. 2, which uses ReLU
-  if (R == 0)
-    hipLaunchKernelGGL(bwd_encoder_kernel<1>, dim3(kBwdBlocks), dim3(kBT), 0, s, dh[cur],
-                       (const uint16_t *)at(saved, SL.x), (const uint16_t *)at(saved, SL.e1),
-                       batch, nx, ny, pack, F, L, part);
+  if (L.nparam <= (size_t)kFewParams * lbm::device_cus())
+    hipLaunchKernelGGL(bwd_reduce_few_kernel,
+                       dim3((unsigned)((L.nparam + kFewParams - 1) / kFewParams)), dim3(kBT), 0, s,
+                       part, L.nparam, grad);
   else
-    hipLaunchKernelGGL(bwd_encoder_kernel<0>, dim3(kBwdBlocks), dim3(kBT), 0, s, dh[cur],
-                       (const uint16_t *)at(saved, SL.x), (const uint16_t *)at(saved, SL.e1),
-                       batch, nx, ny, pack, F, L, part);
-  if (int rc = launch_check("bwd_encoder_kernel")) return rc;
-  hipLaunchKernelGGL(bwd_reduce_kernel,
-                     dim3((unsigned)((L.nparam + kReduceThreads - 1) / kReduceThreads)),
-                     dim3(kReduceThreads), 0, s, part, L.nparam, grad);
+    hipLaunchKernelGGL(bwd_reduce_kernel,
+                       dim3((unsigned)((L.nparam + kReduceThreads - 1) / kReduceThreads)),
+                       dim3(kReduceThreads), 0, s, part, L.nparam, grad);
   return launch_check("bwd_reduce_kernel");
 }
 

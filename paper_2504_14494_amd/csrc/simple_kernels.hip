@@ -18,6 +18,7 @@
 #include "channel_common.hpp"
 #include "gnn_common.hpp"
 #include "lbm_common.hpp"
+#include "simple_common.hpp"
 
 namespace gnn {
 
@@ -32,39 +33,6 @@ using lbm::cy;
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-
-// ReLU of eight accumulators, rounded to a BF16 B-operand fragment.  Rounding
-// keeps the sign, so ReLU after rounding equals rounding after ReLU; on the
-// packed BF16 bits ReLU is a signed 16-bit max with zero (negative values,
-// -0 included, have the sign bit set), two values per instruction.
-__device__ __forceinline__ uint32_t relu_bf16x2(uint32_t v) {
-  s16x2 h = __builtin_bit_cast(s16x2, v);
-  h = __builtin_elementwise_max(h, s16x2{0, 0});
-  return __builtin_bit_cast(uint32_t, h);
-}
-
-__device__ __forceinline__ u32x4 relu_frag(f32x4 lo, f32x4 hi) {
-  u32x4 r = frag_from_acc(lo, hi);
-  return u32x4{relu_bf16x2(r.x), relu_bf16x2(r.y), relu_bf16x2(r.z), relu_bf16x2(r.w)};
-}
-
-// Moments of a node, as lbm::node_moments (same sums, same order) but with
-// the hardware reciprocal of rho (about 1 ulp); what only the collision needs
-// is left to it.
-__device__ __forceinline__ lbm::Moments<float> moments(const float (&g)[9]) {
-#pragma clang fp contract(off)
-  lbm::Moments<float> M = {};
-  M.drho = ((g[0] + (g[1] + g[3])) + (g[2] + g[4])) + ((g[5] + g[7]) + (g[6] + g[8]));
-  M.jx = (g[1] - g[3]) + ((g[5] - g[7]) + (g[8] - g[6]));
-  M.jy = (g[2] - g[4]) + ((g[5] - g[7]) + (g[6] - g[8]));
-  M.rho = 1.0f + M.drho;
-  M.inv = __builtin_amdgcn_rcpf(M.rho);
-  M.u = M.jx * M.inv;
-  M.v = M.jy * M.inv;
-  return M;
-}
 
 // Eq. 3 with the projected correction at one node, given its moments (with
 // Guo's velocity where there is a force).  The sigmoid and the relaxation rate use the
@@ -109,25 +77,15 @@ __device__ __forceinline__ void collide(float (&g)[9], const float (&z)[NOUT], f
 constexpr int kSlot = 12;   // dwords per node: 8 for the features, then 10 head outputs
 
 constexpr int kBlocksPerCu = 4;   // resident blocks (LDS 27 KB, <= 128 registers)
-constexpr int kBlocksPerCuSave = 3;   // the training forward, which also stores activations
-
-// What a training forward keeps per node for the backward pass: the BF16
-// operands the MFMAs consumed (features, both hidden layers, fragment order)
-// and the FP32 head outputs; the layout of gnn_forward's saved buffer for
-// zero rounds.
-struct SimpleSave {
-  uint16_t *x, *e1, *h0;
-  float *z;
-};
 
 // WALLS (with PULL): the channel step, halfway bounce-back at rows 0 and
 // ny - 1 and the body force rho * gx along x.
-template <bool PULL, bool SAVE, bool WALLS>
-__global__ __launch_bounds__(kThreads, SAVE ? kBlocksPerCuSave : kBlocksPerCu) void simple_step_kernel(
+template <bool PULL, bool WALLS>
+__global__ __launch_bounds__(kThreads, kBlocksPerCu) void simple_step_kernel(
     const float *__restrict__ src, float *__restrict__ dst, int batch, int nx, int ny,
     const float *__restrict__ tau_arr, float tau_s, float gx, const uint8_t *__restrict__ pack,
     FragLayout F, float *__restrict__ head_out, Q80 *__restrict__ pmass,
-    unsigned *__restrict__ pflag, SimpleSave sv, unsigned *__restrict__ chunkq) {
+    unsigned *__restrict__ pflag, float *__restrict__ save_z0, unsigned *__restrict__ chunkq) {
   __shared__ u32x4 w_s[14 * 64];   // W1 (4), W2 (8), Wh (2) fragments
   __shared__ f32x4 b_s[9 * 4];     // b1 (4), b2 (4), bh (1), per channel group
   __shared__ __attribute__((aligned(16))) uint32_t slot_s[kWaves][64 * kSlot];
@@ -261,22 +219,6 @@ __global__ __launch_bounds__(kThreads, SAVE ? kBlocksPerCuSave : kBlocksPerCu) v
         hb[h][0] = relu_frag(a[h][0], a[h][1]);
         hb[h][1] = relu_frag(a[h][2], a[h][3]);
       }
-      if constexpr (SAVE) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int xs = xc * 64 + 16 * (2 * pair + h) + n;
-          if (xs < nx) {
-            const size_t node = ((size_t)b * ny + y) * nx + xs;
-            if (q < 2) ((u32x4 *)(sv.x + node * 16))[q] = xb[h];
-            u32x4 *de = (u32x4 *)(sv.e1 + node * HID);
-            de[q] = e1[h][0];
-            de[4 + q] = e1[h][1];
-            u32x4 *dh = (u32x4 *)(sv.h0 + node * HID);
-            dh[q] = hb[h][0];
-            dh[4 + q] = hb[h][1];
-          }
-        }
-      }
       const u32x4 w12 = w[12 * 64], w13 = w[13 * 64];
       const f32x4 b8 = bs[8 * 4];
 #pragma unroll
@@ -317,14 +259,11 @@ __global__ __launch_bounds__(kThreads, SAVE ? kBlocksPerCuSave : kBlocksPerCu) v
       const unsigned bad = (fmin >= 0.0f && fabsf(msum) < INFINITY) ? 0u : 1u;
       mass_acc = q80_add_f32(mass_acc, msum);
       flag_acc |= bad;
+      // what a training forward keeps for the backward pass
+      if (save_z0) save_z0[((size_t)b * ny + y) * nx + x] = z[0];
       if (head_out) {
         const size_t node = ((size_t)b * ny + y) * nx + x;
         for (int k = 0; k < NOUT; ++k) head_out[node * NOUT + k] = z[k];
-      }
-      if constexpr (SAVE) {
-        const size_t node = ((size_t)b * ny + y) * nx + x;
-#pragma unroll
-        for (int k = 0; k < NOUT; ++k) sv.z[node * 12 + k] = z[k];
       }
     }
     wave_lds_sync();
@@ -355,7 +294,7 @@ static inline void *at_(void *base, size_t off) { return (uint8_t *)base + off; 
 // channel step (with pull), body force rho * gx along x.
 static int launch_simple(bool pull, bool walls, float gx, const float *src, float *dst,
                          int batch, int nx, int ny, const float *tau_arr, float tau,
-                         const float *params, float *head_out, void *saved, void *ws,
+                         const float *params, float *head_out, float *save_z0, void *ws,
                          const lbm_fallback *fb, int *nparts, hipStream_t s) {
   const FragLayout F = frag_layout(0);
   const SimpleScratch W = simple_scratch();
@@ -365,37 +304,24 @@ static int launch_simple(bool pull, bool walls, float gx, const float *src, floa
   const long long chunks = (long long)batch * ny * ((nx + 63) / 64);
   long long blocks = (chunks + simple::kWaves - 1) / simple::kWaves;
   // the resident blocks; their waves draw the chunks from a counter
-  long long cap = (long long)lbm::device_cus() *
-                  (saved && !pull ? simple::kBlocksPerCuSave : simple::kBlocksPerCu);
+  long long cap = (long long)lbm::device_cus() * simple::kBlocksPerCu;
   if (cap > kMaxGnnBlocks) cap = kMaxGnnBlocks;
   const int nb = (int)(blocks < cap ? blocks : cap);
   *nparts = nb;
   Q80 *pm = (Q80 *)at_(ws, W.pmass);
   unsigned *pf = (unsigned *)at_(ws, W.pflag);
-  simple::SimpleSave sv{};
-  if (saved) {
-    const SavedLayout SL = saved_layout((long long)batch * nx * ny, 0);
-    sv.x = (uint16_t *)at_(saved, SL.x);
-    sv.e1 = (uint16_t *)at_(saved, SL.e1);
-    sv.h0 = (uint16_t *)at_(saved, SL.h);
-    sv.z = (float *)at_(saved, SL.z);
-  }
   if (pull && walls)
-    hipLaunchKernelGGL((simple::simple_step_kernel<true, false, true>), dim3(nb),
+    hipLaunchKernelGGL((simple::simple_step_kernel<true, true>), dim3(nb),
                        dim3(simple::kThreads), 0, s, src, dst, batch, nx, ny, tau_arr, tau, gx,
-                       pack, F, head_out, pm, pf, sv, ctrl + kCtrlChunkQueue);
+                       pack, F, head_out, pm, pf, save_z0, ctrl + kCtrlChunkQueue);
   else if (pull)
-    hipLaunchKernelGGL((simple::simple_step_kernel<true, false, false>), dim3(nb),
+    hipLaunchKernelGGL((simple::simple_step_kernel<true, false>), dim3(nb),
                        dim3(simple::kThreads), 0, s, src, dst, batch, nx, ny, tau_arr, tau, 0.0f,
-                       pack, F, head_out, pm, pf, sv, ctrl + kCtrlChunkQueue);
-  else if (saved)
-    hipLaunchKernelGGL((simple::simple_step_kernel<false, true, false>), dim3(nb),
-                       dim3(simple::kThreads), 0, s, src, dst, batch, nx, ny, tau_arr, tau, 0.0f,
-                       pack, F, head_out, pm, pf, sv, ctrl + kCtrlChunkQueue);
+                       pack, F, head_out, pm, pf, save_z0, ctrl + kCtrlChunkQueue);
   else
-    hipLaunchKernelGGL((simple::simple_step_kernel<false, false, false>), dim3(nb),
+    hipLaunchKernelGGL((simple::simple_step_kernel<false, false>), dim3(nb),
                        dim3(simple::kThreads), 0, s, src, dst, batch, nx, ny, tau_arr, tau, 0.0f,
-                       pack, F, head_out, pm, pf, sv, ctrl + kCtrlChunkQueue);
+                       pack, F, head_out, pm, pf, save_z0, ctrl + kCtrlChunkQueue);
   return launch_check("simple_step_kernel");
 }
 
@@ -423,7 +349,7 @@ extern "C" int simple_forward(const float *g_pre, float *g_post, int batch, int 
   if (int rc = check_device()) return rc;
   int nparts;
   return launch_simple(false, false, 0.0f, g_pre, g_post, batch, nx, ny, tau, 0.0f, params,
-                       head_out, saved, workspace, nullptr, &nparts, (hipStream_t)stream);
+                       head_out, (float *)saved, workspace, nullptr, &nparts, (hipStream_t)stream);
 }
 
 // The fused step, periodic (walls = 0) or the channel (walls = 1, force gx).
