@@ -316,6 +316,19 @@ int lbm_step_simple_channel(const float *g_src, float *g_dst, int nx, int ny,
                             float tau, float gx, const float *params,
                             const lbm_fallback *fb, void *workspace,
                             size_t ws_bytes, void *stream);
+/* nsteps steps of lbm_step_simple (_channel) in one call, each gated if fb is
+ * given: bitwise the states, flags and decisions of as many single calls (the
+ * FP64 mass of a fallback step may differ in its last digit).
+ * 1 <= nsteps <= lbm_steps_simple_max(nx, ny), which is 1 for lattices larger
+ * than one workgroup holds. */
+int lbm_steps_simple_max(int nx, int ny);
+int lbm_steps_simple(const float *g_src, float *g_dst, int nx, int ny, float tau,
+                     const float *params, int nsteps, const lbm_fallback *fb,
+                     void *workspace, size_t ws_bytes, void *stream);
+int lbm_steps_simple_channel(const float *g_src, float *g_dst, int nx, int ny,
+                             float tau, float gx, const float *params, int nsteps,
+                             const lbm_fallback *fb, void *workspace,
+                             size_t ws_bytes, void *stream);
 /* The same collision alone (no streaming) on a batch of pre-collision states
  * [batch][ny][9][nx], tau: device float[batch]; head_out NULL or
  * [batch][ny][nx][10].  saved: NULL for inference, else a device buffer of

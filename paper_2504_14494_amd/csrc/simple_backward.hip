@@ -111,16 +111,7 @@ __global__ __launch_bounds__(kBT) void simple_backward_kernel(
         Gi[i] = G_nx[i];
       }
       if (c + kTurn < nchunks) prefetch(c + kTurn);
-      const lbm::Moments<float> M = moments(g);
-      const float raw[NFEAT] = {g[0], g[1], g[2], g[3],   g[4], g[5],
-                                g[6], g[7], g[8], M.drho, M.u,  M.v};
-      float ft[NFEAT];
-#pragma unroll
-      for (int k = 0; k < NFEAT; ++k) ft[k] = fmaf(raw[k], isg[k], nmi[k]);
-      u32x4 *o = (u32x4 *)(S.x + lane * 8);
-      o[0] = u32x4{pack_bf16(ft[0], ft[1]), pack_bf16(ft[2], ft[3]), pack_bf16(ft[4], ft[5]),
-                   pack_bf16(ft[6], ft[7])};
-      o[1] = u32x4{pack_bf16(ft[8], ft[9]), pack_bf16(ft[10], ft[11]), 0u, 0u};
+      put_features(S.x + lane * 8, g, moments(g), isg, nmi);
       head_gradient(g, Gi, sdelta, dz);
     }
     wave_lds_sync();

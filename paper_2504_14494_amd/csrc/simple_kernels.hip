@@ -34,34 +34,6 @@ using lbm::cy;
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 
-// Eq. 3 with the projected correction at one node, given its moments (with
-// Guo's velocity where there is a force).  The sigmoid and the relaxation rate use the
-// hardware exp2 and reciprocal (about 1 ulp each); z0 = 0 still gives
-// tau_adj = 1 exactly (2^0 = 1, 1/2 = 0.5).  FORCED: under the channel's body
-// force rho * gx, f^eq is taken at Guo's velocity and Guo's source is added at
-// the effective rate omega = 1 / (tau tau_adj).
-template <bool FORCED>
-__device__ __forceinline__ void collide(float (&g)[9], const float (&z)[NOUT], float tau,
-                                        float sdelta, float gx, lbm::Moments<float> M) {
-#pragma clang fp contract(off)
-  M.uu = FORCED ? __builtin_fmaf(M.v, M.v, M.u * M.u) : __builtin_fmaf(M.u, M.u, M.v * M.v);
-  M.diag = M.u + M.v;
-  M.anti = M.v - M.u;
-  constexpr float kLog2e = 1.4426950408889634f;
-  float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-z[0] * kLog2e));
-  float tau_adj = 0.5f + sig;
-  float omega = __builtin_amdgcn_rcpf(tau * tau_adj);
-  const float fx = M.rho * gx, src_scale = __builtin_fmaf(-0.5f, omega, 1.0f);
-  const Projection P(z);
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    float relaxed = lbm::relax(g[i], lbm::geq_of(i, M), omega);
-    if constexpr (FORCED)
-      relaxed = __builtin_fmaf(src_scale, lbm::guo_source<float>(i, fx, M), relaxed);
-    g[i] = __builtin_fmaf(sdelta, P(i, z), relaxed);
-  }
-}
-
 // A wave takes 64 consecutive nodes of one lattice row (ChunkQueue), one
 // node per lane for everything that is per node: the coalesced pull of the
 // nine populations (kept in registers for the collision), the moments and the
@@ -74,8 +46,6 @@ __device__ __forceinline__ void collide(float (&g)[9], const float (&z)[NOUT], f
 // read serves two blocks, which needs the registers of four blocks per CU
 // instead of five and measured 8 % faster (the LDS reads of one block at a
 // time moved ≈ 145 bytes per cycle per CU).
-constexpr int kSlot = 12;   // dwords per node: 8 for the features, then 10 head outputs
-
 constexpr int kBlocksPerCu = 4;   // resident blocks (LDS 27 KB, <= 128 registers)
 
 // WALLS (with PULL): the channel step, halfway bounce-back at rows 0 and
@@ -86,26 +56,11 @@ __global__ __launch_bounds__(kThreads, kBlocksPerCu) void simple_step_kernel(
     const float *__restrict__ tau_arr, float tau_s, float gx, const uint8_t *__restrict__ pack,
     FragLayout F, float *__restrict__ head_out, Q80 *__restrict__ pmass,
     unsigned *__restrict__ pflag, float *__restrict__ save_z0, unsigned *__restrict__ chunkq) {
-  __shared__ u32x4 w_s[14 * 64];   // W1 (4), W2 (8), Wh (2) fragments
-  __shared__ f32x4 b_s[9 * 4];     // b1 (4), b2 (4), bh (1), per channel group
+  __shared__ u32x4 w_s[kStepFrags * 64];
+  __shared__ f32x4 b_s[kStepBias * 4];
   __shared__ __attribute__((aligned(16))) uint32_t slot_s[kWaves][64 * kSlot];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = lane & 15, q = lane >> 4;
-  {
-    const u32x4 *frags = (const u32x4 *)(pack + F.frag_off);
-    const f32x4 *bias = (const f32x4 *)(pack + F.bias_off);
-    for (int k = threadIdx.x; k < 14 * 64; k += kThreads) {
-      int f = k >> 6, l = k & 63;
-      int src_f = f < 4 ? F.W1 + f : (f < 12 ? F.W2 + (f - 4) : F.WH + (f - 12));
-      w_s[k] = frags[(size_t)src_f * 64 + l];
-    }
-    // a bias fragment holds rows 4q..4q+3 for every node column: lane 16 q
-    if (threadIdx.x < 9 * 4) {
-      int b = threadIdx.x >> 2, g = threadIdx.x & 3;
-      int src_b = b < 4 ? F.B1 + b : (b < 8 ? F.B2 + (b - 4) : F.BH);
-      b_s[threadIdx.x] = bias[(size_t)src_b * 64 + 16 * g];
-    }
-  }
+  load_network(pack, F, w_s, b_s);
   const float *cst = (const float *)(pack + F.const_off);
   const float sdelta = cst[C_SDELTA];
   // normalisation (x - mu) / sigma as one FMA per feature: x * isg + nmi
@@ -166,80 +121,14 @@ __global__ __launch_bounds__(kThreads, kBlocksPerCu) void simple_step_kernel(
       M = moments(gp);
       cw.take(drawn);
       if (WALLS) M.u = __builtin_fmaf(M.jx, M.inv, 0.5f * gx);  // Guo's velocity
-      const float raw[NFEAT] = {gp[0], gp[1], gp[2], gp[3],  gp[4], gp[5],
-                                gp[6], gp[7], gp[8], M.drho, M.u,   M.v};
-      float ft[NFEAT];
-#pragma unroll
-      for (int k = 0; k < NFEAT; ++k) ft[k] = fmaf(raw[k], isg[k], nmi[k]);
-      u32x4 *o = (u32x4 *)(sw + lane * kSlot);
-      o[0] = u32x4{pack_bf16(ft[0], ft[1]), pack_bf16(ft[2], ft[3]), pack_bf16(ft[4], ft[5]),
-                   pack_bf16(ft[6], ft[7])};
-      o[1] = u32x4{pack_bf16(ft[8], ft[9]), pack_bf16(ft[10], ft[11]), 0u, 0u};
+      put_features(sw + lane * kSlot, gp, M, isg, nmi);
     }
     wave_lds_sync();
-    // Two column blocks of 16 nodes at a time: each weight and bias fragment
-    // read from LDS serves both (half the LDS reads of one block at a time).
-#pragma unroll 2
-    for (int pair = 0; pair < 2; ++pair) {
-      int wo = lane;
-      asm volatile("" : "+v"(wo));
-      const u32x4 *w = w_s + wo;
-      const f32x4 *bs = b_s + q;
-      uint32_t *slot[2];
-      u32x4 xb[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        slot[h] = sw + (16 * (2 * pair + h) + n) * kSlot;
-        xb[h] = q < 2 ? *(const u32x4 *)(slot[h] + 4 * q) : u32x4{0u, 0u, 0u, 0u};
-      }
-      f32x4 a[2][4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const u32x4 wt = w[t * 64];
-        const f32x4 bt = bs[t * 4];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) a[h][t] = mfma(wt, xb[h], bt);
-      }
-      u32x4 e1[2][2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        e1[h][0] = relu_frag(a[h][0], a[h][1]);
-        e1[h][1] = relu_frag(a[h][2], a[h][3]);
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const u32x4 w0 = w[(4 + 2 * t) * 64], w1 = w[(5 + 2 * t) * 64];
-        const f32x4 bt = bs[(4 + t) * 4];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) a[h][t] = mfma(w1, e1[h][1], mfma(w0, e1[h][0], bt));
-      }
-      u32x4 hb[2][2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        hb[h][0] = relu_frag(a[h][0], a[h][1]);
-        hb[h][1] = relu_frag(a[h][2], a[h][3]);
-      }
-      const u32x4 w12 = w[12 * 64], w13 = w[13 * 64];
-      const f32x4 b8 = bs[8 * 4];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const f32x4 z = mfma(w13, hb[h][1], mfma(w12, hb[h][0], b8));
-        // the features of these 16 nodes are consumed (z depends on them):
-        // their slots take the head outputs, rows 4q..4q+3
-        if (q < 2) *(f32x4 *)(slot[h] + 4 * q) = z;
-        else if (q == 2) *(float2 *)(slot[h] + 8) = float2{z.x, z.y};
-      }
-    }
+    network(w_s, b_s, sw, lane);
     wave_lds_sync();
     if (valid) {
       float z[NOUT];
-      {
-        const f32x4 *zs = (const f32x4 *)(sw + lane * kSlot);
-        const f32x4 z0 = zs[0], z1 = zs[1], z2 = zs[2];
-        const float zz[12] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w, z2.x, z2.y, z2.z, z2.w};
-#pragma unroll
-        for (int k = 0; k < NOUT; ++k) z[k] = zz[k];
-      }
+      get_head(sw + lane * kSlot, z);
       const float tau = tau_arr ? tau_arr[b] : tau_s;  // b < batch while cw.more()
       collide<WALLS>(gp, z, tau, sdelta, gx, M);
       float *d = dst + (size_t)b * ny * row + (size_t)y * row + x;
@@ -272,6 +161,145 @@ __global__ __launch_bounds__(kThreads, kBlocksPerCu) void simple_step_kernel(
   // every wave is done with its slots: the sum reuses them
   __syncthreads();
   store_partial((PartialSlot *)&slot_s[0][0], mass_acc, flag_acc, pmass, pflag);
+}
+
+// nsteps gated (or ungated) steps of a lattice of up to 1024 nodes in one
+// workgroup, one node per thread.  The state goes from step to step through LDS
+// (the eight directions that move, two buffers), the gate sums its exact mass
+// over the waves between the two barriers that a step has anyway, and a step
+// that trips is the plain BGK collision of the populations the step pulled,
+// which are still in registers.  Same arithmetic as the steps one by one, so
+// bitwise the same states and decisions.  Latency bound: a step of 4 x 32 takes
+// 2.5 us (channel 2.8), in the kernel of large lattices with packing and gate
+// 12.8, its rows filling four lanes of 64; one of 32 x 32 6.0 against 12.3.
+constexpr int kResidentNodes = 1024;
+constexpr int kResidentSteps = 4096;   // a launch of some 20 ms at most
+
+template <bool WALLS, int THREADS>
+__global__ __launch_bounds__(THREADS) void simple_resident_kernel(
+    const float *__restrict__ src, float *__restrict__ dst, int nx, int ny, int nsteps, float tau,
+    float gx, const uint8_t *__restrict__ pack, FragLayout F, double threshold,
+    unsigned *__restrict__ flags, unsigned *__restrict__ n_fallback, double *__restrict__ mass) {
+  constexpr int W = THREADS / 64;
+  __shared__ u32x4 w_s[kStepFrags * 64];
+  __shared__ f32x4 b_s[kStepBias * 4];
+  __shared__ __attribute__((aligned(16))) uint32_t slot_s[W][64 * kSlot];
+  __shared__ float state_s[2][8 * THREADS];
+  __shared__ PartialSlot part_s[2][W];
+  __shared__ double sum_s[W];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  load_network(pack, F, w_s, b_s);
+  const float *cst = (const float *)(pack + F.const_off);
+  const float sdelta = cst[C_SDELTA];
+  float isg[NFEAT], nmi[NFEAT];
+#pragma unroll
+  for (int k = 0; k < NFEAT; ++k) {
+    isg[k] = 1.0f / cst[C_SIGMA + k];
+    nmi[k] = -cst[C_MU + k] * isg[k];
+  }
+  const int nodes = nx * ny;
+  const bool valid = (int)threadIdx.x < nodes;
+  const int k = valid ? (int)threadIdx.x : nodes - 1, y = k / nx, x = k - y * nx;
+  const float omega = 1.0f / tau;  // of the fallback
+  float g[9];
+  if constexpr (WALLS)
+    lbm::pull9_walls(src, nx, ny, x, y, g);
+  else
+    lbm::pull9(src, nx, ny, x, y, g);
+  int from[9];  // where population i of the next step comes from
+#pragma unroll
+  for (int i = 1; i < 9; ++i) {
+    int sx = x - cx(i), sy = y - cy(i), d = i;
+    sx = sx < 0 ? nx - 1 : (sx == nx ? 0 : sx);
+    if (WALLS && (sy < 0 || sy == ny)) {  // back from the wall, reversed
+      sx = x;
+      sy = y;
+      d = lbm::opp(i);
+    }
+    sy = sy < 0 ? ny - 1 : (sy == ny ? 0 : sy);
+    from[i] = (d - 1) * THREADS + sy * nx + sx;
+  }
+  double m_prev = flags ? *mass : 0.0;
+  unsigned seen = 0, fell = 0;
+  __syncthreads();
+
+  uint32_t *sw = slot_s[wave];
+  for (int s = 0; s < nsteps; ++s) {
+    float gn[9];
+    {
+      lbm::Moments<float> M = moments(g);
+      if (WALLS) M.u = __builtin_fmaf(M.jx, M.inv, 0.5f * gx);  // Guo's velocity
+      put_features(sw + lane * kSlot, g, M, isg, nmi);
+      wave_lds_sync();
+      network(w_s, b_s, sw, lane);
+      wave_lds_sync();
+      float z[NOUT];
+      get_head(sw + lane * kSlot, z);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) gn[i] = g[i];
+      collide<WALLS>(gn, z, tau, sdelta, gx, M);
+    }
+    float *buf = state_s[s & 1];
+#pragma unroll
+    for (int i = 1; i < 9; ++i) buf[(i - 1) * THREADS + threadIdx.x] = gn[i];
+    if (flags) {
+      float msum = 0.0f, least = INFINITY;
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        least = fminf(least, gn[i] + lbm::wgt<float>(i));
+        msum += gn[i];
+      }
+      const bool bad = valid && !(least >= 0.0f && fabsf(msum) < INFINITY);
+      const Q80 none{0ull, 0ll};
+      put_partial(part_s[s & 1], valid ? q80_add_f32(none, msum) : none, bad ? 1u : 0u);
+    }
+    __syncthreads();
+    if (flags) {
+      const PartialSlot sum = sum_partials(part_s[s & 1], 0, W);
+      const double m_new = (double)nodes + q80_value(sum.mass);
+      unsigned fl = sum.flag;
+      if (!(fabs(m_new - m_prev) / m_prev <= threshold)) fl |= 2u;
+      m_prev = m_new;
+      if (fl) {  // the whole workgroup
+        seen |= fl;
+        ++fell;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) gn[i] = g[i];
+        if constexpr (WALLS)
+          lbm::forced_collide(gn, omega, gx);
+        else
+          lbm::bgk_collide(gn, omega);
+#pragma unroll
+        for (int i = 1; i < 9; ++i) buf[(i - 1) * THREADS + threadIdx.x] = gn[i];
+        double m = 0.0;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) m += valid ? (double)gn[i] : 0.0;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) m += __shfl_xor(m, d);
+        if (lane == 0) sum_s[wave] = m;
+        __syncthreads();
+        m = sum_s[0];
+        for (int v = 1; v < W; ++v) m += sum_s[v];
+        m_prev = (double)nodes + m;
+        // (the next step's barrier stands between these reads and new sums)
+      }
+    }
+    g[0] = gn[0];
+    if (s + 1 < nsteps) {
+#pragma unroll
+      for (int i = 1; i < 9; ++i) g[i] = buf[from[i]];
+    } else if (valid) {
+      float *d = dst + (size_t)y * 9 * nx + x;
+#pragma unroll
+      for (int i = 0; i < 9; ++i) d[(size_t)i * nx] = gn[i];
+    }
+  }
+  if (flags && threadIdx.x == 0) {
+    if (seen) *flags |= seen;
+    if (n_fallback) *n_fallback += fell;
+    *mass = m_prev;
+  }
 }
 
 }  // namespace simple
@@ -325,6 +353,37 @@ static int launch_simple(bool pull, bool walls, float gx, const float *src, floa
   return launch_check("simple_step_kernel");
 }
 
+// nsteps steps of a lattice of up to simple::kResidentNodes nodes.
+static int launch_simple_resident(bool walls, float gx, const float *src, float *dst, int nx,
+                                  int ny, float tau, const float *params, int nsteps, void *ws,
+                                  const lbm_fallback *fb, hipStream_t s) {
+  const SimpleScratch W = simple_scratch();
+  uint8_t *pack = (uint8_t *)at_(ws, W.pack);
+  if (int rc = launch_prep(params, 0, pack, nullptr, nullptr, s)) return rc;
+  const FragLayout F = frag_layout(0);
+  const double threshold = fb ? fb->drift_threshold : 0.0;
+  unsigned *flags = fb ? fb->flags : nullptr, *nf = fb ? fb->n_fallback : nullptr;
+  double *mass = fb ? fb->mass : nullptr;
+  const int nodes = nx * ny;
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, s, src, dst, nx, ny, nsteps, tau, gx,
+                       pack, F, threshold, flags, nf, mass);
+    return launch_check("simple_resident_kernel");
+  };
+  // (fewer waves, fewer to wait for at the barrier)
+  if (nodes <= 128)
+    return walls ? launch(simple::simple_resident_kernel<true, 128>, 128)
+                 : launch(simple::simple_resident_kernel<false, 128>, 128);
+  if (nodes <= 256)
+    return walls ? launch(simple::simple_resident_kernel<true, 256>, 256)
+                 : launch(simple::simple_resident_kernel<false, 256>, 256);
+  if (nodes <= 512)
+    return walls ? launch(simple::simple_resident_kernel<true, 512>, 512)
+                 : launch(simple::simple_resident_kernel<false, 512>, 512);
+  return walls ? launch(simple::simple_resident_kernel<true, 1024>, 1024)
+               : launch(simple::simple_resident_kernel<false, 1024>, 1024);
+}
+
 static int check_simple(const char *who, int batch, int nx, int ny, const float *params) {
   if (!params) return fail(LBM_EINVAL, "%s: null parameters", who);
   if (batch < 1 || !lbm::lattice_ok(nx, ny) || (long long)batch * nx * ny >= (1LL << 31))
@@ -354,7 +413,7 @@ extern "C" int simple_forward(const float *g_pre, float *g_post, int batch, int 
 
 // The fused step, periodic (walls = 0) or the channel (walls = 1, force gx).
 static int step_simple(const char *who, const float *g_src, float *g_dst, int nx, int ny,
-                       float tau, bool walls, float gx, const float *params,
+                       float tau, bool walls, float gx, const float *params, int nsteps,
                        const lbm_fallback *fb, void *workspace, size_t ws_bytes, void *stream) {
   if (int rc = check_simple(who, 1, nx, ny, params)) return rc;
   if (!g_src || !g_dst) return fail(LBM_EINVAL, "%s: null pointer", who);
@@ -367,8 +426,14 @@ static int step_simple(const char *who, const float *g_src, float *g_dst, int nx
     return fail(LBM_EINVAL, "%s: fallback needs flags and mass pointers", who);
   if (!workspace || ws_bytes < simple_scratch().total)
     return fail(LBM_EWORKSPACE, "%s: workspace needs %zu bytes", who, simple_scratch().total);
+  const int most = lbm_steps_simple_max(nx, ny);
+  if (nsteps < 1 || nsteps > most)
+    return fail(LBM_EINVAL, "%s: %d steps, not 1 to %d", who, nsteps, most);
   if (int rc = check_device()) return rc;
   hipStream_t s = (hipStream_t)stream;
+  if ((long long)nx * ny <= simple::kResidentNodes)
+    return launch_simple_resident(walls, gx, g_src, g_dst, nx, ny, tau, params, nsteps, workspace,
+                                  fb, s);
   int nparts;
   if (int rc = launch_simple(true, walls, gx, g_src, g_dst, 1, nx, ny, nullptr, tau, params,
                              nullptr, nullptr, workspace, fb, &nparts, s))
@@ -383,7 +448,7 @@ static int step_simple(const char *who, const float *g_src, float *g_dst, int nx
 extern "C" int lbm_step_simple(const float *g_src, float *g_dst, int nx, int ny, float tau,
                                const float *params, const lbm_fallback *fb, void *workspace,
                                size_t ws_bytes, void *stream) {
-  return step_simple("lbm_step_simple", g_src, g_dst, nx, ny, tau, false, 0.0f, params, fb,
+  return step_simple("lbm_step_simple", g_src, g_dst, nx, ny, tau, false, 0.0f, params, 1, fb,
                      workspace, ws_bytes, stream);
 }
 
@@ -391,6 +456,27 @@ extern "C" int lbm_step_simple_channel(const float *g_src, float *g_dst, int nx,
                                        float tau, float gx, const float *params,
                                        const lbm_fallback *fb, void *workspace,
                                        size_t ws_bytes, void *stream) {
-  return step_simple("lbm_step_simple_channel", g_src, g_dst, nx, ny, tau, true, gx, params, fb,
+  return step_simple("lbm_step_simple_channel", g_src, g_dst, nx, ny, tau, true, gx, params, 1, fb,
                      workspace, ws_bytes, stream);
+}
+
+extern "C" int lbm_steps_simple_max(int nx, int ny) {
+  return lbm::lattice_ok(nx, ny) && (long long)nx * ny <= simple::kResidentNodes
+             ? simple::kResidentSteps
+             : 1;
+}
+
+extern "C" int lbm_steps_simple(const float *g_src, float *g_dst, int nx, int ny, float tau,
+                                const float *params, int nsteps, const lbm_fallback *fb,
+                                void *workspace, size_t ws_bytes, void *stream) {
+  return step_simple("lbm_steps_simple", g_src, g_dst, nx, ny, tau, false, 0.0f, params, nsteps,
+                     fb, workspace, ws_bytes, stream);
+}
+
+extern "C" int lbm_steps_simple_channel(const float *g_src, float *g_dst, int nx, int ny,
+                                        float tau, float gx, const float *params, int nsteps,
+                                        const lbm_fallback *fb, void *workspace, size_t ws_bytes,
+                                        void *stream) {
+  return step_simple("lbm_steps_simple_channel", g_src, g_dst, nx, ny, tau, true, gx, params,
+                     nsteps, fb, workspace, ws_bytes, stream);
 }

@@ -19,7 +19,7 @@ __all__ = ["gnn_param_count", "gnn_blob_len", "saved_bytes", "gnn_forward", "lbm
            "lbm_step_gnn_noalloc",
            "Fallback", "GnnLattice", "gnn_backward", "gnn_mse", "gnn_adam", "GnnCollide",
            "GnnMse", "gnn_mse_weighted", "simple_forward", "lbm_step_simple", "lbm_step_simple_channel",
-           "gnn_gelu_rate", "collide"]
+           "lbm_steps_simple_max", "lbm_steps_simple", "lbm_steps_simple_channel", "gnn_gelu_rate", "collide"]
 
 
 def gnn_param_count(rounds: int = 2) -> int:
@@ -212,6 +212,33 @@ def lbm_step_simple_channel(src: torch.Tensor, dst: torch.Tensor, tau: float, gx
     return dst
 
 
+def lbm_steps_simple_max(nx: int, ny: int) -> int:
+    """The most steps that one call of lbm_steps_simple(_channel) takes."""
+    return int(_lib.load().lbm_steps_simple_max(nx, ny))
+
+
+def lbm_steps_simple(src: torch.Tensor, dst: torch.Tensor, tau: float, blob: torch.Tensor,
+                     nsteps: int, fallback: Fallback = None, ws: Workspace = None):
+    """nsteps (1 to lbm_steps_simple_max) steps of lbm_step_simple in one call."""
+    nx, ny, fb, buf = _simple_step_args(src, dst, blob, fallback, ws)
+    rc = _lib.load().lbm_steps_simple(_ptr(src), _ptr(dst), nx, ny, float(tau), _ptr(blob),
+                                      int(nsteps), fb, _ptr(buf), buf.numel(), _stream())
+    check(rc, "lbm_steps_simple")
+    return dst
+
+
+def lbm_steps_simple_channel(src: torch.Tensor, dst: torch.Tensor, tau: float, gx: float,
+                             blob: torch.Tensor, nsteps: int, fallback: Fallback = None,
+                             ws: Workspace = None):
+    """nsteps steps of lbm_step_simple_channel in one call."""
+    nx, ny, fb, buf = _simple_step_args(src, dst, blob, fallback, ws)
+    rc = _lib.load().lbm_steps_simple_channel(_ptr(src), _ptr(dst), nx, ny, float(tau), float(gx),
+                                              _ptr(blob), int(nsteps), fb, _ptr(buf), buf.numel(),
+                                              _stream())
+    check(rc, "lbm_steps_simple_channel")
+    return dst
+
+
 class GnnLattice(Lattice):
     """A/B buffers of one periodic lattice stepped with the plain BGK or the
     GNN-corrected collision, with the per-step fallback gate."""
@@ -222,6 +249,7 @@ class GnnLattice(Lattice):
         self.blob, self.rounds = blob, rounds
         self.ws = Workspace()
         self.fallback = Fallback(float(nx * ny), threshold, device)
+        self._most_simple = lbm_steps_simple_max(nx, ny)
 
     @property
     def n_fallback(self):
@@ -271,8 +299,10 @@ class GnnLattice(Lattice):
         per-node network of Fig. 2 for rounds == 0.  With the gate, the
         fallback state is updated on the device every step, also inside a
         captured graph."""
-        def step(src, dst, fb):
-            if self.rounds == 0:
+        def step(src, dst, fb, k=1):
+            if self.rounds == 0 and k > 1:
+                lbm_steps_simple(src, dst, tau, self.blob, k, fb, self.ws)
+            elif self.rounds == 0:
                 lbm_step_simple(src, dst, tau, self.blob, fb, self.ws)
             else:
                 lbm_step_gnn(src, dst, tau, self.blob, self.rounds, fb, self.ws)
@@ -287,7 +317,8 @@ class GnnLattice(Lattice):
                 tmp.mass.copy_(self.fallback.mass)
             step(self.a.clone(), torch.empty_like(self.a), tmp)
         return self._run(("gnn", float(tau), bool(gate)) + self._graph_key(gate),
-                         lambda s, d, k: step(s, d, fb), warm, n, graph)
+                         lambda s, d, k: step(s, d, fb, k), warm, n, graph,
+                         self._most_simple if self.rounds == 0 else 1)
 
     def step_gnn_channel(self, tau: float, gx: float, n: int = 1, gate: bool = True,
                          graph: bool = False):
@@ -297,8 +328,11 @@ class GnnLattice(Lattice):
             raise ValueError("the channel step runs the per-node network (rounds = 0): "
                              "message passing has no wall treatment")
 
-        def step(src, dst, fb):
-            lbm_step_simple_channel(src, dst, tau, gx, self.blob, fb, self.ws)
+        def step(src, dst, fb, k=1):
+            if k > 1:
+                lbm_steps_simple_channel(src, dst, tau, gx, self.blob, k, fb, self.ws)
+            else:
+                lbm_step_simple_channel(src, dst, tau, gx, self.blob, fb, self.ws)
 
         fb = self.fallback if gate else None
 
@@ -309,7 +343,7 @@ class GnnLattice(Lattice):
                 tmp.mass.copy_(self.fallback.mass)
             step(self.a.clone(), torch.empty_like(self.a), tmp)
         return self._run(("gnn_channel", float(tau), float(gx), bool(gate)) + self._graph_key(gate),
-                         lambda s, d, k: step(s, d, fb), warm, n, graph)
+                         lambda s, d, k: step(s, d, fb, k), warm, n, graph, self._most_simple)
 
 
 def backward_ws_bytes(batch: int, nx: int, ny: int, rounds: int = 2) -> int:
