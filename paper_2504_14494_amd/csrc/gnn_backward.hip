@@ -34,6 +34,20 @@ namespace gnn {
 int launch_simple_backward(const float *G, const float *g_pre, const float *tau, const float *z0,
                            int batch, int nx, int ny, const uint8_t *pack, float *part, hipStream_t s);
 
+// The kernels below but the head's give two waves, on one SIMD, the chunks of one
+// partial, each half of the 64 channels: every sum keeps the order it has with one
+// wave, and a SIMD has two waves to issue from (a workgroup holds the four pairs
+// of a CU; with one wave each these kernels waited 20 to 40 % of their time).
+// What a product over all channels needs of the other half goes through LDS, a
+// barrier per group.  A pair past the last chunk spends the turn at the barriers.
+//
+// 32 lattices of 128^2, one wave per partial and node-by-node buffers -> pairs and
+// group planes (bwd_common.hpp): receiver 277 -> 225 us, sender 207 -> 189, node
+// 135 -> 114, encoder 88 -> 77, head 76 -> 58 (planes only).  Moving 0.87, 1.0,
+// 0.54, 0.22 and 0.24 GB, they take 135, 155, 83, 34 and 37 us at the rate of a
+// large copy.
+constexpr int kPairT = 2 * kBT;
+
 // ------------------------------------------------------------ the head ---
 
 // dz from dL/dg_post at each node, dh_R = Wh^T dz, dWh, dbh.
@@ -43,7 +57,8 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
     const uint8_t *__restrict__ pack, FragLayout F, BlobLayout L, float *__restrict__ dh,
     float *__restrict__ part) {
   __shared__ Stage<16, 64> st[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, q = lane >> 4;
   Stage<16, 64> &S = st[wave];
   const u32x4 *frags = (const u32x4 *)(pack + F.frag_off);
@@ -51,17 +66,16 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
   u32x4 wht[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) wht[t] = load_frag(frags, F.WHT + t, lane);
-  const long long gxn = (nx + 15) / 16, ngroups = (long long)batch * ny * gxn;
-  const long long nchunks = (ngroups + 1) / 2;
-  const int w = blockIdx.x * 4 + wave;
+  const unsigned gxn = (nx + 15) / 16, ngroups = (unsigned)batch * ny * gxn;
+  const unsigned nchunks = (ngroups + 1) / 2;
+  const unsigned w = blockIdx.x * 4 + wave;
   f32x4 acc[1][4] = {};
   float bsum[NOUT] = {};
   // One wave per SIMD: the next chunk's inputs (both groups) are loaded while
-  // this chunk is computed; one explicit wait before the chunk's first store
-  // covers them.
+  // this chunk is computed.
   float g_nx[2][9], G_nx[2][9], z_nx[2], tau_nx[2];
   u32x4 hf_nx[2][2];
-  auto prefetch = [&](long long cc) {
+  auto prefetch = [&](unsigned cc) {
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
       const Pos P = group_pos(2 * cc + hh, ngroups, n, nx, ny, gxn);
@@ -77,8 +91,7 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
     }
   };
   if (w < nchunks) prefetch(w);
-  __builtin_amdgcn_s_waitcnt(kBwdWaitVmcnt0);
-  for (long long c = w; c < nchunks; c += kBwdWaves) {
+  for (unsigned c = w; c < nchunks; c += kBwdWaves) {
     float gc[2][9], Gc[2][9], zc[2], tauc[2];
     u32x4 hfc[2][2];
 #pragma unroll
@@ -95,7 +108,7 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
     }
     if (c + kBwdWaves < nchunks) prefetch(c + kBwdWaves);
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
+    for (unsigned half = 0; half < 2; ++half) {
       Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
       float(&g)[9] = gc[half];
       float(&Gi)[9] = Gc[half];
@@ -118,8 +131,7 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
       f32x4 o[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) o[t] = mfma(wht[t], dzb, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
-      if (half == 0) __builtin_amdgcn_s_waitcnt(kBwdWaitVmcnt0);
-      if (P.valid) store_acc(dh, P.node, q, o);
+      store_acc(dh, P, n, q, o);
       const u32x4 hf[2] = {hfc[half][0], hfc[half][1]};
       const int col = 16 * half + n;
 #pragma unroll
@@ -152,60 +164,66 @@ __global__ __launch_bounds__(kBT) void bwd_head_kernel(
 
 // ------------------------------------------------------ node update, r ---
 
-// dp, [dh; da] = Wn^T dp, dWn, dbn.  dh_out is overwritten.
-__global__ __launch_bounds__(kBT) void bwd_node_kernel(
+// dp, [dh; da] = Wn^T dp, dWn, dbn.  dh_out is overwritten.  Wave 0 of a pair
+// forms and stores dh, wave 1 da.
+__global__ __launch_bounds__(kPairT, 2) void bwd_node_kernel(
     const float *__restrict__ dh_in, const uint16_t *__restrict__ h, const uint16_t *__restrict__ agg,
     int batch, int nx, int ny, int r, const uint8_t *__restrict__ pack, FragLayout F,
     BlobLayout L, float *__restrict__ dh_out, float *__restrict__ dagg, float *__restrict__ part) {
   __shared__ Stage<64, 128> st[4];
   __shared__ u32x4 wn_s[16 * 64], wnt_s[16 * 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ u32x4 x_s[4][2][2][64];  // pair, half, channels: dp as an operand
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int pair = wave & 3, hh = wave >> 2;
   const int n = lane & 15, q = lane >> 4;
-  Stage<64, 128> &S = st[wave];
+  Stage<64, 128> &S = st[pair];
   const u32x4 *frags = (const u32x4 *)(pack + F.frag_off);
   const f32x4 *bias = (const f32x4 *)(pack + F.bias_off);
-  for (int k = threadIdx.x; k < 16 * 64; k += kBT) {
+  for (int k = threadIdx.x; k < 16 * 64; k += kPairT) {
     wn_s[k] = frags[(size_t)F.WN[r] * 64 + k];
     wnt_s[k] = frags[(size_t)F.WNT[r] * 64 + k];
   }
-  f32x4 bn[4];
+  f32x4 bn[2];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) bn[t] = load_bias(bias, F.BN[r] + t, lane);
+  for (int t = 0; t < 2; ++t) bn[t] = load_bias(bias, F.BN[r] + 2 * hh + t, lane);
   __syncthreads();
-  const long long gxn = (nx + 15) / 16, ngroups = (long long)batch * ny * gxn;
-  const long long nchunks = (ngroups + 1) / 2;
-  const int w = blockIdx.x * 4 + wave;
-  f32x4 acc[4][8] = {};
-  f32x4 bsum[4] = {};
-  // One wave per SIMD: each group's node state, aggregate and incoming
-  // gradient are loaded while the previous group is computed, and one
-  // explicit wait before the group's first store covers them (vmcnt counts
-  // loads and stores together; waiting there, the loads have had most of the
-  // group to land and the previous group's stores are long complete).
+  const unsigned gxn = (nx + 15) / 16, ngroups = (unsigned)batch * ny * gxn;
+  const unsigned nchunks = (ngroups + 1) / 2;
+  const unsigned w = blockIdx.x * 4 + pair;
+  float *const d_out = hh ? dagg : dh_out;
+  f32x4 acc[2][8] = {};
+  f32x4 bsum[2] = {};
+  // Each group's node state, aggregate and incoming gradient are loaded while
+  // the previous group is computed.
   u32x4 hf_nx[2], af_nx[2];
-  f32x4 G_nx[4];
-  auto prefetch = [&](long long grp) {
+  f32x4 G_nx[2];
+  auto prefetch = [&](unsigned grp) {
     const Pos P = group_pos(grp, ngroups, n, nx, ny, gxn);
     load_frags(h, P.node, q, hf_nx);
     load_frags(agg, P.node, q, af_nx);
-    load_acc(dh_in, P.node, q, G_nx);
+    load_acc(dh_in, P, n, q, G_nx, 2 * hh);
   };
-  if (w < nchunks) prefetch(2 * (long long)w);
-  __builtin_amdgcn_s_waitcnt(kBwdWaitVmcnt0);
-  for (long long c = w; c < nchunks; c += kBwdWaves) {
+  if (w < nchunks) prefetch(2 * w);
+  for (unsigned c0 = blockIdx.x * 4; c0 < nchunks; c0 += kBwdWaves) {
+    const unsigned c = c0 + pair;
+    if (c >= nchunks) {
+      for (int k = 0; k < 4; ++k) lds_barrier();
+      break;
+    }
 #pragma unroll 1
     for (int half = 0; half < 2; ++half) {
       int wo = lane;
       asm volatile("" : "+v"(wo));
-      const u32x4 *wn = wn_s + wo, *wnt = wnt_s + wo;
-      Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
+      const u32x4 *wn = wn_s + 8 * hh * 64 + wo, *wnt = wnt_s + 8 * hh * 64 + wo;
+      const Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
       const u32x4 hf[2] = {hf_nx[0], hf_nx[1]}, af[2] = {af_nx[0], af_nx[1]};
-      const f32x4 G[4] = {G_nx[0], G_nx[1], G_nx[2], G_nx[3]};
+      const f32x4 G[2] = {G_nx[0], G_nx[1]};
       if (half == 0 || c + kBwdWaves < nchunks)
         prefetch(half == 0 ? 2 * c + 1 : 2 * (c + kBwdWaves));
-      f32x4 dp[4];
+      f32x4 dp[2];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < 2; ++t) {
         f32x4 p = mfma(wn[(4 * t) * 64], hf[0], bn[t]);
         p = mfma(wn[(4 * t + 1) * 64], hf[1], p);
         p = mfma(wn[(4 * t + 2) * 64], af[0], p);
@@ -215,32 +233,28 @@ __global__ __launch_bounds__(kBT) void bwd_node_kernel(
                         : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         bsum[t] += dp[t];
       }
-      const u32x4 dpb[2] = {frag_from_acc(dp[0], dp[1]), frag_from_acc(dp[2], dp[3])};
-      f32x4 o[8];
+      lds_barrier();  // the products with the previous chunk's columns are done
+      const int col = 16 * half + n;
+      x_s[pair][half][hh][lane] = frag_from_acc(dp[0], dp[1]);
+      stage_acc(S.d, dp, q, col, 32 * hh);
+      const u32x4 own[2] = {hh ? af[0] : hf[0], hh ? af[1] : hf[1]};
+      stage_frag(S.a, own, q, col, HID * hh);
+      lds_barrier();
+      const u32x4 dpb[2] = {x_s[pair][half][0][lane], x_s[pair][half][1][lane]};
+      f32x4 o[4];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
+      for (int t = 0; t < 4; ++t) {
         o[t] = mfma(wnt[(2 * t) * 64], dpb[0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
         o[t] = mfma(wnt[(2 * t + 1) * 64], dpb[1], o[t]);
       }
-      __builtin_amdgcn_s_waitcnt(kBwdWaitVmcnt0);
-      if (P.valid) {
-        const f32x4 o_h[4] = {o[0], o[1], o[2], o[3]};
-        const f32x4 o_a[4] = {o[4], o[5], o[6], o[7]};
-        store_acc(dh_out, P.node, q, o_h);
-        store_acc(dagg, P.node, q, o_a);
-      }
-      const int col = 16 * half + n;
-      stage_acc(S.d, dp, q, col);
-      stage_frag(S.a, hf, q, col, 0);
-      stage_frag(S.a, af, q, col, HID);
+      store_acc(d_out, P, n, q, o);
     }
-    wave_lds_sync();
-    dw_mma<4, 8>(acc, S.d, S.a, lane);
-    wave_lds_sync();
+    dw_mma<2, 8>(acc, S.d + 32 * hh * kPitch, S.a, lane);
   }
+  lds_barrier();
   float *pw = part + (size_t)w * L.nparam;
-  write_dw<4, 8>(pw, L.Wn[r], NODE_IN, 0, HID, NODE_IN, acc, lane);
-  write_vec(pw, L.bn[r], 1, bsum, S.red, lane);
+  write_dw<2, 8>(pw, L.Wn[r] + (size_t)32 * hh * NODE_IN, NODE_IN, 0, 32, NODE_IN, acc, lane);
+  write_vec_half(pw, L.bn[r], 1, hh, bsum, S.red, lane);
 }
 
 // --------------------------------------------- edge layer, receiver side ---
@@ -265,56 +279,68 @@ constexpr bool ring_divisions_exact() {
 }
 static_assert(kRingNodeBytes == 9 * 16 && ring_divisions_exact(), "ring staging");
 
+// dq, BF16, lies by group of c columns like the FP32 vectors, in pieces of 64 bytes:
+// (direction, half of the channels, column).  The sender side reads it one column
+// to the left or right, so the unit it shares with the next group is one 64-byte
+// piece, not one of 16 in each of 4 planes (send 194 us instead of 221 for 32
+// lattices of 128^2; node by node, 207, and this kernel 15 % slower).
+constexpr int kEdgeBytes = 8 * HID * 2;
+
 // dq_{n,d} (stored BF16), T_n, dWa, dbe, dWc; Wa^T T_n over dL/dagg_n.
-// One wave per SIMD (the kernel needs 400+ registers), so memory latency is
-// hidden by prefetching instead of by other waves: while a wave works on one
-// group of 16 receivers, direct-to-LDS loads bring the next group's node
-// states and ring into the wave's other LDS buffer, and the next group's
-// dL/dagg rows come into registers.  One explicit wait late in each
-// group (vmcnt counts loads and stores together, so it also drains the
-// group's earlier stores, long complete by then) covers all of them.  The
-// arithmetic and its order are those of the direct loads.
-__global__ __launch_bounds__(kBT) void bwd_edge_recv_kernel(
+// 128 GELU derivatives per 16 receivers are 145 us of VALU work for 32 lattices of
+// 128^2 (72 % of the cycles issue VALU).  The waves of a pair share the node
+// states, each loading half of them, and exchange T, whose product with Wa^T runs
+// over all channels.  While a pair works on one group of 16 receivers,
+// direct-to-LDS loads bring the next group's node states and ring into its other
+// LDS buffer, and the next group's dL/dagg rows come into registers.  A barrier
+// per group publishes both; the wait before it leaves the group's stores, issued
+// after those loads, in flight.
+__global__ __launch_bounds__(kPairT, 2) void bwd_edge_recv_kernel(
     float *__restrict__ dagg_io, const uint16_t *__restrict__ h, int batch, int nx, int ny,
     int r, const uint8_t *__restrict__ pack, FragLayout F, BlobLayout L,
     uint16_t *__restrict__ dq_out, float *__restrict__ part) {
   const float *dagg = dagg_io;
   __shared__ Stage<64, 64> st[4];
   __shared__ u32x4 wa_s[8 * 64], wat_s[8 * 64];
+  __shared__ f32x4 be_s[4 * 4];
+  __shared__ u32x4 t_s[4][2][2][64];  // pair, half, channels: T as an operand
   __shared__ __attribute__((aligned(16))) uint8_t ring_s[4][2][kRingBytes];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int pair = wave & 3, hh = wave >> 2;
   const int n = lane & 15, q = lane >> 4;
-  Stage<64, 64> &S = st[wave];
+  Stage<64, 64> &S = st[pair];
   const u32x4 *frags = (const u32x4 *)(pack + F.frag_off);
   const f32x4 *bias = (const f32x4 *)(pack + F.bias_off);
-  for (int k = threadIdx.x; k < 8 * 64; k += kBT) {
-    wa_s[k] = frags[(size_t)F.WA[r] * 64 + k];
-    wat_s[k] = frags[(size_t)F.WAT[r] * 64 + k];
-  }
-  u32x4 wb[4][2];
-  uint32_t wc[4];
-  f32x4 be[4];
+  wa_s[threadIdx.x] = frags[(size_t)F.WA[r] * 64 + threadIdx.x];
+  wat_s[threadIdx.x] = frags[(size_t)F.WAT[r] * 64 + threadIdx.x];
+  static_assert(kPairT == 8 * 64, "one fragment entry per thread");
+  u32x4 wb[2][2];
+  uint32_t wc[2];
+  if (threadIdx.x < 4 * 4)  // 16 lanes share a bias
+    be_s[threadIdx.x] = bias[(size_t)(F.BE[r] + (threadIdx.x >> 2)) * 64 + 16 * (threadIdx.x & 3)];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    wb[t][0] = load_frag(frags, F.WB[r] + 2 * t, lane);
-    wb[t][1] = load_frag(frags, F.WB[r] + 2 * t + 1, lane);
-    wc[t] = load_frag(frags, F.WC[r] + t, lane).x;
-    be[t] = load_bias(bias, F.BE[r] + t, lane);
+  for (int t = 0; t < 2; ++t) {
+    const int tt = 2 * hh + t;
+    wb[t][0] = load_frag(frags, F.WB[r] + 2 * tt, lane);
+    wb[t][1] = load_frag(frags, F.WB[r] + 2 * tt + 1, lane);
+    wc[t] = load_frag(frags, F.WC[r] + tt, lane).x;
   }
-  __syncthreads();
-  const long long gxn = (nx + 15) / 16, ngroups = (long long)batch * ny * gxn;
-  const long long nchunks = (ngroups + 1) / 2;
-  const int w = blockIdx.x * 4 + wave;
+  const unsigned gxn = (nx + 15) / 16, ngroups = (unsigned)batch * ny * gxn;
+  const unsigned nchunks = (ngroups + 1) / 2;
+  const unsigned w = blockIdx.x * 4 + pair;
+  const bool narrow = nx < 16 || ny < 2;  // the ring wraps more than once
 
-  // Issues the loads of group `grp` (clamped as group_pos clamps it): its
-  // ring into `buf` (direct to LDS, wrapped at the lattice edges; slots past
-  // the last node repeat its last chunk) and its dL/dagg rows into registers.
-  auto prefetch = [&](long long grp, uint8_t *buf, f32x4(&da)[4]) {
+  // Issues this wave's loads of group `grp` (clamped as group_pos clamps it):
+  // half of its ring into `buf` (direct to LDS, wrapped at the lattice edges;
+  // slots past the last node repeat its last chunk) and its channels of the
+  // dL/dagg rows into registers.
+  auto prefetch = [&](unsigned grp, uint8_t *buf, f32x4(&da)[2]) {
     const Pos P = group_pos(grp, ngroups, n, nx, ny, gxn);
-    const int x0 = (int)((grp < ngroups ? grp : 0) % gxn) * 16;
     const size_t lat_nodes = (size_t)P.b * ny * nx;
 #pragma unroll
-    for (int k = 0; k < kRingLoads; ++k) {
+    for (int i = 0; i < kRingLoads / 2; ++i) {
+      const int k = 2 * i + hh;
       const unsigned slot = 64 * k + lane;
       unsigned ln = __umul24(slot, kRingDiv9) >> 16;
       unsigned c = slot - 9 * ln;
@@ -325,252 +351,286 @@ __global__ __launch_bounds__(kBT) void bwd_edge_recv_kernel(
       c = c < 7 ? c : 7;
       const int hy = (int)(__umul24(ln, kRingDiv18) >> 16);
       const int hx = (int)ln - kRingX * hy;
-      int gx = x0 - 1 + hx, gy = P.y - 1 + hy;
+      int gx = P.x0 - 1 + hx, gy = P.y - 1 + hy;
       gx = gx < 0 ? gx + nx : (gx >= nx ? gx - nx : gx);
       gy = gy < 0 ? gy + ny : (gy >= ny ? gy - ny : gy);
-      if (gx >= nx) gx %= nx;  // lattices narrower than the ring
-      if (gy >= ny) gy %= ny;
+      if (narrow) {
+        gx %= nx;
+        gy %= ny;
+      }
       const uint16_t *src = h + (lat_nodes + (size_t)gy * nx + gx) * HID + c * 8;
       __builtin_amdgcn_global_load_lds((const void *)src,
                                        (__attribute__((address_space(3))) void *)(buf + k * 1024),
                                        16, 0, 0);
     }
-    load_acc(dagg, P.node, q, da);
+    __builtin_amdgcn_sched_barrier(0);  // nothing of the group passes its loads
+    load_acc(dagg, P, n, q, da, 2 * hh);
   };
+  static_assert(kRingLoads % 2 == 0, "each wave of a pair loads half of a ring");
 
-  f32x4 acc[4][4] = {};
-  f32x4 tsum[4] = {}, vxs[4] = {}, vys[4] = {};
-  f32x4 da_nx[4];
+  f32x4 acc[2][4] = {};
+  f32x4 tsum[2] = {}, vxs[2] = {}, vys[2] = {};
+  f32x4 da_nx[2] = {};
   // One group: half 0 or 1 of chunk c, its ring in `cur`; the next group's
-  // loads go to `nxt`.
-  auto group = [&](long long c, int half, const uint8_t *cur, uint8_t *nxt) {
-      int wo = lane;
-      asm volatile("" : "+v"(wo));
-      const u32x4 *wa = wa_s + wo, *wat = wat_s + wo;
-      const Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
-      // (zero on lanes outside the lattice)
-      f32x4 da[4];
+  // loads go to `nxt`.  Leaves T staged.
+  auto group = [&](unsigned c, int half, const uint8_t *cur, uint8_t *nxt) {
+    int wo = lane;
+    asm volatile("" : "+v"(wo));
+    const u32x4 *wa = wa_s + 4 * hh * 64 + wo;
+    const Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
+    // (zero on lanes outside the lattice)
+    f32x4 da[2];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) da[t] = P.valid ? da_nx[t] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      // the next group of this wave: the chunk's second half, or the first
-      // half of the wave's next chunk
-      // chunk q of this receiver's lower-left neighbour; every neighbour's
-      // chunk is at a constant offset from it
-      const uint8_t *nb = cur + n * kRingNodeBytes + q * 16;
-      auto frag_at = [&](int dx, int dy, int sidx) {
-        return *(const u32x4 *)(nb + ((dy + 1) * kRingX + dx + 1) * kRingNodeBytes + sidx * 64);
-      };
-      // all of the group's ring reads, before the next group's loads
-      const u32x4 hn[2] = {frag_at(0, 0, 0), frag_at(0, 0, 1)};
-      u32x4 hj[8][2];
+    for (int t = 0; t < 2; ++t) da[t] = P.valid ? da_nx[t] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // chunk q of this receiver's lower-left neighbour; every neighbour's
+    // chunk is at a constant offset from it
+    const uint8_t *nb = cur + n * kRingNodeBytes + q * 16;
+    auto frag_at = [&](int dx, int dy, int sidx) {
+      return *(const u32x4 *)(nb + ((dy + 1) * kRingX + dx + 1) * kRingNodeBytes + sidx * 64);
+    };
+    // all of the group's LDS reads, before the next group's loads: the
+    // compiler cannot tell the two buffers apart and would wait for the loads
+    // before a read
+    const u32x4 hn[2] = {frag_at(0, 0, 0), frag_at(0, 0, 1)};
+    u32x4 hj[8][2];
 #pragma unroll
-      for (int d = 1; d < 9; ++d) {
-        hj[d - 1][0] = frag_at(cx(d), cy(d), 0);
-        hj[d - 1][1] = frag_at(cx(d), cy(d), 1);
+    for (int d = 1; d < 9; ++d) {
+      hj[d - 1][0] = frag_at(cx(d), cy(d), 0);
+      hj[d - 1][1] = frag_at(cx(d), cy(d), 1);
+    }
+    f32x4 an[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      an[t] = mfma(wa[(2 * t) * 64], hn[0], be_s[4 * (2 * hh + t) + (wo >> 4)]);
+      an[t] = mfma(wa[(2 * t + 1) * 64], hn[1], an[t]);
+    }
+    u32x4 own = hh ? hn[1] : hn[0];
+    asm volatile("" : "+v"(own));  // select it once
+    // the next group of this wave: the chunk's second half, or the first
+    // half of the wave's next chunk
+    const unsigned next = half == 0 ? 2 * c + 1 : 2 * (c + kBwdWaves);
+    if (half == 0 || c + kBwdWaves < nchunks) prefetch(next, nxt, da_nx);
+    const __amdgpu_buffer_rsrc_t dq_rows =
+        rows_resource(dq_out, P.node0 * kEdgeBytes, P.cols * kEdgeBytes);
+    const int dq_off = P.valid ? n * 64 + q * 16 : 1 << 30;
+    f32x4 T[2] = {};
+    // The edge loop is unrolled in full, so the direction of each edge (its
+    // edge feature, the sign it adds to the Wc gradients with) is a
+    // compile-time constant and the loop has no branches to split its
+    // schedule.
+    const uint32_t q0 = q == 0 ? 0xffffffffu : 0u;
+    // pre-activation of the message from direction d (MFMA only)
+    auto message = [&](int d, f32x4(&a)[2]) {
+      const u32x4 ed = {q0 & (bf16_unit(cx(d)) | (bf16_unit(cy(d)) << 16)), 0u, 0u, 0u};
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        a[t] = mfma(u32x4{wc[t], 0u, 0u, 0u}, ed, an[t]);
+        a[t] = mfma(wb[t][0], hj[d - 1][0], a[t]);
+        a[t] = mfma(wb[t][1], hj[d - 1][1], a[t]);
       }
-      f32x4 an[4];
+    };
+    // Software pipeline as in the forward round: the MFMA chains of edge
+    // d + 1 are issued among the VALU work of edge d.  The sums run over d in
+    // the same order as without the pipeline.
+    f32x4 pre[2][2];
+    message(1, pre[1]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        an[t] = mfma(wa[(2 * t) * 64], hn[0], be[t]);
-        an[t] = mfma(wa[(2 * t + 1) * 64], hn[1], an[t]);
-      }
-      const long long next = half == 0 ? 2 * c + 1 : 2 * (c + kBwdWaves);
-      if (half == 0 || c + kBwdWaves < nchunks) prefetch(next, nxt, da_nx);
-      f32x4 T[4] = {};
-      // The edge loop is unrolled in full, so the direction of each edge (its
-      // edge feature, the sign it adds to the Wc gradients with) is a
-      // compile-time constant and the loop has no branches to split its
-      // schedule.
-      const uint32_t q0 = q == 0 ? 0xffffffffu : 0u;
-      // pre-activation of the message from direction d (MFMA only)
-      auto message = [&](int d, f32x4(&a)[4]) {
-        const u32x4 ed = {q0 & (bf16_unit(cx(d)) | (bf16_unit(cy(d)) << 16)), 0u, 0u, 0u};
+    for (int d = 1; d < 9; ++d) {
+      if (d < 8) message(d + 1, pre[(d + 1) & 1]);
+      f32x4 dq[2];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          a[t] = mfma(u32x4{wc[t], 0u, 0u, 0u}, ed, an[t]);
-          a[t] = mfma(wb[t][0], hj[d - 1][0], a[t]);
-          a[t] = mfma(wb[t][1], hj[d - 1][1], a[t]);
-        }
-      };
-      // Software pipeline as in the forward round: the MFMA chains of edge
-      // d + 1 are issued among the VALU work of edge d (one wave per SIMD
-      // here, so nothing else fills the matrix-core latency).  The sums run
-      // over d in the same order as without the pipeline.
-      f32x4 pre[2][4];
-      message(1, pre[1]);
-#pragma unroll
-      for (int d = 1; d < 9; ++d) {
-        if (d < 8) message(d + 1, pre[(d + 1) & 1]);
-        f32x4 dq[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const f32x4 a = pre[d & 1][t];
-          dq[t] = da[t] * f32x4{gelu_grad(a.x), gelu_grad(a.y), gelu_grad(a.z), gelu_grad(a.w)};
+      for (int t = 0; t < 2; ++t) {
+        const f32x4 a = pre[d & 1][t];
+        dq[t] = da[t] * f32x4{gelu_grad(a.x), gelu_grad(a.y), gelu_grad(a.z), gelu_grad(a.w)};
+        {
+          // sums of the rounded products, as they are stored
+#pragma clang fp contract(off)
           T[t] += dq[t];
           if (cx(d) > 0) vxs[t] += dq[t];
           if (cx(d) < 0) vxs[t] -= dq[t];
           if (cy(d) > 0) vys[t] += dq[t];
           if (cy(d) < 0) vys[t] -= dq[t];
         }
-        // The next group's loads were issued at the start of this one: wait
-        // for them here, where they have had most of the group to land.
-        // Unconditional, so the compiler also counts them as complete.
-        if (d == 6) __builtin_amdgcn_s_waitcnt(kBwdWaitVmcnt0);
-        if (P.valid) {
-          // non-temporal: 1 KB per node, read back once by the sender side
-          // (measured: the sender side then runs 18 % faster, this kernel 4 %
-          // slower)
-          u32x4 *o = (u32x4 *)(dq_out + (P.node * 8 + (d - 1)) * HID);
-          __builtin_nontemporal_store(frag_from_acc(dq[0], dq[1]), o + q);
-          __builtin_nontemporal_store(frag_from_acc(dq[2], dq[3]), o + 4 + q);
-        }
-        if (d < 8) {
-          // each of edge d + 1's 12 MFMAs followed by 10 VALU instructions
+      }
+      // non-temporal: 1 KB per node, read back once by the sender side
+      // (measured: the sender side then runs 18 % faster, this kernel 4 %
+      // slower)
+      __builtin_amdgcn_raw_buffer_store_b128(
+          __builtin_bit_cast(i32x4_t, frag_from_acc(dq[0], dq[1])), dq_rows,
+          dq_off + ((d - 1) * 2 + hh) * 64 * P.cols, 0, kBufferNt);
+      if (d < 8) {
+        // each of edge d + 1's 6 MFMAs followed by 10 VALU instructions
 #pragma unroll
-          for (int i = 0; i < 12; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);
-          }
+        for (int i = 0; i < 6; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);
         }
       }
-      const u32x4 tb[2] = {frag_from_acc(T[0], T[1]), frag_from_acc(T[2], T[3])};
-      f32x4 o[4];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // The pair's products with the previous chunk's columns are done.  (Needed
+    // in half 0 only, but a branch here makes the compiler put the sums off
+    // past it, and spill the products of all edges.)
+    lds_barrier();
+    const int col = 16 * half + n;
+    t_s[pair][half][hh][lane] = frag_from_acc(T[0], T[1]);
+    stage_acc(S.d, T, q, col, 32 * hh);
+    stage_frag1(S.a, own, hh, q, col);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        o[t] = mfma(wat[(2 * t) * 64], tb[0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
-        o[t] = mfma(wat[(2 * t + 1) * 64], tb[1], o[t]);
-        tsum[t] += T[t];
-      }
-      // Wa^T T replaces this group's dL/dagg rows, read by nobody after
-      // this group; the sender-side kernel adds it to dh.
-      if (P.valid) store_acc(dagg_io, P.node, q, o);
-      const int col = 16 * half + n;
-      stage_acc(S.d, T, q, col);
-      stage_frag(S.a, hn, q, col);
+    for (int t = 0; t < 2; ++t) tsum[t] += T[t];
+    // the next group's loads, with this group's 8 stores behind them
+    __builtin_amdgcn_s_waitcnt(wait_vmcnt(8));
+  };
+  // After the barrier that follows a group: Wa^T T, both waves' channels.
+  auto finish = [&](unsigned c, int half) {
+    int wo = lane;
+    asm volatile("" : "+v"(wo));
+    const u32x4 *wat = wat_s + 4 * hh * 64 + wo;
+    const Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
+    const u32x4 tb[2] = {t_s[pair][half][0][lane], t_s[pair][half][1][lane]};
+    f32x4 o[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      o[t] = mfma(wat[(2 * t) * 64], tb[0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+      o[t] = mfma(wat[(2 * t + 1) * 64], tb[1], o[t]);
+    }
+    // replaces this group's dL/dagg rows, read by nobody after this group;
+    // the sender-side kernel adds it to dh
+    store_acc(dagg_io, P, n, q, o, 2 * hh);
   };
 
-  // Group i of this wave works from ring_s[wave][i % 2].  The compiler
-  // cannot tell the two buffers apart, so it would wait for loads in flight
-  // into one before any LDS read: each group therefore does all its ring and
-  // Wa reads before it issues the next group's loads, and reads LDS again
-  // only after its explicit wait.
-  if (w < nchunks) prefetch(2 * (long long)w, ring_s[wave][0], da_nx);
-  __builtin_amdgcn_s_waitcnt(kBwdWaitVmcnt0);
-  for (long long c = w; c < nchunks; c += kBwdWaves) {
+  // Group i of a pair works from ring_s[pair][i % 2].  The pairs of a block
+  // have the same number of turns but for the last, which those past the end
+  // spend at its barriers.
+  if (w < nchunks) prefetch(2 * w, ring_s[pair][0], da_nx);
+  __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
+  lds_barrier();
+  for (unsigned c0 = blockIdx.x * 4; c0 < nchunks; c0 += kBwdWaves) {
+    const unsigned c = c0 + pair;
+    if (c >= nchunks) {
+      for (int k = 0; k < 4; ++k) lds_barrier();
+      break;
+    }
 #pragma unroll 1
-    for (int half = 0; half < 2; ++half) group(c, half, ring_s[wave][half], ring_s[wave][half ^ 1]);
-    wave_lds_sync();
-    dw_mma<4, 4>(acc, S.d, S.a, lane);
-    wave_lds_sync();
+    for (int half = 0; half < 2; ++half) {
+      group(c, half, ring_s[pair][half], ring_s[pair][half ^ 1]);
+      lds_barrier();
+      finish(c, half);
+    }
+    dw_mma<2, 4>(acc, S.d + 32 * hh * kPitch, S.a, lane);
   }
+  lds_barrier();
   float *pw = part + (size_t)w * L.nparam;
-  write_dw<4, 4>(pw, L.We[r], EDGE_IN, 0, HID, HID, acc, lane);
-  write_vec(pw, L.be[r], 1, tsum, S.red, lane);
-  write_vec(pw, L.We[r] + 2 * HID, EDGE_IN, vxs, S.red, lane);
-  write_vec(pw, L.We[r] + 2 * HID + 1, EDGE_IN, vys, S.red, lane);
+  write_dw<2, 4>(pw, L.We[r] + (size_t)32 * hh * EDGE_IN, EDGE_IN, 0, 32, HID, acc, lane);
+  write_vec_half(pw, L.be[r], 1, hh, tsum, S.red, lane);
+  write_vec_half(pw, L.We[r] + 2 * HID, EDGE_IN, hh, vxs, S.red, lane);
+  write_vec_half(pw, L.We[r] + 2 * HID + 1, EDGE_IN, hh, vys, S.red, lane);
 }
 
 // ----------------------------------------------- edge layer, sender side ---
 
 // S_m = sum_d dq_{m - e_d, d}; dWb; dh_m += Wa^T T_m (left by the receiver
-// side in orecv), then dh_m += Wb^T S_m.
-__global__ __launch_bounds__(kBT) void bwd_edge_send_kernel(
+// side in orecv), then dh_m += Wb^T S_m.  Bound by the reads of dq.
+__global__ __launch_bounds__(kPairT, 2) void bwd_edge_send_kernel(
     const uint16_t *__restrict__ dq_in, const uint16_t *__restrict__ h, int batch, int nx,
     int ny, int r, const uint8_t *__restrict__ pack, FragLayout F, BlobLayout L,
     const float *__restrict__ orecv, float *__restrict__ dh, float *__restrict__ part) {
   __shared__ Stage<64, 64> st[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ u32x4 x_s[4][2][2][64];  // pair, half, channels: S as an operand
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int pair = wave & 3, hh = wave >> 2;
   const int n = lane & 15, q = lane >> 4;
-  Stage<64, 64> &S = st[wave];
+  Stage<64, 64> &S = st[pair];
   const u32x4 *frags = (const u32x4 *)(pack + F.frag_off);
-  u32x4 wbt[4][2];
+  u32x4 wbt[2][2];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    wbt[t][0] = load_frag(frags, F.WBT[r] + 2 * t, lane);
-    wbt[t][1] = load_frag(frags, F.WBT[r] + 2 * t + 1, lane);
+  for (int t = 0; t < 2; ++t) {
+    wbt[t][0] = load_frag(frags, F.WBT[r] + 2 * (2 * hh + t), lane);
+    wbt[t][1] = load_frag(frags, F.WBT[r] + 2 * (2 * hh + t) + 1, lane);
   }
-  const long long gxn = (nx + 15) / 16, ngroups = (long long)batch * ny * gxn;
-  const long long nchunks = (ngroups + 1) / 2;
-  const int w = blockIdx.x * 4 + wave;
-  f32x4 acc[4][4] = {};
-  // One wave per SIMD: the next group's dq rows (eight directions), node
-  // state, dh and the receiver side's term are loaded while this group is
-  // computed; one explicit wait before the group's store covers them.
-  u32x4 dq_nx[8][2], hm_nx[2];
-  f32x4 dh_nx[4], or_nx[4];
-  auto prefetch = [&](long long grp) {
+  const unsigned gxn = (nx + 15) / 16, ngroups = (unsigned)batch * ny * gxn;
+  const unsigned nchunks = (ngroups + 1) / 2;
+  const unsigned w = blockIdx.x * 4 + pair;
+  f32x4 acc[2][4] = {};
+  // The next group's dq rows (eight directions), node state, dh and the
+  // receiver side's term are loaded while this group is computed.
+  u32x4 dq_nx[8], hm_nx;
+  f32x4 dh_nx[2], or_nx[2];
+  auto prefetch = [&](unsigned grp) {
     const Pos P = group_pos(grp, ngroups, n, nx, ny, gxn);
     const size_t lat_nodes = (size_t)P.b * ny * nx;
+    // receivers whose edge d points here: columns x - 1, x, x + 1 of three rows
+    size_t at[3];
+    int wide[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      int xn = P.x + k - 1;
+      xn = xn < 0 ? xn + nx : (xn >= nx ? xn - nx : xn);
+      const int xg = xn & ~15;
+      wide[k] = nx - xg < 16 ? nx - xg : 16;
+      at[k] = (size_t)xg * kEdgeBytes + (xn - xg) * 64 + q * 16;
+    }
 #pragma unroll
     for (int d = 1; d < 9; ++d) {
-      int xn = P.x - cx(d), yn = P.y - cy(d);  // receiver whose edge d points here
-      xn = xn < 0 ? xn + nx : (xn >= nx ? xn - nx : xn);
+      int yn = P.y - cy(d);
       yn = yn < 0 ? yn + ny : (yn >= ny ? yn - ny : yn);
-      const u32x4 *src =
-          (const u32x4 *)(dq_in + ((lat_nodes + (size_t)yn * nx + xn) * 8 + (d - 1)) * HID);
-      dq_nx[d - 1][0] = __builtin_nontemporal_load(src + q);  // read once
-      dq_nx[d - 1][1] = __builtin_nontemporal_load(src + 4 + q);
+      const int k = 1 - cx(d);
+      const uint8_t *src = (const uint8_t *)dq_in + (lat_nodes + (size_t)yn * nx) * kEdgeBytes +
+                           at[k] + (size_t)(((d - 1) * 2 + hh) * 64 * wide[k]);
+      dq_nx[d - 1] = __builtin_nontemporal_load((const u32x4 *)src);  // read once
     }
-    load_frags(h, P.node, q, hm_nx);
-    load_acc(dh, P.node, q, dh_nx);
-    load_acc(orecv, P.node, q, or_nx);
+    hm_nx = ((const u32x4 *)(h + P.node * HID))[4 * hh + q];
+    load_acc(dh, P, n, q, dh_nx, 2 * hh);
+    load_acc(orecv, P, n, q, or_nx, 2 * hh);
   };
-  if (w < nchunks) prefetch(2 * (long long)w);
-  __builtin_amdgcn_s_waitcnt(kBwdWaitVmcnt0);
-  for (long long c = w; c < nchunks; c += kBwdWaves) {
+  if (w < nchunks) prefetch(2 * w);
+  for (unsigned c0 = blockIdx.x * 4; c0 < nchunks; c0 += kBwdWaves) {
+    const unsigned c = c0 + pair;
+    if (c >= nchunks) {
+      for (int k = 0; k < 4; ++k) lds_barrier();
+      break;
+    }
 #pragma unroll 1
     for (int half = 0; half < 2; ++half) {
-      Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
-      u32x4 dqc[8][2], hm[2];
-      f32x4 dhc[4], orc[4];
+      const Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
+      u32x4 dqc[8];
 #pragma unroll
-      for (int d = 0; d < 8; ++d) {
-        dqc[d][0] = dq_nx[d][0];
-        dqc[d][1] = dq_nx[d][1];
-      }
-      hm[0] = hm_nx[0];
-      hm[1] = hm_nx[1];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        dhc[t] = dh_nx[t];
-        orc[t] = or_nx[t];
-      }
+      for (int d = 0; d < 8; ++d) dqc[d] = dq_nx[d];
+      const u32x4 hm = hm_nx;
+      const f32x4 dhc[2] = {dh_nx[0], dh_nx[1]}, orc[2] = {or_nx[0], or_nx[1]};
       if (half == 0 || c + kBwdWaves < nchunks)
         prefetch(half == 0 ? 2 * c + 1 : 2 * (c + kBwdWaves));
-      f32x4 Sm[4] = {};
+      f32x4 Sm[2] = {};
 #pragma unroll
       for (int d = 0; d < 8; ++d) {
-        Sm[0] += unpack_lo(dqc[d][0]);
-        Sm[1] += unpack_hi(dqc[d][0]);
-        Sm[2] += unpack_lo(dqc[d][1]);
-        Sm[3] += unpack_hi(dqc[d][1]);
+        Sm[0] += unpack_lo(dqc[d]);
+        Sm[1] += unpack_hi(dqc[d]);
       }
       if (!P.valid)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) Sm[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      const u32x4 sb[2] = {frag_from_acc(Sm[0], Sm[1]), frag_from_acc(Sm[2], Sm[3])};
-      f32x4 o[4];
+        for (int t = 0; t < 2; ++t) Sm[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      lds_barrier();  // the products with the previous chunk's columns are done
+      const int col = 16 * half + n;
+      x_s[pair][half][hh][lane] = frag_from_acc(Sm[0], Sm[1]);
+      stage_acc(S.d, Sm, q, col, 32 * hh);
+      stage_frag1(S.a, hm, hh, q, col);
+      lds_barrier();
+      const u32x4 sb[2] = {x_s[pair][half][0][lane], x_s[pair][half][1][lane]};
+      f32x4 o[2];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < 2; ++t) {
         o[t] = mfma(wbt[t][0], sb[0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
         o[t] = mfma(wbt[t][1], sb[1], o[t]);
+        o[t] = (dhc[t] + orc[t]) + o[t];
       }
-      __builtin_amdgcn_s_waitcnt(kBwdWaitVmcnt0);
-      if (P.valid) {
-        f32x4 *p = (f32x4 *)(dh + P.node * HID) + q * 4;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) p[t] = (dhc[t] + orc[t]) + o[t];
-      }
-      const int col = 16 * half + n;
-      stage_acc(S.d, Sm, q, col);
-      stage_frag(S.a, hm, q, col);
+      store_acc(dh, P, n, q, o, 2 * hh);
     }
-    wave_lds_sync();
-    dw_mma<4, 4>(acc, S.d, S.a, lane);
-    wave_lds_sync();
+    dw_mma<2, 4>(acc, S.d + 32 * hh * kPitch, S.a, lane);
   }
   float *pw = part + (size_t)w * L.nparam;
-  write_dw<4, 4>(pw, L.We[r], EDGE_IN, HID, HID, HID, acc, lane);
+  write_dw<2, 4>(pw, L.We[r] + (size_t)32 * hh * EDGE_IN, EDGE_IN, HID, 32, HID, acc, lane);
 }
 
 // ------------------------------------------------------------- encoder ---
@@ -579,95 +639,110 @@ __device__ __forceinline__ f32x4 gelu_grad4(f32x4 p) {
   return f32x4{gelu_grad(p.x), gelu_grad(p.y), gelu_grad(p.z), gelu_grad(p.w)};
 }
 
-__global__ __launch_bounds__(kBT) void bwd_encoder_kernel(
+__global__ __launch_bounds__(kPairT, 2) void bwd_encoder_kernel(
     const float *__restrict__ dh0, const uint16_t *__restrict__ sx, const uint16_t *__restrict__ se1,
     int batch, int nx, int ny, const uint8_t *__restrict__ pack, FragLayout F, BlobLayout L,
     float *__restrict__ part) {
   __shared__ Stage<64, 64> st[4];
   __shared__ uint16_t d1s[4][64 * kPitch], x1s[4][16 * kPitch];
   __shared__ u32x4 w2t_s[8 * 64], w1_s[4 * 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ u32x4 x_s[4][2][2][64];  // pair, half, channels: dp2 as an operand
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int pair = wave & 3, hh = wave >> 2;
   const int n = lane & 15, q = lane >> 4;
-  Stage<64, 64> &S = st[wave];
-  uint16_t *D1 = d1s[wave], *X1 = x1s[wave];
+  Stage<64, 64> &S = st[pair];
+  uint16_t *D1 = d1s[pair], *X1 = x1s[pair];
   const u32x4 *frags = (const u32x4 *)(pack + F.frag_off);
   const f32x4 *bias = (const f32x4 *)(pack + F.bias_off);
   // W2^T and W1 are read from LDS inside the loop, so that the loop issues
   // no global loads besides its node data
-  for (int k = threadIdx.x; k < 8 * 64; k += kBT) w2t_s[k] = frags[(size_t)F.W2T * 64 + k];
-  for (int k = threadIdx.x; k < 4 * 64; k += kBT) w1_s[k] = frags[(size_t)F.W1 * 64 + k];
-  u32x4 w2[4][2];
-  f32x4 b1[4], b2[4];
+  w2t_s[threadIdx.x] = frags[(size_t)F.W2T * 64 + threadIdx.x];
+  if (threadIdx.x < 4 * 64) w1_s[threadIdx.x] = frags[(size_t)F.W1 * 64 + threadIdx.x];
+  u32x4 w2[2][2];
+  f32x4 b1[2], b2[2];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    w2[t][0] = load_frag(frags, F.W2 + 2 * t, lane);
-    w2[t][1] = load_frag(frags, F.W2 + 2 * t + 1, lane);
-    b1[t] = load_bias(bias, F.B1 + t, lane);
-    b2[t] = load_bias(bias, F.B2 + t, lane);
+  for (int t = 0; t < 2; ++t) {
+    const int tt = 2 * hh + t;
+    w2[t][0] = load_frag(frags, F.W2 + 2 * tt, lane);
+    w2[t][1] = load_frag(frags, F.W2 + 2 * tt + 1, lane);
+    b1[t] = load_bias(bias, F.B1 + tt, lane);
+    b2[t] = load_bias(bias, F.B2 + tt, lane);
   }
-  const long long gxn = (nx + 15) / 16, ngroups = (long long)batch * ny * gxn;
-  const long long nchunks = (ngroups + 1) / 2;
-  const int w = blockIdx.x * 4 + wave;
+  const unsigned gxn = (nx + 15) / 16, ngroups = (unsigned)batch * ny * gxn;
+  const unsigned nchunks = (ngroups + 1) / 2;
+  const unsigned w = blockIdx.x * 4 + pair;
   __syncthreads();
-  f32x4 acc2[4][4] = {}, acc1[4][1] = {};
-  f32x4 s1[4] = {}, s2[4] = {};
-  // One wave per SIMD: the next group's first-layer output, features and
-  // incoming gradient are loaded while this group is computed (the loop has
-  // no stores, so the compiler's in-order load counts cover them).
+  f32x4 acc2[2][4] = {}, acc1[2][1] = {};
+  f32x4 s1[2] = {}, s2[2] = {};
+  // The next group's first-layer output, features and incoming gradient are
+  // loaded while this group is computed.
   u32x4 e1_nx[2], xb_nx;
-  f32x4 G_nx[4];
-  auto prefetch = [&](long long grp) {
+  f32x4 G_nx[2];
+  auto prefetch = [&](unsigned grp) {
     const Pos P = group_pos(grp, ngroups, n, nx, ny, gxn);
     load_frags(se1, P.node, q, e1_nx);
     xb_nx = q < 2 ? ((const u32x4 *)(sx + P.node * 16))[q] : u32x4{0u, 0u, 0u, 0u};
-    load_acc(dh0, P.node, q, G_nx);
+    load_acc(dh0, P, n, q, G_nx, 2 * hh);
   };
-  if (w < nchunks) prefetch(2 * (long long)w);
-  for (long long c = w; c < nchunks; c += kBwdWaves) {
+  if (w < nchunks) prefetch(2 * w);
+  for (unsigned c0 = blockIdx.x * 4; c0 < nchunks; c0 += kBwdWaves) {
+    const unsigned c = c0 + pair;
+    if (c >= nchunks) {
+      for (int k = 0; k < 5; ++k) lds_barrier();
+      break;
+    }
 #pragma unroll 1
     for (int half = 0; half < 2; ++half) {
       int wo = lane;
       asm volatile("" : "+v"(wo));
-      Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
+      const u32x4 *w2t = w2t_s + 4 * hh * 64 + wo, *w1 = w1_s + 2 * hh * 64 + wo;
+      const Pos P = group_pos(2 * c + half, ngroups, n, nx, ny, gxn);
       const u32x4 e1[2] = {e1_nx[0], e1_nx[1]};
       const u32x4 xb = xb_nx;
-      const f32x4 G[4] = {G_nx[0], G_nx[1], G_nx[2], G_nx[3]};
+      const f32x4 G[2] = {G_nx[0], G_nx[1]};
       if (half == 0 || c + kBwdWaves < nchunks)
         prefetch(half == 0 ? 2 * c + 1 : 2 * (c + kBwdWaves));
-      f32x4 dp2[4];
+      f32x4 dp2[2];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < 2; ++t) {
         f32x4 p = mfma(w2[t][0], e1[0], b2[t]);
         p = mfma(w2[t][1], e1[1], p);
         dp2[t] = P.valid ? G[t] * gelu_grad4(p) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         s2[t] += dp2[t];
       }
-      const u32x4 dpb[2] = {frag_from_acc(dp2[0], dp2[1]), frag_from_acc(dp2[2], dp2[3])};
-      f32x4 dp1[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        f32x4 de1 = mfma(w2t_s[(2 * t) * 64 + wo], dpb[0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
-        de1 = mfma(w2t_s[(2 * t + 1) * 64 + wo], dpb[1], de1);
-        f32x4 p1 = mfma(w1_s[t * 64 + wo], xb, b1[t]);
-        dp1[t] = de1 * gelu_grad4(p1);
-        s1[t] += dp1[t];
-      }
+      lds_barrier();  // the products with the previous chunk's columns are done
       const int col = 16 * half + n;
-      stage_acc(S.d, dp2, q, col);
-      stage_frag(S.a, e1, q, col);
-      stage_acc(D1, dp1, q, col);
-      stage_rows16(X1, xb, q, col);
+      x_s[pair][half][hh][lane] = frag_from_acc(dp2[0], dp2[1]);
+      stage_acc(S.d, dp2, q, col, 32 * hh);
+      stage_frag1(S.a, hh ? e1[1] : e1[0], hh, q, col);
+      if (hh == 0) stage_rows16(X1, xb, q, col);
+      lds_barrier();
+      const u32x4 dpb[2] = {x_s[pair][half][0][lane], x_s[pair][half][1][lane]};
+      f32x4 dp1[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x4 de1 = mfma(w2t[(2 * t) * 64], dpb[0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+        de1 = mfma(w2t[(2 * t + 1) * 64], dpb[1], de1);
+        f32x4 p1 = mfma(w1[t * 64], xb, b1[t]);
+        dp1[t] = de1 * gelu_grad4(p1);
+        {
+#pragma clang fp contract(off)
+          s1[t] += dp1[t];
+        }
+      }
+      stage_acc(D1, dp1, q, col, 32 * hh);
     }
-    wave_lds_sync();
-    dw_mma<4, 4>(acc2, S.d, S.a, lane);
-    dw_mma<4, 1>(acc1, D1, X1, lane);
-    wave_lds_sync();
+    lds_barrier();
+    dw_mma<2, 4>(acc2, S.d + 32 * hh * kPitch, S.a, lane);
+    dw_mma<2, 1>(acc1, D1 + 32 * hh * kPitch, X1, lane);
   }
+  lds_barrier();
   float *pw = part + (size_t)w * L.nparam;
-  write_dw<4, 4>(pw, L.W2, HID, 0, HID, HID, acc2, lane);
-  write_dw<4, 1>(pw, L.W1, NFEAT, 0, HID, NFEAT, acc1, lane);
-  write_vec(pw, L.b2, 1, s2, S.red, lane);
-  write_vec(pw, L.b1, 1, s1, S.red, lane);
+  write_dw<2, 4>(pw, L.W2 + (size_t)32 * hh * HID, HID, 0, 32, HID, acc2, lane);
+  write_dw<2, 1>(pw, L.W1 + (size_t)32 * hh * NFEAT, NFEAT, 0, 32, NFEAT, acc1, lane);
+  write_vec_half(pw, L.b2, 1, hh, s2, S.red, lane);
+  write_vec_half(pw, L.b1, 1, hh, s1, S.red, lane);
 }
 
 // Fixed-order sum of the per-wave partials: one thread per parameter, the
@@ -866,18 +941,18 @@ extern "C" int gnn_backward(const float *dL_dgpost, const float *g_pre, const vo
     if (int rc = launch_check("bwd_head_kernel")) return rc;
     for (int r = R - 1; r >= 0; --r) {
       float *din = dh[cur], *dout = dh[cur ^ 1];
-      hipLaunchKernelGGL(bwd_node_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, din, hsaved(r),
+      hipLaunchKernelGGL(bwd_node_kernel, dim3(kBwdBlocks), dim3(kPairT), 0, s, din, hsaved(r),
                          asaved(r), batch, nx, ny, r, pack, F, L, dout, dagg, part);
       if (int rc = launch_check("bwd_node_kernel")) return rc;
-      hipLaunchKernelGGL(bwd_edge_recv_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dagg, hsaved(r),
+      hipLaunchKernelGGL(bwd_edge_recv_kernel, dim3(kBwdBlocks), dim3(kPairT), 0, s, dagg, hsaved(r),
                          batch, nx, ny, r, pack, F, L, dq, part);
       if (int rc = launch_check("bwd_edge_recv_kernel")) return rc;
-      hipLaunchKernelGGL(bwd_edge_send_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dq, hsaved(r),
+      hipLaunchKernelGGL(bwd_edge_send_kernel, dim3(kBwdBlocks), dim3(kPairT), 0, s, dq, hsaved(r),
                          batch, nx, ny, r, pack, F, L, dagg, dout, part);
       if (int rc = launch_check("bwd_edge_send_kernel")) return rc;
       cur ^= 1;
     }
-    hipLaunchKernelGGL(bwd_encoder_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, dh[cur],
+    hipLaunchKernelGGL(bwd_encoder_kernel, dim3(kBwdBlocks), dim3(kPairT), 0, s, dh[cur],
                        (const uint16_t *)at(saved, SL.x), (const uint16_t *)at(saved, SL.e1),
                        batch, nx, ny, pack, F, L, part);
     if (int rc = launch_check("bwd_encoder_kernel")) return rc;

@@ -295,6 +295,31 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Workgroup barrier that makes this wave's LDS writes visible (lgkmcnt(0))
+// but does not wait for its global stores.  __syncthreads() cannot be used
+// in a loop with direct-to-LDS loads: its release fence then waits for every
+// vector memory operation, fresh stores included.  The loads into LDS are
+// waited for explicitly (s_waitcnt) before the barrier that publishes them; the
+// memory clobber keeps the compiler from moving memory accesses across it.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Raw buffer resource of `bytes` bytes at base + offset: the hardware drops
+// stores at offsets past its end.  Base and size are wave-uniform; saying so keeps
+// the resource in scalar registers (no per-lane loop over resources).
+constexpr int kBufferRsrcWord3 = 0x00020000;
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_resource(void *base, size_t offset,
+                                                                int bytes) {
+  const uint64_t pb = (uint64_t)base + offset;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)pb);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(pb >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void *)(((uint64_t)hi << 32) | lo), 0,
+                                           __builtin_amdgcn_readfirstlane(bytes),
+                                           kBufferRsrcWord3);
+}
+
 // ------------------------------------------------------------------ gate ---
 
 // The per-step fallback gate.  The kernel that produces the corrected step

@@ -408,34 +408,14 @@ static_assert(HALO_X == 18 && magic_divisions_exact(), "staging divisions");
 // for this wave's vector memory operations only (the stores counted too).
 constexpr int kWaitVmcnt0 = 0x0F70;
 
-// Workgroup barrier that makes this wave's LDS writes visible (lgkmcnt(0))
-// but does not wait for its global stores.  __syncthreads() cannot be used
-// inside the tile loop: with direct-to-LDS loads in the kernel its release
-// fence waits for every vector memory operation, the fresh stores of the
-// tile included.  The loads into LDS are waited for explicitly
-// (kWaitVmcnt0) before the barrier that publishes them; the memory clobber
-// keeps the compiler from moving memory accesses across the barrier.
 // Stores a row's fragments (chunks q and 4 + q of the node in lane 16 q + n)
 // through a raw buffer resource of `bytes` bytes at `base`: stores at
 // offsets past the range are dropped by the hardware.
 constexpr int kNodeStateBytes = HID * 2;
-constexpr int kBufferRsrcWord3 = 0x00020000;
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_row(uint16_t *base, int bytes, int off, const u32x4 (&v)[2]) {
-  // base and bytes are wave-uniform; saying so keeps the resource in scalar
-  // registers (no per-lane loop over resources)
-  const uint64_t pb = (uint64_t)base;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)pb);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(pb >> 32));
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      (void *)(((uint64_t)hi << 32) | lo), 0, __builtin_amdgcn_readfirstlane(bytes),
-      kBufferRsrcWord3);
+  const __amdgpu_buffer_rsrc_t rs = rows_resource(base, 0, bytes);
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4_t, v[0]), rs, off, 0, 0);
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4_t, v[1]), rs, off + 64, 0, 0);
-}
-
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 template <bool HEAD, bool PULL, bool SAVE>

@@ -135,7 +135,7 @@ inline size_t step_workspace_bytes(int nx, int ny, int R) {
 
 // Backward scratch: packed weights, two FP32 node-gradient buffers
 // (ping-pong over the rounds), FP32 gradients of the summed messages, BF16
-// per-edge gradients of the edge-layer pre-activations [N][8][64], and one
+// per-edge gradients of the edge-layer pre-activations (8 x 64 per node), and one
 // FP32 partial parameter gradient per wave of the fixed backward grid.
 constexpr int kBwdBlocks = 256;
 constexpr int kBwdWaves = kBwdBlocks * 4;
