@@ -249,6 +249,15 @@ int lbm_step_gnn(const float *g_src, float *g_dst, int nx, int ny, float tau,
                  const float *params, int n_rounds, const lbm_fallback *fb,
                  void *workspace, size_t ws_bytes, void *stream);
 
+/* nsteps steps of lbm_step_gnn in one call, alternately from g_a into g_b and back:
+ * the states, flags, decisions and masses of as many single calls, with the weights
+ * packed once on small lattices.  The last state is in g_b if nsteps is odd, in
+ * g_a if it is even; the other buffer holds the state before it.  nsteps >= 1;
+ * other arguments and errors as for lbm_step_gnn. */
+int lbm_steps_gnn(float *g_a, float *g_b, int nx, int ny, float tau,
+                  const float *params, int n_rounds, int nsteps,
+                  const lbm_fallback *fb, void *workspace, size_t ws_bytes,
+                  void *stream);
 /* lbm_step_gnn without a workspace and without any allocation, for callers
  * that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  The step's scratch

@@ -31,7 +31,7 @@ EXPORTS = [
     "lbm_step_gnn", "lbm_step_gnn_noalloc", "gnn_forward", "gnn_backward", "gnn_mse",
     "gnn_mse_weighted", "gnn_adam",
     "lbm_step_simple", "lbm_step_simple_channel", "lbm_steps_simple_max", "lbm_steps_simple",
-    "lbm_steps_simple_channel", "simple_forward", "gnn_gelu_rate",
+    "lbm_steps_simple_channel", "lbm_steps_gnn", "simple_forward", "gnn_gelu_rate",
     "lbm_workspace_bytes",
 ]
 
@@ -99,6 +99,7 @@ def load(path: str = LIB_PATH):
         "lbm_step_simple": ([vp, vp, i, i, f, vp, ctypes.POINTER(LbmFallback), vp, sz, vp], i),
         "lbm_step_simple_channel": ([vp, vp, i, i, f, f, vp, ctypes.POINTER(LbmFallback), vp, sz,
                                      vp], i),
+        "lbm_steps_gnn": ([vp, vp, i, i, f, vp, i, i, ctypes.POINTER(LbmFallback), vp, sz, vp], i),
         "lbm_steps_simple_max": ([i, i], i),
         "lbm_steps_simple": ([vp, vp, i, i, f, vp, i, ctypes.POINTER(LbmFallback), vp, sz, vp], i),
         "lbm_steps_simple_channel": ([vp, vp, i, i, f, f, vp, i, ctypes.POINTER(LbmFallback), vp,

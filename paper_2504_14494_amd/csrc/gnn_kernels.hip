@@ -348,6 +348,8 @@ struct HeadArgs {
   float *save_z;          // [N][12] head outputs kept for the backward pass
   Q80 *pmass;             // [gridDim.x] sum of g* over the nodes of a workgroup
   unsigned *pflag;        // [gridDim.x] 1 if a population came out negative / non-finite
+  const double *mass;     // gate's reference mass, copied to mold by the small kernel, or NULL
+  double *mold;
 };
 
 // Corrected collision of one node (Eq. 3 with the projected correction),
@@ -930,6 +932,8 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gnn_small_kernel(
   const int tile = blockIdx.x, tx = tile % txn, ty = tile / txn % tyn, b = tile / txn / tyn;
   const int x0 = tx * TILE_X, y0 = ty * kSmallY;
   const float *lat = args.src + (size_t)b * ny * 9 * nx;
+  // what the gate, whose first workgroup updates the mass, compares with
+  if (args.mass && blockIdx.x == 0 && threadIdx.x == 0) *args.mold = *args.mass;
 
   // The populations of the frame's nodes, one node per lane, and the weights
   // are all requested before the first wait.
@@ -1239,7 +1243,10 @@ __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
     if ((int)threadIdx.x < s) sm[threadIdx.x] += sm[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *gate.mass = (double)nodes + sm[0];
+  if (threadIdx.x == 0) {
+    *gate.mass = (double)nodes + sm[0];
+    ctrl[kCtrlFallback] = 0u;  // for the next step on the same packed weights
+  }
 }
 
 }  // namespace gnn
@@ -1291,19 +1298,32 @@ int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, const
   return launch_check("gnn_prep_kernel");
 }
 
-// Launches weight packing, encoder and rounds.  src: populations the
-// collision starts from (post-collision state of the previous step when
-// PULL, else pre-collision); the last kernel writes dst and *nparts mass and
-// flag partials.
+// Small lattices take one fused kernel, up to two workgroups per CU one after
+// the other: gated steps took 24 us at 128^2 (256 tiles; encoder and rounds
+// launched on their own 46), 39 at 160 x 160 (400 tiles; 43) and 55 at 192^2
+// (576 tiles; 54).
+static bool small_lattice(int batch, int nx, int ny, int R) {
+  const long long tiles =
+      (long long)batch * ((nx + TILE_X - 1) / TILE_X) * ((ny + kSmallY - 1) / kSmallY);
+  return R <= kSmallRounds && tiles <= 2 * device_cus();
+}
+
+// Launches weight packing (unless `packed`, for a small lattice: the scratch holds
+// these weights), encoder and rounds.  src: populations the collision starts from
+// (post-collision state of the previous step when PULL, else pre-collision); the
+// last kernel writes dst and *nparts mass and flag partials.
 int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, int ny,
                    const float *tau_arr, float tau, const float *params, int R, float *head_out,
-                   void *saved, void *ws, const lbm_fallback *fb, int *nparts, hipStream_t s) {
+                   void *saved, void *ws, const lbm_fallback *fb, int *nparts, hipStream_t s,
+                   bool packed = false) {
   const long long nodes = (long long)batch * nx * ny;
   const FragLayout F = frag_layout(R);
   const ForwardScratch W = forward_scratch(nodes);
   uint8_t *pack = (uint8_t *)at(ws, W.pack);
   unsigned *ctrl = (unsigned *)at(ws, W.ctrl);
-  if (int rc = launch_prep(params, R, pack, ctrl, fb ? fb->mass : nullptr, s)) return rc;
+  const bool small = !saved && small_lattice(batch, nx, ny, R);
+  if (!packed)
+    if (int rc = launch_prep(params, R, pack, ctrl, fb && !small ? fb->mass : nullptr, s)) return rc;
 
   const int cus = device_cus();
   const bool save = saved != nullptr;
@@ -1314,13 +1334,8 @@ int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, i
     return (uint16_t *)at(ws, (r & 1) ? W.hB : W.hA);
   };
 
-  // Small lattices take one fused kernel, up to two workgroups per CU one after
-  // the other: gated steps took 24 us at 128^2 (256 tiles; encoder and rounds
-  // launched on their own 46), 39 at 160 x 160 (400 tiles; 43) and 55 at 192^2
-  // (576 tiles; 54).
-  const long long small_tiles =
-      (long long)batch * ((nx + TILE_X - 1) / TILE_X) * ((ny + kSmallY - 1) / kSmallY);
-  if (R <= kSmallRounds && !save && small_tiles <= 2 * device_cus()) {
+  if (small) {
+    const int small_tiles = batch * ((nx + TILE_X - 1) / TILE_X) * ((ny + kSmallY - 1) / kSmallY);
     HeadArgs ha{};
     ha.src = src;
     ha.dst = dst;
@@ -1329,7 +1344,11 @@ int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, i
     ha.head_out = head_out;
     ha.pmass = (Q80 *)at(ws, W.pmass);
     ha.pflag = (unsigned *)at(ws, W.pflag);
-    *nparts = (int)small_tiles;
+    if (fb) {
+      ha.mass = fb->mass;
+      ha.mold = (double *)(ctrl + kCtrlMass);
+    }
+    *nparts = small_tiles;
     const dim3 grid((unsigned)small_tiles), block(kSmallThreads);
     if (pull && R == 1)
       hipLaunchKernelGGL((gnn_small_kernel<1, true>), grid, block, 0, s, batch, nx, ny, pack, F, ha);
@@ -1464,10 +1483,10 @@ extern "C" int gnn_forward(const float *g_pre, float *g_post, int batch, int nx,
 // lbm_step_gnn on a given scratch of forward_scratch(nx * ny) bytes or more.
 static int step_gnn(const float *g_src, float *g_dst, int nx, int ny, float tau,
                     const float *params, int n_rounds, const lbm_fallback *fb, void *workspace,
-                    hipStream_t s) {
+                    hipStream_t s, bool packed = false) {
   int nparts;
   if (int rc = launch_forward(true, g_src, g_dst, 1, nx, ny, nullptr, tau, params, n_rounds,
-                              nullptr, nullptr, workspace, fb, &nparts, s))
+                              nullptr, nullptr, workspace, fb, &nparts, s, packed))
     return rc;
   if (!fb) return LBM_OK;
   const ForwardScratch W = forward_scratch((long long)nx * ny);
@@ -1500,6 +1519,28 @@ extern "C" int lbm_step_gnn(const float *g_src, float *g_dst, int nx, int ny, fl
   if (int rc = check_device()) return rc;
   return step_gnn(g_src, g_dst, nx, ny, tau, params, n_rounds, fb, workspace,
                   (hipStream_t)stream);
+}
+
+// A step of a small lattice is two short kernels besides the packing of the
+// weights, which takes as long as the gate: several steps pack once.  128^2, gated:
+// 23.0 us a step one by one, 19.7 so.  Larger lattices would gain a 400th.
+extern "C" int lbm_steps_gnn(float *g_a, float *g_b, int nx, int ny, float tau,
+                             const float *params, int n_rounds, int nsteps,
+                             const lbm_fallback *fb, void *workspace, size_t ws_bytes,
+                             void *stream) {
+  if (int rc = check_step_gnn("lbm_steps_gnn", g_a, g_b, nx, ny, tau, params, n_rounds, fb))
+    return rc;
+  if (nsteps < 1) return fail(LBM_EINVAL, "lbm_steps_gnn: nsteps %d", nsteps);
+  const size_t need = step_workspace_bytes(nx, ny, n_rounds);
+  if (!workspace || ws_bytes < need)
+    return fail(LBM_EWORKSPACE, "lbm_steps_gnn: workspace needs %zu bytes", need);
+  if (int rc = check_device()) return rc;
+  const bool small = small_lattice(1, nx, ny, n_rounds);
+  for (int k = 0; k < nsteps; ++k)
+    if (int rc = step_gnn(k & 1 ? g_b : g_a, k & 1 ? g_a : g_b, nx, ny, tau, params, n_rounds, fb,
+                          workspace, (hipStream_t)stream, small && k > 0))
+      return rc;
+  return LBM_OK;
 }
 
 // ------------------------------------------------- allocation-free step ---

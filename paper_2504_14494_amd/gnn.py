@@ -99,22 +99,36 @@ class Fallback:
                            self.mass.data_ptr())
 
 
-def lbm_step_gnn(src: torch.Tensor, dst: torch.Tensor, tau: float, blob: torch.Tensor,
-                 rounds: int = 2, fallback: Fallback = None, ws: Workspace = None):
+def _gnn_step_args(src, dst, blob, rounds, fallback, ws):
     _need(src, torch.float32, "src")
     _need(dst, torch.float32, "dst")
     if src.dim() != 3 or src.shape[1] != 9 or src.shape != dst.shape:
         raise ValueError("src and dst must both be [ny, 9, nx]")
     _check_blob(blob, rounds)
     ny, nx = int(src.shape[0]), int(src.shape[2])
-    L = _lib.load()
-    wsb = L.lbm_workspace_bytes(_lib.LBM_WS_GNN_STEP, 1, nx, ny, rounds)
-    buf = (ws or _ws).get(wsb)
+    wsb = _lib.load().lbm_workspace_bytes(_lib.LBM_WS_GNN_STEP, 1, nx, ny, rounds)
     fb = ctypes.byref(fallback.struct()) if fallback is not None else None
-    rc = L.lbm_step_gnn(_ptr(src), _ptr(dst), nx, ny, float(tau), _ptr(blob), rounds, fb,
-                        _ptr(buf), buf.numel(), _stream())
+    return nx, ny, fb, (ws or _ws).get(wsb)
+
+
+def lbm_step_gnn(src: torch.Tensor, dst: torch.Tensor, tau: float, blob: torch.Tensor,
+                 rounds: int = 2, fallback: Fallback = None, ws: Workspace = None):
+    nx, ny, fb, buf = _gnn_step_args(src, dst, blob, rounds, fallback, ws)
+    rc = _lib.load().lbm_step_gnn(_ptr(src), _ptr(dst), nx, ny, float(tau), _ptr(blob), rounds, fb,
+                                  _ptr(buf), buf.numel(), _stream())
     check(rc, "lbm_step_gnn")
     return dst
+
+
+def lbm_steps_gnn(a: torch.Tensor, b: torch.Tensor, tau: float, blob: torch.Tensor, nsteps: int,
+                  rounds: int = 2, fallback: Fallback = None, ws: Workspace = None):
+    """nsteps steps of lbm_step_gnn in one call, alternately from a into b and
+    back.  Returns the buffer of the last state: b if nsteps is odd, else a."""
+    nx, ny, fb, buf = _gnn_step_args(a, b, blob, rounds, fallback, ws)
+    rc = _lib.load().lbm_steps_gnn(_ptr(a), _ptr(b), nx, ny, float(tau), _ptr(blob), rounds,
+                                   int(nsteps), fb, _ptr(buf), buf.numel(), _stream())
+    check(rc, "lbm_steps_gnn")
+    return b if nsteps % 2 else a
 
 
 def lbm_step_gnn_noalloc(src: torch.Tensor, dst: torch.Tensor, tau: float, blob: torch.Tensor,
@@ -304,6 +318,8 @@ class GnnLattice(Lattice):
                 lbm_steps_simple(src, dst, tau, self.blob, k, fb, self.ws)
             elif self.rounds == 0:
                 lbm_step_simple(src, dst, tau, self.blob, fb, self.ws)
+            elif k > 1:
+                lbm_steps_gnn(src, dst, tau, self.blob, k, self.rounds, fb, self.ws)
             else:
                 lbm_step_gnn(src, dst, tau, self.blob, self.rounds, fb, self.ws)
 
@@ -318,7 +334,7 @@ class GnnLattice(Lattice):
             step(self.a.clone(), torch.empty_like(self.a), tmp)
         return self._run(("gnn", float(tau), bool(gate)) + self._graph_key(gate),
                          lambda s, d, k: step(s, d, fb, k), warm, n, graph,
-                         self._most_simple if self.rounds == 0 else 1)
+                         self._most_simple if self.rounds == 0 else 1, pair=self.rounds > 0)
 
     def step_gnn_channel(self, tau: float, gx: float, n: int = 1, gate: bool = True,
                          graph: bool = False):

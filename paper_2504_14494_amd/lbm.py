@@ -260,7 +260,7 @@ class Lattice:
         self._most = lbm_steps_max(nx, ny, dtype)
         self._most_walls = lbm_steps_max(nx, ny, dtype, walls=True)
 
-    def _capture(self, advance, warmup, most):
+    def _capture(self, advance, warmup, most, pair=False):
         """HIP graph of GRAPH_CHUNK steps from self.a, ping-ponging with
         self.b over an even number of launches, so that the state returns to
         self.a.  `warmup()` runs one step on scratch copies first, on the
@@ -277,6 +277,9 @@ class Lattice:
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g):
             src, dst = self.a, self.b
+            if pair:
+                advance(src, dst, self.GRAPH_CHUNK)
+                return g
             for k in _shares(self.GRAPH_CHUNK, launches):
                 advance(src, dst, k)
                 src, dst = dst, src
@@ -288,19 +291,26 @@ class Lattice:
         cannot leave it pointing at freed memory."""
         return [self.a, self.b]
 
-    def _run(self, key, advance, warmup, n: int, graph: bool, most: int = 1):
+    def _run(self, key, advance, warmup, n: int, graph: bool, most: int = 1, pair: bool = False):
         """n steps: whole chunks from a captured graph when `graph`, the rest
-        eagerly.  advance(src, dst, k) takes src k steps on into dst, k <= most."""
+        eagerly.  advance(src, dst, k) takes src k steps on into dst, k <= most;
+        with `pair` any k, alternately into dst and src (back in src if k is even)."""
         if graph and n >= self.GRAPH_CHUNK and 2 * most <= self.GRAPH_CHUNK:
             k = (key, self.a.data_ptr())
             if k not in self._graphs:
-                g = self._capture(advance, warmup, most)
+                g = self._capture(advance, warmup, most, pair)
                 self._graphs[k] = (g, list(self._graph_buffers()))
             g = self._graphs[k][0]
             for _ in range(n // self.GRAPH_CHUNK):
                 g.replay()
             self.steps += (n // self.GRAPH_CHUNK) * self.GRAPH_CHUNK
             n %= self.GRAPH_CHUNK
+        if pair and n > 1:
+            advance(self.a, self.b, n)
+            if n % 2:
+                self.a, self.b = self.b, self.a
+            self.steps += n
+            return self
         for k in _shares(n, -(-n // most)) if n > 1 else (1,) * n:
             advance(self.a, self.b, k)
             self.a, self.b = self.b, self.a
