@@ -948,9 +948,9 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gnn_small_kernel(
     const int f = k * kSmallWaves + wave;
     wl[k] = frags[(size_t)(f < G::kFrags ? f : 0) * 64 + lane];
   }
-  f32x4 bl = {};
-  if (threadIdx.x < G::kBias * 4)
-    bl = bias[(size_t)(threadIdx.x >> 2) * 64 + 16 * (threadIdx.x & 3)];
+  // (no branch: the compiler would wait in it, for the weights too)
+  const unsigned bt = threadIdx.x < G::kBias * 4 ? threadIdx.x : 0u;
+  const f32x4 bl = bias[(size_t)(bt >> 2) * 64 + 16 * (bt & 3)];
   const float sdelta = cst[C_SDELTA];
   if (framed) {
     const lbm::Moments<float> M = lbm::node_moments(gp);
@@ -965,13 +965,13 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gnn_small_kernel(
                  pack_bf16(ft[6], ft[7])};
     o[1] = u32x4{pack_bf16(ft[8], ft[9]), pack_bf16(ft[10], ft[11]), 0u, 0u};
   }
+  // The encoder's weights first: the others arrive while it runs (256 gated steps
+  // of 128^2: 5029 -> 4932 us).
+  constexpr int kEncLoads = (12 + kSmallWaves - 1) / kSmallWaves;
 #pragma unroll
-  for (int k = 0; k < kLoads; ++k) {
-    const int f = k * kSmallWaves + wave;
-    if (f < G::kFrags) w_s[f * 64 + lane] = wl[k];
-  }
+  for (int k = 0; k < kEncLoads; ++k) w_s[(k * kSmallWaves + wave) * 64 + lane] = wl[k];
   if (threadIdx.x < G::kBias * 4) b_s[threadIdx.x] = bl;
-  __syncthreads();
+  lds_barrier();
 
   const u32x4 *w = w_s + lane;
   const f32x4 *bs = b_s + q;
@@ -992,6 +992,11 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gnn_small_kernel(
     u32x4 *dst = (u32x4 *)(h_s[0] + k * kNodeBytes);
     dst[q] = frag_from_acc(a[0], a[1]);  // (lanes past the frame repeat its last node)
     dst[4 + q] = frag_from_acc(a[2], a[3]);
+  }
+#pragma unroll
+  for (int k = kEncLoads; k < kLoads; ++k) {
+    const int f = k * kSmallWaves + wave;
+    if (f < G::kFrags) w_s[f * 64 + lane] = wl[k];
   }
   __syncthreads();
 
@@ -1299,7 +1304,7 @@ int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, const
 }
 
 // Small lattices take one fused kernel, up to two workgroups per CU one after
-// the other: gated steps took 24 us at 128^2 (256 tiles; encoder and rounds
+// the other: gated steps took 23 us at 128^2 (256 tiles; encoder and rounds
 // launched on their own 46), 39 at 160 x 160 (400 tiles; 43) and 55 at 192^2
 // (576 tiles; 54).
 static bool small_lattice(int batch, int nx, int ny, int R) {
@@ -1523,7 +1528,7 @@ extern "C" int lbm_step_gnn(const float *g_src, float *g_dst, int nx, int ny, fl
 
 // A step of a small lattice is two short kernels besides the packing of the
 // weights, which takes as long as the gate: several steps pack once.  128^2, gated:
-// 23.0 us a step one by one, 19.7 so.  Larger lattices would gain a 400th.
+// 22.6 us a step one by one, 19.3 so.  Larger lattices would gain a 400th.
 extern "C" int lbm_steps_gnn(float *g_a, float *g_b, int nx, int ny, float tau,
                              const float *params, int n_rounds, int nsteps,
                              const lbm_fallback *fb, void *workspace, size_t ws_bytes,
