@@ -932,8 +932,6 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gnn_small_kernel(
   const int tile = blockIdx.x, tx = tile % txn, ty = tile / txn % tyn, b = tile / txn / tyn;
   const int x0 = tx * TILE_X, y0 = ty * kSmallY;
   const float *lat = args.src + (size_t)b * ny * 9 * nx;
-  // what the gate, whose first workgroup updates the mass, compares with
-  if (args.mass && blockIdx.x == 0 && threadIdx.x == 0) *args.mold = *args.mass;
 
   // The populations of the frame's nodes, one node per lane, and the weights
   // are all requested before the first wait.
@@ -1017,6 +1015,8 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gnn_small_kernel(
     const int wo = G::width(r), no = wo * G::rows(r);
     if (last && (wave == 4 || wave == 5))
       node_pops<PULL>(lat, nx, ny, inside ? xo : x0, inside ? yo : y0, gp);
+    // what the gate, whose first workgroup updates the mass, compares with
+    if (last && wave == 6 && blockIdx.x == 0 && lane == 0 && args.mass) *args.mold = *args.mass;
     if (16 * wave < no) {
       const int k = 16 * wave + n < no ? 16 * wave + n : no - 1;
       const int ry = k / wo, rx = k - ry * wo;
@@ -1184,11 +1184,11 @@ __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
   {
     Q80 m{0ull, 0ll};
     unsigned f = 0;
+    const double mold = *(const double *)(ctrl + kCtrlMass);  // (loaded with the partials)
     for (int k = threadIdx.x; k < gate.nparts; k += kThreads) {
       m = q80_add(m, gate.pmass[k]);
       f |= gate.pflag[k];
     }
-    const double mold = *(const double *)(ctrl + kCtrlMass);
     put_partial(part_s, m, f);
     __syncthreads();
     const PartialSlot sum = sum_partials(part_s, 0, kWaves);
