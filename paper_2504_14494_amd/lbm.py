@@ -243,13 +243,14 @@ class Lattice:
     lattice), which writes only the last state.  Stepping methods take
     `graph=True` to run whole chunks of steps as one captured HIP graph
     (torch.cuda.CUDAGraph over the library's launches on the current stream),
-    which removes the per-launch host cost that dominates small lattices; a
-    lattice whose steps one launch takes by the thousand needs none.  The
-    graph holds the buffer addresses, so one is captured per (step kind,
-    parameters, buffer holding the state) and replayed.  Results are bitwise
+    which removes the per-launch host cost that dominates small lattices (larger
+    ones, and those whose steps one launch takes by the thousand, run eagerly all
+    the same).  The graph holds the buffer addresses, so one is captured per (step
+    kind, parameters, buffer holding the state) and replayed.  Results are bitwise
     those of single eager steps."""
 
     GRAPH_CHUNK = 64   # steps per captured graph
+    GRAPH_BYTES = 65536  # of one population, the largest whose several steps replay faster
 
     def __init__(self, nx: int, ny: int, dtype=torch.float32, device="cuda"):
         self.nx, self.ny = nx, ny
@@ -295,6 +296,12 @@ class Lattice:
         """n steps: whole chunks from a captured graph when `graph`, the rest
         eagerly.  advance(src, dst, k) takes src k steps on into dst, k <= most;
         with `pair` any k, alternately into dst and src (back in src if k is even)."""
+        # Several steps of a larger lattice in one launch outlast the 9 us it takes
+        # to issue one, and a capture costs 1 to 5 ms (640 steps, replayed and
+        # eager: 534 and 719 us at 64^2 FP32, 661 and 700 at 128^2; 917 and 880 at
+        # 128^2 FP64, 972 and 922 at 256^2 FP32, 2455 and 2258 at 512^2 FP64).
+        if most > 1 and self.a.nbytes > 9 * self.GRAPH_BYTES:
+            graph = False
         if graph and n >= self.GRAPH_CHUNK and 2 * most <= self.GRAPH_CHUNK:
             k = (key, self.a.data_ptr())
             if k not in self._graphs:

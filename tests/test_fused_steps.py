@@ -94,3 +94,17 @@ def test_most_steps_and_refusals_need_no_gpu():
     assert L.lbm_steps_bgk(pa, pb, 64, 0, 0.8, 2, None) == EINVAL
     assert L.lbm_steps_bgk(pa, pb, 64, 64, 0.0, 2, None) == EINVAL
     assert L.lbm_steps_channel(pa, pb, 64, 64, 0.5, 1e-6, 2, None) == EINVAL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny,dtype,captured", [
+    (128, 128, torch.float32, True), (129, 128, torch.float32, False),
+    (64, 128, torch.float64, True), (65, 128, torch.float64, False)])
+def test_graph_is_taken_up_to_its_size(nx, ny, dtype, captured):
+    start = torch.as_tensor(inputs.random_shifted_state((ny, 9, nx), 1e-3, 3), dtype=dtype)
+    a, b = (lbm.Lattice(nx, ny, dtype).load(start) for _ in range(2))
+    for n in (130, 64):
+        a.step_bgk(0.7, n, graph=True)
+        b.step_bgk(0.7, n)
+    assert torch.equal(a.g, b.g) and a.steps == b.steps == 194
+    assert bool(a._graphs) == captured
