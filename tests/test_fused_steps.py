@@ -6,7 +6,7 @@ import ctypes
 import pytest
 import torch
 
-from paper_2504_14494_amd import _lib, lbm
+from paper_2504_14494_amd import _lib, inputs, lbm
 
 EINVAL = -1
 
