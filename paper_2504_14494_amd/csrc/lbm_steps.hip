@@ -214,31 +214,44 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(
 
 // ----------------------------------------------------------------- tiles ---
 
-constexpr int kTileThreads = 1024;
-
 // nsteps steps of a region of rx x ry nodes, one node per thread, passed from
-// step to step through LDS (the eight directions that move; `bufs` buffers in
-// turn: one barrier per step with two, two with one).  The first step pulls
+// step to step through LDS (the eight directions that move, PLANE values each;
+// one barrier per step with two buffers in turn, two with one).  The first step pulls
 // from memory.  RESIDENT: the region is the whole lattice, whose neighbours
 // wrap inside it, and nsteps is any number; else every further step spoils one
 // more ring of the region, and the nodes at least nsteps - 1 away from its edge
 // are stored.
-template <typename T, bool WALLS, bool RESIDENT>
-__global__ __launch_bounds__(kTileThreads) void tile_kernel(const T *__restrict__ src,
+//
+// A step is some 100 VALU instructions and 16 LDS accesses; PLANE is a constant,
+// and the steps come in pairs, so that the places in LDS are offsets of the
+// accesses instead of 16 additions (1024 steps of 64^2: 851 -> 767 us; 2048 of a
+// 4 x 32 channel, resident: 782 -> 629; pairs of one 512^2 FP64 run: -2 %).
+template <typename T, bool WALLS, bool RESIDENT, int PLANE>
+__global__ __launch_bounds__(PLANE) void tile_kernel(const T *__restrict__ src,
                                                             T *__restrict__ dst, int nx, int ny,
-                                                            int rx, int ry, int nsteps, int txn,
-                                                            int bufs, T omega, T gx) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t tile_lds[];
-  T *lds = (T *)tile_lds;
-  const int nodes = rx * ry, plane = (int)blockDim.x;
+                                                            int rx, int ry, unsigned inv_rx,
+                                                            int nsteps, int txn, T omega,
+                                                            T gx) {
+  // two buffers while two workgroups still fit the LDS of a CU
+  constexpr int kBufs = 2 * 8 * PLANE * sizeof(T) <= 65536 ? 2 : 1;
+  __shared__ T lds[kBufs * 8 * PLANE];
+  const int nodes = rx * ry;
   const int halo = RESIDENT ? 0 : nsteps - 1;
   const int k = threadIdx.x < (unsigned)nodes ? (int)threadIdx.x : nodes - 1;
-  const int ty = k / rx, tx = k - ty * rx;
+  // The entry was as many instructions as three steps: no divisions by the region's
+  // or the lattice's sides (k < 2^10 and inv_rx = ceil(2^20 / rx) give k / rx
+  // exactly), and the neighbours' places are sums.
+  const int ty = (int)(__umul24((unsigned)k, inv_rx) >> 20), tx = k - (int)__umul24(ty, rx);
   const int by = blockIdx.x / txn, bx = blockIdx.x - by * txn;
   const int xg = bx * (rx - 2 * halo) + tx - halo, yg = by * (ry - 2 * halo) + ty - halo;
-  int x = xg % nx, y = yg % ny;
-  x = x < 0 ? x + nx : x;
-  y = y < 0 ? y + ny : y;
+  int x = xg < 0 ? xg + nx : (xg >= nx ? xg - nx : xg);
+  int y = yg < 0 ? yg + ny : (yg >= ny ? yg - ny : yg);
+  if (nx < rx || ny < ry) {  // lattices narrower than a region
+    x = xg % nx;
+    y = yg % ny;
+    x = x < 0 ? x + nx : x;
+    y = y < 0 ? y + ny : y;
+  }
   if (WALLS) y = yg < 0 ? 0 : (yg >= ny ? ny - 1 : yg);
   T g[9];
   if constexpr (WALLS)
@@ -248,34 +261,35 @@ __global__ __launch_bounds__(kTileThreads) void tile_kernel(const T *__restrict_
   collide_at<T, WALLS>(g, omega, gx);
   // where population i of the next step comes from (the edge of a region
   // reads itself: those nodes are spoilt anyway)
+  const int last_x = rx - 1, last_y = (int)__umul24(ry - 1, rx);
+  const int left = tx > 0 ? -1 : (RESIDENT ? last_x : 0);
+  const int right = tx < last_x ? 1 : (RESIDENT ? -last_x : 0);
+  const int down = ty > 0 ? -rx : (RESIDENT && !WALLS ? last_y : 0);
+  const int up = ty < ry - 1 ? rx : (RESIDENT && !WALLS ? -last_y : 0);
   int from[9];
 #pragma unroll
   for (int i = 1; i < 9; ++i) {
-    int sx = tx - cx(i), sy = ty - cy(i), d = i;
-    if (RESIDENT) {
-      sx = sx < 0 ? rx - 1 : (sx == rx ? 0 : sx);
-      if (!WALLS) sy = sy < 0 ? ry - 1 : (sy == ry ? 0 : sy);
-    } else {
-      sx = sx < 0 ? 0 : (sx == rx ? rx - 1 : sx);
-      sy = sy < 0 ? 0 : (sy == ry ? ry - 1 : sy);
-    }
-    if (WALLS && ((cy(i) > 0 && yg == 0) || (cy(i) < 0 && yg == ny - 1))) {
-      sx = tx;
-      sy = ty;
-      d = opp(i);
-    }
-    from[i] = (d - 1) * plane + sy * rx + sx;
+    from[i] = (i - 1) * PLANE + k + (cx(i) > 0 ? left : cx(i) < 0 ? right : 0) +
+              (cy(i) > 0 ? down : cy(i) < 0 ? up : 0);
+    if (WALLS && ((cy(i) > 0 && yg == 0) || (cy(i) < 0 && yg == ny - 1)))
+      from[i] = (opp(i) - 1) * PLANE + k;
+    asm volatile("" : "+v"(from[i]));  // not put together again at every step
   }
-  for (int s = 1; s < nsteps; ++s) {
-    T *buf = bufs == 2 ? lds + (s & 1) * 8 * plane : lds;
+  auto step = [&](T *buf) {
 #pragma unroll
-    for (int i = 1; i < 9; ++i) buf[(i - 1) * plane + threadIdx.x] = g[i];
+    for (int i = 1; i < 9; ++i) buf[(i - 1) * PLANE + threadIdx.x] = g[i];
     __syncthreads();
 #pragma unroll
     for (int i = 1; i < 9; ++i) g[i] = buf[from[i]];
-    if (bufs == 1) __syncthreads();
+    if (kBufs == 1) __syncthreads();
     collide_at<T, WALLS>(g, omega, gx);
+  };
+  int s = 1;
+  for (; s + 1 < nsteps; s += 2) {
+    step(lds + (kBufs - 1) * 8 * PLANE);
+    step(lds);
   }
+  if (s < nsteps) step(lds + (kBufs - 1) * 8 * PLANE);
   if (threadIdx.x < (unsigned)nodes && tx >= halo && tx < rx - halo && ty >= halo &&
       ty < ry - halo && xg < nx && yg < ny) {
     T *d = dst + (size_t)yg * 9 * nx + xg;
@@ -379,22 +393,26 @@ static int launch_march(const T *src, T *dst, int nx, int ny, T omega, T gx, hip
 template <typename T, bool WALLS>
 static int launch_tiles(const T *src, T *dst, int nx, int ny, const StepsPlan &P, int nsteps,
                         T omega, T gx, hipStream_t s) {
-  const bool resident = P.kind == kStepsResident;
-  const int threads = (P.rx * P.ry + 63) / 64 * 64;
-  // two buffers while two workgroups still fit the LDS of a CU
-  const int bufs = (size_t)2 * 8 * threads * sizeof(T) <= 65536 ? 2 : 1;
-  const size_t lds = (size_t)bufs * 8 * threads * sizeof(T);
-  if (resident) {
-    hipLaunchKernelGGL((tile_kernel<T, WALLS, true>), dim3(1), dim3(threads), lds, s, src, dst,
-                       nx, ny, nx, ny, nsteps, 1, bufs, omega, gx);
+  const unsigned inv_rx = ((1u << 20) + P.rx - 1) / P.rx;
+  if (P.kind == kStepsResident) {
+    const int nodes = nx * ny, threads = (nodes + 63) / 64 * 64;
+    auto *kernel = threads <= 128   ? tile_kernel<T, WALLS, true, 128>
+                   : threads <= 512 ? tile_kernel<T, WALLS, true, 512>
+                                    : tile_kernel<T, WALLS, true, 1024>;
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, s, src, dst, nx, ny, nx, ny, inv_rx,
+                       nsteps, 1, omega, gx);
     return launch_check("tile_kernel");
   }
   const int ox = P.rx - 2 * (nsteps - 1), oy = P.ry - 2 * (nsteps - 1);
   const int txn = (nx + ox - 1) / ox;
   const long long blocks = (long long)txn * ((ny + oy - 1) / oy);
   if (blocks > 0x7fffffffLL) return fail(LBM_EINVAL, "lbm_steps: lattice too large");
-  hipLaunchKernelGGL((tile_kernel<T, WALLS, false>), dim3((unsigned)blocks), dim3(threads), lds, s,
-                     src, dst, nx, ny, P.rx, P.ry, nsteps, txn, bufs, omega, gx);
+  const int threads = P.rx * P.ry;
+  auto *kernel = threads == 512   ? tile_kernel<T, WALLS, false, 512>
+                 : threads == 576 ? tile_kernel<T, WALLS, false, 576>
+                                  : tile_kernel<T, WALLS, false, 1024>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, s, src, dst, nx, ny, P.rx,
+                     P.ry, inv_rx, nsteps, txn, omega, gx);
   return launch_check("tile_kernel");
 }
 
