@@ -1,10 +1,12 @@
 """Throughput benchmark of the LBM-GNN hot path on one MI355X.
 
-Headline: MLUPS of the fused D2Q9 BGK pull step on the 8192x8192 Taylor-Green
+Headline: MLUPS of the fused D2Q9 BGK step on the 8192x8192 Taylor-Green
 workload (FP32, row-interleaved SoA, Re = 1000, u0 = 0.04), with the
-populations resident in HBM, and the roofline of that kernel (algorithmic
-72 B per lattice update against 8 TB/s, HBM traffic from the committed
-rocprofv3 counters).  Beside it:
+populations resident in HBM.  Lattice.step_bgk takes several steps per pass over
+the lattice (each computed in full at every node), so its roofline is VALU issue,
+with the 72 B per node and pass against 8 TB/s beside it.  Then:
+  bgk_single_step  the same lattice one step per call, which HBM bounds (72 B per
+               lattice update, traffic from the committed rocprofv3 counters);
   gnn          the GNN-corrected step on 2048x2048 (MLUPS, MFMA and GELU/VALU
                rooflines, committed counter utilisation);
   gnn_per_node the paper's Fig. 2 per-node network fused into the pull step,
@@ -38,6 +40,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 BGK_BYTES_PER_LU = 72           # 9 FP32 loads + 9 FP32 stores per node
+BGK_VALU_PER_LU = 82            # instructions of one node's BGK collision
+VALU_PEAK_TOPS = 39.3           # 256 CUs x 64 lanes x 2.4 GHz, no packed FP32
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bgk_pull_8192_traffic.json")
 
 
@@ -62,9 +66,16 @@ def bgk_src_hash():
     return hashlib.sha256(_read("lbm_common.hpp") + body[a:b]).hexdigest()[:16]
 
 
-def bgk_kernel_name(nx):
-    """The kernel lbm_step_bgk launches for FP32 lattices (any width)."""
-    return "bgk_pull_wave_kernel"
+def bgk_single_leg(lat, tau32, steps):
+    """The lattice one step per call: the HBM-bound kernel of lbm_step_bgk."""
+    import torch
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record()
+    for _ in range(steps):
+        lat.step_bgk(tau32, 1)
+    e1.record()
+    torch.cuda.synchronize()
+    return e0.elapsed_time(e1) / steps
 
 
 def simple_src_hash():
@@ -81,7 +92,7 @@ def gnn_src_hash():
                           _read("channel_common.hpp")).hexdigest()[:16]
 
 
-def bgk_leg(n, re, u0, steps, warmup):
+def bgk_leg(n, re, u0, steps, warmup, single=0):
     import numpy as np
     import torch
     from paper_2504_14494_amd import inputs, lbm
@@ -103,7 +114,10 @@ def bgk_leg(n, re, u0, steps, warmup):
     spec = inputs.tgv_spec(n, n, u0, nu, warmup + steps)
     _, _, _, sums = lat.moments(spec)
     s = sums.cpu().numpy()
+    per_pass = lbm.lbm_steps_max(n, n)
     return {
+        "steps_per_pass": per_pass, "passes": -(-steps // per_pass),
+        "ms_single_step": bgk_single_leg(lat, tau32, single) if single else None,
         "n": n, "re": re, "u0": u0, "tau": tau32, "ms_total": ms, "wall_s": wall,
         "ms_per_step": ms / steps,
         "mlups": n * n * steps / (ms * 1e-3) / 1e6,
@@ -559,15 +573,22 @@ def main():
         print("no GPU visible", file=sys.stderr)
         return 1
 
-    bgk = bgk_leg(args.n, args.re, 0.04, args.steps, args.warmup)
+    bgk = bgk_leg(args.n, args.re, 0.04, args.steps, args.warmup, single=50)
     cp = copy_leg(args.n)
-    achieved = BGK_BYTES_PER_LU * args.n * args.n / (bgk["ms_per_step"] * 1e-3) / 1e9
-    roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-            "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": traffic_entry(),
-            "kernel": bgk_kernel_name(args.n),
-            "copy_ceiling_gbs": round(cp["gbs"], 1),
-            "frac_of_copy": round(achieved / cp["gbs"], 4)}
+    nodes = args.n * args.n
+
+    def hbm_roof(passes, ms):
+        gbs = BGK_BYTES_PER_LU * nodes * passes / (ms * 1e-3) / 1e9
+        return {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": round(gbs / HBM_PEAK_GBS, 4), "copy_ceiling_gbs": round(cp["gbs"], 1),
+                "frac_of_copy": round(gbs / cp["gbs"], 4)}
+
+    ops = BGK_VALU_PER_LU * bgk["mlups"] * 1e6 / 1e12
+    roof = {"bound": "valu", "achieved": round(ops, 2), "peak": VALU_PEAK_TOPS,
+            "unit": "T lane-ops/s", "frac": round(ops / VALU_PEAK_TOPS, 4),
+            "ops_per_lattice_update": BGK_VALU_PER_LU, "steps_per_pass": bgk["steps_per_pass"],
+            "hbm": hbm_roof(bgk["passes"], bgk["ms_total"])}
+    ms1 = bgk["ms_single_step"]
     out = {
         "metric": "D2Q9 MLUPS: plain BGK vs GNN collision at fixed TGV L2 err; "
                   "% HBM/MFMA peak",
@@ -587,6 +608,9 @@ def main():
                                f"Re={args.re:g}, u0=0.04, fused pull collide+stream",
                    "nx": args.n, "ny": args.n, "re": args.re, "tau": bgk["tau"]},
         "roofline": roof,
+        "bgk_single_step": {"ms_per_step": round(ms1, 5), "mlups": round(nodes / (ms1 * 1e3), 1),
+                            "kernel": "bgk_pull_wave_kernel",
+                            "roofline": dict(hbm_roof(1, ms1), traffic=traffic_entry())},
         "tgv_l2_err_bgk": bgk["tgv_l2_err"],
     }
     if args.n == 8192:

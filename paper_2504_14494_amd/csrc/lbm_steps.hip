@@ -321,9 +321,9 @@ enum StepsKind { kStepsResident, kStepsTile, kStepsMarch };
 //    next to nothing but needs many waves: 512^2 3.2, 1024^2 5.8 against 7.7 in
 //    tiles; FP64 4.2 and 10.3.  It takes 224 columns at a time, so lattices
 //    that would leave most of them idle stay with the tiles.
-// March: five steps where the state leaves the Infinity Cache (8192^2: 4 at a
-// time 230 us per step, 5 at a time 201, 6 at a time 199 with three waves per
-// SIMD left), four where it stays (1501 x 1003: 6.6 against 7.0), and fewer in
+// March: five steps where the state leaves the Infinity Cache (8192^2: 217 us per
+// step; four at a time 14 % slower, six 1 % faster with three waves per SIMD
+// left), four where it stays (1501 x 1003: 6.6 against 7.0), and fewer in
 // FP64, whose rows take twice the registers.
 struct StepsPlan {
   StepsKind kind;
