@@ -32,7 +32,8 @@ namespace gnn {
 
 // simple_backward.hip
 int launch_simple_backward(const float *G, const float *g_pre, const float *tau, const float *z0,
-                           int batch, int nx, int ny, const uint8_t *pack, float *part, hipStream_t s);
+                           int batch, int nx, int ny, const float *params, float *part,
+                           hipStream_t s);
 
 // The kernels below but the head's give two waves, on one SIMD, the chunks of one
 // partial, each half of the 64 channels: every sum keeps the order it has with one
@@ -936,7 +937,8 @@ extern "C" int gnn_backward(const float *dL_dgpost, const float *g_pre, const vo
   const BackwardScratch W = backward_scratch(nodes, R);
   const SavedLayout SL = saved_layout(nodes, R);
   uint8_t *pack = (uint8_t *)at(workspace, W.pack);
-  if (int rc = launch_prep(params, R, pack, nullptr, nullptr, s)) return rc;
+  if (R > 0)
+    if (int rc = launch_prep(params, R, pack, nullptr, nullptr, s)) return rc;
   float *part = (float *)at(workspace, W.part);
   float *dh[2] = {(float *)at(workspace, W.dhA), (float *)at(workspace, W.dhB)};
   float *dagg = (float *)at(workspace, W.dagg);
@@ -947,7 +949,7 @@ extern "C" int gnn_backward(const float *dL_dgpost, const float *g_pre, const vo
 
   if (R == 0) {  // the per-node network, one kernel
     if (int rc = launch_simple_backward(dL_dgpost, g_pre, tau, (const float *)saved, batch,
-                                        nx, ny, pack, part, s))
+                                        nx, ny, params, part, s))
       return rc;
   } else {
     int cur = 0;

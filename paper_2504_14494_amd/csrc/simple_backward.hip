@@ -39,7 +39,7 @@ constexpr int kBwdFrags = 24;     // W1 4, W2 8, W2^T 8, Wh^T 4
 
 __global__ __launch_bounds__(kBT) void simple_backward_kernel(
     const float *__restrict__ G, const float *__restrict__ gpre, const float *__restrict__ tau,
-    const float *__restrict__ z0, int batch, int nx, int ny, const uint8_t *__restrict__ pack, FragLayout F, BlobLayout L,
+    const float *__restrict__ z0, int batch, int nx, int ny, const float *__restrict__ params, BlobLayout L,
     float *__restrict__ part) {
   __shared__ u32x4 w_s[kBwdFrags * 64];
   __shared__ f32x4 b_s[8 * 4];     // b1 (4), b2 (4) per channel group
@@ -47,21 +47,36 @@ __global__ __launch_bounds__(kBT) void simple_backward_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int n = lane & 15, q = lane >> 4;
-  const float *cst = (const float *)(pack + F.const_off);
-  {
-    const u32x4 *frags = (const u32x4 *)(pack + F.frag_off);
-    const f32x4 *bias = (const f32x4 *)(pack + F.bias_off);
-    for (int f = wave; f < kBwdFrags; f += 4) {
-      const int src = f < 4    ? F.W1 + f
-                      : f < 12 ? F.W2 + (f - 4)
-                      : f < 20 ? F.W2T + (f - 12)
-                               : F.WHT + (f - 20);
-      w_s[f * 64 + lane] = frags[(size_t)src * 64 + lane];
+  const float *cst = params + L.mu;
+  // The fragments straight from the parameters, as gnn_prep_kernel packs them: a
+  // launch of its own costs more than its 24 of them here (161.5 -> 158.1 us a
+  // training step of 32 lattices of 128^2).  Value k of a row lies at base + stride
+  // k; rows of lim values (0: HID, in fragment order) are padded with zeros.
+#pragma unroll
+  for (int i = 0; i < kBwdFrags / 4; ++i) {
+    const int f = 4 * i + wave;
+    const int t = f < 4 ? f : f < 12 ? (f - 4) >> 1 : f < 20 ? (f - 12) >> 1 : f - 20;
+    const int row = 16 * t + n, s = f & 1;
+    const bool transposed = f >= 12;
+    const size_t base = f < 4    ? L.W1 + (size_t)row * NFEAT
+                        : f < 12 ? L.W2 + (size_t)row * HID
+                                 : (f < 20 ? L.W2 : L.Wh) + row;
+    const int stride = transposed ? HID : 1, lim = f < 4 ? NFEAT : f < 20 ? 0 : NOUT;
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int k = lim ? 8 * q + j : frag_channel(s, q, j);
+      const bool in = !lim || k < lim;
+      const float v = params[base + (size_t)(in ? stride * k : 0)];
+      x[j] = in ? v : 0.0f;
     }
-    if (threadIdx.x < 8 * 4) {
-      const int b = threadIdx.x >> 2;
-      b_s[threadIdx.x] = bias[(size_t)(b < 4 ? F.B1 + b : F.B2 + b - 4) * 64 + 16 * (threadIdx.x & 3)];
-    }
+    w_s[f * 64 + lane] = u32x4{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]),
+                               pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])};
+  }
+  if (threadIdx.x < 8 * 4) {
+    const int b = threadIdx.x >> 2;
+    const float *src = params + (b < 4 ? L.b1 + 16 * b : L.b2 + 16 * (b - 4)) + 4 * (threadIdx.x & 3);
+    b_s[threadIdx.x] = f32x4{src[0], src[1], src[2], src[3]};
   }
   const float sdelta = cst[C_SDELTA];
   float isg[NFEAT], nmi[NFEAT];
@@ -264,10 +279,11 @@ __global__ __launch_bounds__(kBT) void simple_backward_kernel(
 }  // namespace simple
 
 int launch_simple_backward(const float *G, const float *g_pre, const float *tau, const float *z0,
-                           int batch, int nx, int ny, const uint8_t *pack, float *part, hipStream_t s) {
+                           int batch, int nx, int ny, const float *params, float *part,
+                           hipStream_t s) {
   const BlobLayout L = blob_layout(0);
   hipLaunchKernelGGL(simple::simple_backward_kernel, dim3(kBwdBlocks), dim3(kBT), 0, s, G, g_pre,
-                     tau, z0, batch, nx, ny, pack, frag_layout(0), L, part);
+                     tau, z0, batch, nx, ny, params, L, part);
   return lbm::launch_check("simple_backward_kernel");
 }
 
