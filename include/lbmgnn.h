@@ -249,11 +249,11 @@ int lbm_step_gnn(const float *g_src, float *g_dst, int nx, int ny, float tau,
                  const float *params, int n_rounds, const lbm_fallback *fb,
                  void *workspace, size_t ws_bytes, void *stream);
 
-/* nsteps steps of lbm_step_gnn in one call, alternately from g_a into g_b and back:
- * the states, flags, decisions and masses of as many single calls, with the weights
- * packed once on small lattices.  The last state is in g_b if nsteps is odd, in
+/* nsteps steps of lbm_step_gnn (n_rounds = 0: lbm_step_simple) in one call,
+ * alternately from g_a into g_b and back: the states, flags, decisions and masses of
+ * as many single calls, with the weights packed once.  The last state is in g_b if nsteps is odd, in
  * g_a if it is even; the other buffer holds the state before it.  nsteps >= 1;
- * other arguments and errors as for lbm_step_gnn. */
+ * other arguments and errors as for the single step. */
 int lbm_steps_gnn(float *g_a, float *g_b, int nx, int ny, float tau,
                   const float *params, int n_rounds, int nsteps,
                   const lbm_fallback *fb, void *workspace, size_t ws_bytes,

@@ -336,9 +336,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_resource(void *base, size
 // fused per-node step (0), ctrl[kCtrlChunkQueue + 32 p].
 constexpr int kCtrlFallback = 2;
 constexpr int kCtrlTileQueue = 4;
-constexpr int kCtrlMass = 8;         // two words, 8-byte aligned
+constexpr int kCtrlMass = 8;         // two doubles: the gate's reference mass of even and odd steps
 constexpr int kCtrlChunkQueue = 32;  // kQueueParts counters, 128 bytes apart
-static_assert(kCtrlTileQueue + MAX_ROUNDS <= kCtrlMass && kCtrlMass + 2 <= kCtrlChunkQueue,
+static_assert(kCtrlTileQueue + MAX_ROUNDS <= kCtrlMass && kCtrlMass + 4 <= kCtrlChunkQueue,
               "control words");
 static_assert(kCtrlChunkQueue + kQueueParts * kQueueStride <= kCtrlWords, "control words fit their bytes");
 

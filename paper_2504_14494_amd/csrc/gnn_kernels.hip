@@ -348,8 +348,6 @@ struct HeadArgs {
   float *save_z;          // [N][12] head outputs kept for the backward pass
   Q80 *pmass;             // [gridDim.x] sum of g* over the nodes of a workgroup
   unsigned *pflag;        // [gridDim.x] 1 if a population came out negative / non-finite
-  const double *mass;     // gate's reference mass, copied to mold by the small kernel, or NULL
-  double *mold;
 };
 
 // Corrected collision of one node (Eq. 3 with the projected correction),
@@ -1015,8 +1013,6 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gnn_small_kernel(
     const int wo = G::width(r), no = wo * G::rows(r);
     if (last && (wave == 4 || wave == 5))
       node_pops<PULL>(lat, nx, ny, inside ? xo : x0, inside ? yo : y0, gp);
-    // what the gate, whose first workgroup updates the mass, compares with
-    if (last && wave == 6 && blockIdx.x == 0 && lane == 0 && args.mass) *args.mold = *args.mass;
     if (16 * wave < no) {
       const int k = 16 * wave + n < no ? 16 * wave + n : no - 1;
       const int ry = k / wo, rx = k - ry * wo;
@@ -1171,6 +1167,8 @@ struct GateArgs {
   double threshold;
   unsigned *flags, *n_fallback;
   double *mass;
+  int turn;               // the step's number, modulo 2, since the weights were packed
+  int more;               // another step on these weights follows
 };
 
 __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
@@ -1184,7 +1182,9 @@ __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
   {
     Q80 m{0ull, 0ll};
     unsigned f = 0;
-    const double mold = *(const double *)(ctrl + kCtrlMass);  // (loaded with the partials)
+    // (loaded with the partials; the next step's is another word, since the first
+    // workgroup may set it before the others have read theirs)
+    const double mold = *(const double *)(ctrl + kCtrlMass + 2 * gate.turn);
     for (int k = threadIdx.x; k < gate.nparts; k += kThreads) {
       m = q80_add(m, gate.pmass[k]);
       f |= gate.pflag[k];
@@ -1196,12 +1196,17 @@ __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
     unsigned fl = sum.flag;
     const double rel = fabs(mnew - mold) / mold;
     if (!(rel <= gate.threshold)) fl |= 2u;
+    if (gate.more && blockIdx.x == 0) {  // the next step's work counters
+      if (threadIdx.x < MAX_ROUNDS) ctrl[kCtrlTileQueue + threadIdx.x] = 0u;
+      if (threadIdx.x < kQueueParts) ctrl[kCtrlChunkQueue + kQueueStride * threadIdx.x] = 0u;
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       if (fl) {
         *gate.flags |= fl;
         if (gate.n_fallback) *gate.n_fallback += 1u;
       } else {
         *gate.mass = mnew;
+        if (gate.more) *(double *)(ctrl + kCtrlMass + 2 * (gate.turn ^ 1)) = mnew;
       }
     }
     if (!fl) return;
@@ -1249,8 +1254,10 @@ __global__ __launch_bounds__(kThreads) void gate_fallback_kernel(
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    *gate.mass = (double)nodes + sm[0];
-    ctrl[kCtrlFallback] = 0u;  // for the next step on the same packed weights
+    const double mnew = (double)nodes + sm[0];
+    *gate.mass = mnew;
+    *(double *)(ctrl + kCtrlMass + 2 * (gate.turn ^ 1)) = mnew;
+    ctrl[kCtrlFallback] = 0u;
   }
 }
 
@@ -1313,8 +1320,8 @@ static bool small_lattice(int batch, int nx, int ny, int R) {
   return R <= kSmallRounds && tiles <= 2 * device_cus();
 }
 
-// Launches weight packing (unless `packed`, for a small lattice: the scratch holds
-// these weights), encoder and rounds.  src: populations the collision starts from
+// Launches weight packing (unless `packed`: the scratch holds these weights, and the
+// last step's gate has set the control words), encoder and rounds.  src: populations the collision starts from
 // (post-collision state of the previous step when PULL, else pre-collision); the
 // last kernel writes dst and *nparts mass and flag partials.
 int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, int ny,
@@ -1328,7 +1335,7 @@ int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, i
   unsigned *ctrl = (unsigned *)at(ws, W.ctrl);
   const bool small = !saved && small_lattice(batch, nx, ny, R);
   if (!packed)
-    if (int rc = launch_prep(params, R, pack, ctrl, fb && !small ? fb->mass : nullptr, s)) return rc;
+    if (int rc = launch_prep(params, R, pack, ctrl, fb ? fb->mass : nullptr, s)) return rc;
 
   const int cus = device_cus();
   const bool save = saved != nullptr;
@@ -1349,10 +1356,6 @@ int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, i
     ha.head_out = head_out;
     ha.pmass = (Q80 *)at(ws, W.pmass);
     ha.pflag = (unsigned *)at(ws, W.pflag);
-    if (fb) {
-      ha.mass = fb->mass;
-      ha.mold = (double *)(ctrl + kCtrlMass);
-    }
     *nparts = small_tiles;
     const dim3 grid((unsigned)small_tiles), block(kSmallThreads);
     if (pull && R == 1)
@@ -1436,21 +1439,31 @@ int launch_forward(bool pull, const float *src, float *dst, int batch, int nx, i
 
 namespace gnn {
 
-// The gate of a corrected step whose producing kernel left `nparts` partials.
+// The gate of a corrected step whose producing kernel left `nparts` partials;
+// turn: the step's number since the weights were packed; more: another follows.
 int launch_gate(const float *g_src, float *g_dst, int nx, int ny, float tau, int walls,
                 float gx, const lbm_fallback *fb, const void *pmass, const void *pflag,
-                int nparts, void *pmass2, void *ctrl, hipStream_t s) {
+                int nparts, void *pmass2, void *ctrl, int turn, bool more, hipStream_t s) {
   // four workgroups per CU: each of them reads every partial, and a fallback
   // walks the lattice in strides of the grid
   const long long fbn = ((long long)nx * ny + kThreads - 1) / kThreads;
   const long long cap = 4LL * device_cus() < kMaxGnnBlocks ? 4LL * device_cus() : kMaxGnnBlocks;
   const GateArgs gate{(const Q80 *)pmass, (const unsigned *)pflag, nparts,
-                      fb->drift_threshold, fb->flags, fb->n_fallback, fb->mass};
+                      fb->drift_threshold, fb->flags, fb->n_fallback, fb->mass, turn & 1, more};
   hipLaunchKernelGGL(gate_fallback_kernel, dim3((unsigned)(fbn < cap ? fbn : cap)),
                      dim3(kThreads), 0, s, g_src, g_dst, nx, ny, 1.0f / tau, walls, gx,
                      (unsigned *)ctrl, (double *)pmass2, gate);
   return launch_check("gate_fallback_kernel");
 }
+
+}  // namespace gnn
+
+namespace gnn {
+
+// simple_kernels.hip: nsteps steps of the per-node network between two buffers.
+int steps_simple_pair(const char *who, float *g_a, float *g_b, int nx, int ny, float tau,
+                      const float *params, int nsteps, const lbm_fallback *fb, void *workspace,
+                      size_t ws_bytes, hipStream_t s);
 
 }  // namespace gnn
 
@@ -1488,8 +1501,10 @@ extern "C" int gnn_forward(const float *g_pre, float *g_post, int batch, int nx,
 // lbm_step_gnn on a given scratch of forward_scratch(nx * ny) bytes or more.
 static int step_gnn(const float *g_src, float *g_dst, int nx, int ny, float tau,
                     const float *params, int n_rounds, const lbm_fallback *fb, void *workspace,
-                    hipStream_t s, bool packed = false) {
+                    hipStream_t s, int turn = 0, bool more = false) {
   int nparts;
+  // without a gate only the fused kernel, which draws no work, can do without packing
+  const bool packed = turn > 0 && (fb || small_lattice(1, nx, ny, n_rounds));
   if (int rc = launch_forward(true, g_src, g_dst, 1, nx, ny, nullptr, tau, params, n_rounds,
                               nullptr, nullptr, workspace, fb, &nparts, s, packed))
     return rc;
@@ -1497,7 +1512,7 @@ static int step_gnn(const float *g_src, float *g_dst, int nx, int ny, float tau,
   const ForwardScratch W = forward_scratch((long long)nx * ny);
   return launch_gate(g_src, g_dst, nx, ny, tau, 0, 0.0f, fb, at(workspace, W.pmass),
                      at(workspace, W.pflag), nparts, at(workspace, W.pmass2),
-                     at(workspace, W.ctrl), s);
+                     at(workspace, W.ctrl), turn, more, s);
 }
 
 static int check_step_gnn(const char *who, const float *g_src, float *g_dst, int nx, int ny,
@@ -1526,24 +1541,27 @@ extern "C" int lbm_step_gnn(const float *g_src, float *g_dst, int nx, int ny, fl
                   (hipStream_t)stream);
 }
 
-// A step of a small lattice is two short kernels besides the packing of the
-// weights, which takes as long as the gate: several steps pack once.  128^2, gated:
-// 22.6 us a step one by one, 19.3 so.  Larger lattices would gain a 400th.
+// The packing of the weights takes as long as the gate, 4.5 us and a launch: several
+// steps pack once.  Gated steps one by one and so: message passing 22.6 and 19.2 us
+// at 128^2, 58.8 and 54.4 at 256^2; the Fig. 2 network 12.3 and 9.1 at 128^2, 22.9
+// and 19.5 at 512^2.
 extern "C" int lbm_steps_gnn(float *g_a, float *g_b, int nx, int ny, float tau,
                              const float *params, int n_rounds, int nsteps,
                              const lbm_fallback *fb, void *workspace, size_t ws_bytes,
                              void *stream) {
+  if (nsteps < 1) return fail(LBM_EINVAL, "lbm_steps_gnn: nsteps %d", nsteps);
+  if (n_rounds == 0)
+    return steps_simple_pair("lbm_steps_gnn", g_a, g_b, nx, ny, tau, params, nsteps, fb, workspace,
+                             ws_bytes, (hipStream_t)stream);
   if (int rc = check_step_gnn("lbm_steps_gnn", g_a, g_b, nx, ny, tau, params, n_rounds, fb))
     return rc;
-  if (nsteps < 1) return fail(LBM_EINVAL, "lbm_steps_gnn: nsteps %d", nsteps);
   const size_t need = step_workspace_bytes(nx, ny, n_rounds);
   if (!workspace || ws_bytes < need)
     return fail(LBM_EWORKSPACE, "lbm_steps_gnn: workspace needs %zu bytes", need);
   if (int rc = check_device()) return rc;
-  const bool small = small_lattice(1, nx, ny, n_rounds);
   for (int k = 0; k < nsteps; ++k)
     if (int rc = step_gnn(k & 1 ? g_b : g_a, k & 1 ? g_a : g_b, nx, ny, tau, params, n_rounds, fb,
-                          workspace, (hipStream_t)stream, small && k > 0))
+                          workspace, (hipStream_t)stream, k, k + 1 < nsteps))
       return rc;
   return LBM_OK;
 }

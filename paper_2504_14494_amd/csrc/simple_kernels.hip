@@ -307,7 +307,7 @@ __global__ __launch_bounds__(THREADS) void simple_resident_kernel(
 // The gate's fallback kernel, shared with the message-passing step (gnn_kernels.hip).
 int launch_gate(const float *g_src, float *g_dst, int nx, int ny, float tau, int walls,
                 float gx, const lbm_fallback *fb, const void *pmass, const void *pflag,
-                int nparts, void *pmass2, void *ctrl, hipStream_t s);
+                int nparts, void *pmass2, void *ctrl, int turn, bool more, hipStream_t s);
 
 }  // namespace gnn
 
@@ -323,12 +323,14 @@ static inline void *at_(void *base, size_t off) { return (uint8_t *)base + off; 
 static int launch_simple(bool pull, bool walls, float gx, const float *src, float *dst,
                          int batch, int nx, int ny, const float *tau_arr, float tau,
                          const float *params, float *head_out, float *save_z0, void *ws,
-                         const lbm_fallback *fb, int *nparts, hipStream_t s) {
+                         const lbm_fallback *fb, int *nparts, hipStream_t s,
+                         bool packed = false) {
   const FragLayout F = frag_layout(0);
   const SimpleScratch W = simple_scratch();
   uint8_t *pack = (uint8_t *)at_(ws, W.pack);
   unsigned *ctrl = (unsigned *)at_(ws, W.ctrl);
-  if (int rc = launch_prep(params, 0, pack, ctrl, fb ? fb->mass : nullptr, s)) return rc;
+  if (!packed)
+    if (int rc = launch_prep(params, 0, pack, ctrl, fb ? fb->mass : nullptr, s)) return rc;
   const long long chunks = (long long)batch * ny * ((nx + 63) / 64);
   long long blocks = (chunks + simple::kWaves - 1) / simple::kWaves;
   // the resident blocks; their waves draw the chunks from a counter
@@ -411,10 +413,26 @@ extern "C" int simple_forward(const float *g_pre, float *g_post, int batch, int 
                        head_out, (float *)saved, workspace, nullptr, &nparts, (hipStream_t)stream);
 }
 
-// The fused step, periodic (walls = 0) or the channel (walls = 1, force gx).
-static int step_simple(const char *who, const float *g_src, float *g_dst, int nx, int ny,
-                       float tau, bool walls, float gx, const float *params, int nsteps,
-                       const lbm_fallback *fb, void *workspace, size_t ws_bytes, void *stream) {
+// One step and its gate; turn: its number since the weights were packed (0 packs
+// them; without a gate, which zeroes the work counters, every step does); more:
+// another follows.
+static int gated_step(const float *g_src, float *g_dst, int nx, int ny, float tau, bool walls,
+                      float gx, const float *params, const lbm_fallback *fb, void *workspace,
+                      int turn, bool more, hipStream_t s) {
+  int nparts;
+  if (int rc = launch_simple(true, walls, gx, g_src, g_dst, 1, nx, ny, nullptr, tau, params,
+                             nullptr, nullptr, workspace, fb, &nparts, s, fb && turn > 0))
+    return rc;
+  if (!fb) return LBM_OK;
+  const SimpleScratch W = simple_scratch();
+  return launch_gate(g_src, g_dst, nx, ny, tau, walls ? 1 : 0, gx, fb, at_(workspace, W.pmass),
+                     at_(workspace, W.pflag), nparts, at_(workspace, W.pmass2),
+                     at_(workspace, W.ctrl), turn, more, s);
+}
+
+static int check_step_simple(const char *who, const float *g_src, const float *g_dst, int nx,
+                             int ny, float tau, bool walls, float gx, const float *params,
+                             const lbm_fallback *fb, void *workspace, size_t ws_bytes) {
   if (int rc = check_simple(who, 1, nx, ny, params)) return rc;
   if (!g_src || !g_dst) return fail(LBM_EINVAL, "%s: null pointer", who);
   if (!(tau > 0.0f)) return fail(LBM_EINVAL, "%s: tau must be positive", who);
@@ -426,6 +444,39 @@ static int step_simple(const char *who, const float *g_src, float *g_dst, int nx
     return fail(LBM_EINVAL, "%s: fallback needs flags and mass pointers", who);
   if (!workspace || ws_bytes < simple_scratch().total)
     return fail(LBM_EWORKSPACE, "%s: workspace needs %zu bytes", who, simple_scratch().total);
+  return LBM_OK;
+}
+
+namespace gnn {
+
+int steps_simple_pair(const char *who, float *g_a, float *g_b, int nx, int ny, float tau,
+                      const float *params, int nsteps, const lbm_fallback *fb, void *workspace,
+                      size_t ws_bytes, hipStream_t s) {
+  if (int rc = check_step_simple(who, g_a, g_b, nx, ny, tau, false, 0.0f, params, fb, workspace,
+                                 ws_bytes))
+    return rc;
+  if (int rc = check_device()) return rc;
+  const bool resident = (long long)nx * ny <= simple::kResidentNodes;
+  for (int k = 0; k < nsteps; ++k) {
+    float *src = k & 1 ? g_b : g_a, *dst = k & 1 ? g_a : g_b;
+    if (int rc = resident ? launch_simple_resident(false, 0.0f, src, dst, nx, ny, tau, params, 1,
+                                                   workspace, fb, s)
+                          : gated_step(src, dst, nx, ny, tau, false, 0.0f, params, fb, workspace,
+                                       k, k + 1 < nsteps, s))
+      return rc;
+  }
+  return LBM_OK;
+}
+
+}  // namespace gnn
+
+// The fused step, periodic (walls = 0) or the channel (walls = 1, force gx).
+static int step_simple(const char *who, const float *g_src, float *g_dst, int nx, int ny,
+                       float tau, bool walls, float gx, const float *params, int nsteps,
+                       const lbm_fallback *fb, void *workspace, size_t ws_bytes, void *stream) {
+  if (int rc = check_step_simple(who, g_src, g_dst, nx, ny, tau, walls, gx, params, fb, workspace,
+                                 ws_bytes))
+    return rc;
   const int most = lbm_steps_simple_max(nx, ny);
   if (nsteps < 1 || nsteps > most)
     return fail(LBM_EINVAL, "%s: %d steps, not 1 to %d", who, nsteps, most);
@@ -434,15 +485,7 @@ static int step_simple(const char *who, const float *g_src, float *g_dst, int nx
   if ((long long)nx * ny <= simple::kResidentNodes)
     return launch_simple_resident(walls, gx, g_src, g_dst, nx, ny, tau, params, nsteps, workspace,
                                   fb, s);
-  int nparts;
-  if (int rc = launch_simple(true, walls, gx, g_src, g_dst, 1, nx, ny, nullptr, tau, params,
-                             nullptr, nullptr, workspace, fb, &nparts, s))
-    return rc;
-  if (!fb) return LBM_OK;
-  const SimpleScratch W = simple_scratch();
-  return launch_gate(g_src, g_dst, nx, ny, tau, walls ? 1 : 0, gx, fb, at_(workspace, W.pmass),
-                     at_(workspace, W.pflag), nparts, at_(workspace, W.pmass2),
-                     at_(workspace, W.ctrl), s);
+  return gated_step(g_src, g_dst, nx, ny, tau, walls, gx, params, fb, workspace, 0, false, s);
 }
 
 extern "C" int lbm_step_simple(const float *g_src, float *g_dst, int nx, int ny, float tau,

@@ -106,7 +106,8 @@ def _gnn_step_args(src, dst, blob, rounds, fallback, ws):
         raise ValueError("src and dst must both be [ny, 9, nx]")
     _check_blob(blob, rounds)
     ny, nx = int(src.shape[0]), int(src.shape[2])
-    wsb = _lib.load().lbm_workspace_bytes(_lib.LBM_WS_GNN_STEP, 1, nx, ny, rounds)
+    kind = _lib.LBM_WS_GNN_STEP if rounds else _lib.LBM_WS_SIMPLE
+    wsb = _lib.load().lbm_workspace_bytes(kind, 1, nx, ny, rounds)
     fb = ctypes.byref(fallback.struct()) if fallback is not None else None
     return nx, ny, fb, (ws or _ws).get(wsb)
 
@@ -122,7 +123,7 @@ def lbm_step_gnn(src: torch.Tensor, dst: torch.Tensor, tau: float, blob: torch.T
 
 def lbm_steps_gnn(a: torch.Tensor, b: torch.Tensor, tau: float, blob: torch.Tensor, nsteps: int,
                   rounds: int = 2, fallback: Fallback = None, ws: Workspace = None):
-    """nsteps steps of lbm_step_gnn in one call, alternately from a into b and
+    """nsteps steps of lbm_step_gnn (rounds = 0: lbm_step_simple) in one call, alternately from a into b and
     back.  Returns the buffer of the last state: b if nsteps is odd, else a."""
     nx, ny, fb, buf = _gnn_step_args(a, b, blob, rounds, fallback, ws)
     rc = _lib.load().lbm_steps_gnn(_ptr(a), _ptr(b), nx, ny, float(tau), _ptr(blob), rounds,
@@ -314,9 +315,9 @@ class GnnLattice(Lattice):
         fallback state is updated on the device every step, also inside a
         captured graph."""
         def step(src, dst, fb, k=1):
-            if self.rounds == 0 and k > 1:
+            if self.rounds == 0 and 1 < k <= self._most_simple:
                 lbm_steps_simple(src, dst, tau, self.blob, k, fb, self.ws)
-            elif self.rounds == 0:
+            elif self.rounds == 0 and k == 1:
                 lbm_step_simple(src, dst, tau, self.blob, fb, self.ws)
             elif k > 1:
                 lbm_steps_gnn(src, dst, tau, self.blob, k, self.rounds, fb, self.ws)
@@ -334,7 +335,8 @@ class GnnLattice(Lattice):
             step(self.a.clone(), torch.empty_like(self.a), tmp)
         return self._run(("gnn", float(tau), bool(gate)) + self._graph_key(gate),
                          lambda s, d, k: step(s, d, fb, k), warm, n, graph,
-                         self._most_simple if self.rounds == 0 else 1, pair=self.rounds > 0)
+                         self._most_simple if self.rounds == 0 else 1,
+                         pair=self.rounds > 0 or self._most_simple == 1)
 
     def step_gnn_channel(self, tau: float, gx: float, n: int = 1, gate: bool = True,
                          graph: bool = False):

@@ -1,6 +1,6 @@
-"""Several gated message-passing steps in one call (lbm_steps_gnn) against as many
-single ones: small lattices, whose weights are packed once, at and past the edge of
-that route, and larger ones."""
+"""Several gated corrected steps in one call (lbm_steps_gnn), which packs the weights
+once, against as many single ones: message passing in the fused kernel, at its edge
+and past it, and the per-node network (no rounds) within and past one workgroup."""
 import pytest
 import torch
 
@@ -24,7 +24,8 @@ def _gate(g, threshold):
 
 
 @pytest.mark.parametrize("nx,ny,rounds", [(1, 1, 1), (16, 4, 2), (17, 5, 1), (100, 60, 2), (128, 128, 2),
-                                          (256, 129, 2), (64, 32, 3)])
+                                          (256, 129, 2), (64, 32, 3), (300, 211, 1), (16, 16, 0),
+                                          (45, 23, 0), (128, 128, 0), (700, 301, 0)])
 def test_several_steps_equal_single_ones(nx, ny, rounds):
     # every step kept, every step redone, some of each (a drift threshold at the
     # size of the steps' own rounding), and without the gate
@@ -34,7 +35,10 @@ def test_several_steps_equal_single_ones(nx, ny, rounds):
         one = None if threshold is None else _gate(start, threshold)
         a, b = start.clone(), torch.empty_like(start)
         for n in range(1, 7):
-            gnn.lbm_step_gnn(a, b, 0.7, blob, rounds, one)
+            if rounds:
+                gnn.lbm_step_gnn(a, b, 0.7, blob, rounds, one)
+            else:
+                gnn.lbm_step_simple(a, b, 0.7, blob, one)
             a, b = b, a
             if n not in (1, 2, 5, 6):
                 continue
@@ -50,23 +54,28 @@ def test_several_steps_equal_single_ones(nx, ny, rounds):
                 assert torch.equal(fb.mass, one.mass)
 
 
+@pytest.mark.parametrize("rounds", [0, 2])
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 130])
-def test_lattice_steps_with_and_without_a_graph(n):
-    blob, start = _setup(48, 20, 2, 1e-4, False)
+def test_lattice_steps_with_and_without_a_graph(n, rounds):
+    nx, ny = 48, 30
+    blob, start = _setup(nx, ny, rounds, 1e-4, False)
     states = []
     for graph in (False, True):
-        lat = gnn.GnnLattice(48, 20, blob, 2)
+        lat = gnn.GnnLattice(nx, ny, blob, rounds)
         lat.load(start)
         for _ in range(2):   # the second run replays what the first captured
             lat.step_gnn(0.7, n, graph=graph)
         states.append((lat.a.clone(), lat.fallback.mass.clone(), lat.steps))
     ref, tmp = start.clone(), torch.empty_like(start)
     fb = gnn.Fallback(0.0)
-    lat = gnn.GnnLattice(48, 20, blob, 2)
+    lat = gnn.GnnLattice(nx, ny, blob, rounds)
     lat.load(start)
     fb.mass.copy_(lat.fallback.mass)
     for _ in range(2 * n):
-        gnn.lbm_step_gnn(ref, tmp, 0.7, blob, 2, fb)
+        if rounds:
+            gnn.lbm_step_gnn(ref, tmp, 0.7, blob, rounds, fb)
+        else:
+            gnn.lbm_step_simple(ref, tmp, 0.7, blob, fb)
         ref, tmp = tmp, ref
     for state, mass, steps in states:
         assert torch.equal(state, ref) and torch.equal(mass, fb.mass) and steps == 2 * n
