@@ -94,9 +94,9 @@ int lbm_step_bgk_f64(const double *g_src, double *g_dst, int nx, int ny,
 /* nsteps steps of lbm_step_bgk in one pass over the lattice, bitwise the
  * state that as many single steps leave (the states in between exist on the
  * chip only).  2 <= nsteps <= lbm_steps_max(nx, ny, f64, walls), the most steps
- * that one call takes for this lattice: f64 1 for FP64 populations, walls 1 for
- * the channel (lbm_steps_channel, below).  Other arguments and errors as
- * lbm_step_bgk. */
+ * that are worth taking in one call for this lattice: f64 1 for FP64 populations,
+ * walls 1 for the channel (lbm_steps_channel, below).  (Lattices of few rows take
+ * a few more, at a loss.)  Other arguments and errors as lbm_step_bgk. */
 int lbm_steps_max(int nx, int ny, int f64, int walls);
 int lbm_steps_bgk(const float *g_src, float *g_dst, int nx, int ny, float tau,
                   int nsteps, void *stream);

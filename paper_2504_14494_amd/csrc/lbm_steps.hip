@@ -325,29 +325,64 @@ enum StepsKind { kStepsResident, kStepsTile, kStepsMarch };
 // step; four at a time 14 % slower, six 1 % faster with three waves per SIMD
 // left), four where it stays (1501 x 1003: 6.6 against 7.0), and fewer in
 // FP64, whose rows take twice the registers.
+// Lattices of few rows.  A region of 32 x 32 that steps one row five times makes use
+// of 24 of its 1024 nodes: 480,000 x 1 took 42 us per step (single steps 7.3), 240,000 x 2 with
+// walls in FP64 60 (15.0).  So a region that has more rows than the lattice and its
+// halos takes just those and is wider instead, if the tiles would be more than one per
+// CU (below, their latency counts, and they stay ahead whatever they recompute):
+// as many steps as leave one per CU (20,000 x 1 with walls in FP64: 2.0 with six, 3.3
+// with eight), else ny + 1; more recompute more than they save, and on one row two at
+// once are no faster than single steps (240,000 x 1 with walls: 5.0 and 3.6).  In
+// the march ny + 1 at most, too (4,000,000 x 1: 44 with two, 53 with four, single 50).
 struct StepsPlan {
   StepsKind kind;
-  int max_steps;
-  int rx, ry;  // tile region
+  int max_steps;  // that are worth taking at once (1: none)
+  int limit;      // that are taken at all
+  int rx, ry;     // tile region; ry 0: the lattice's rows (flat_region)
 };
 
 constexpr int kResidentNodes = 1024;
 constexpr int kResidentSteps = 16384;      // a launch of some 10 ms at most
 constexpr size_t kCacheBytes = 128u << 20;  // both buffers well inside the Infinity Cache
+constexpr int kRegionNodes = 1024;
+constexpr int kTilesAtOnce = 256;  // one per CU
+
+static void flat_region(int ny, int nsteps, int &rx, int &ry) {
+  ry = ny + 2 * (nsteps - 1);
+  rx = kRegionNodes / ry;
+}
+
+static long long tiles_of(int nx, int ny, int rx, int ry, int nsteps) {
+  const long long ox = rx - 2 * (nsteps - 1), oy = ry - 2 * (nsteps - 1);
+  return ((nx + ox - 1) / ox) * ((ny + oy - 1) / oy);
+}
 
 static StepsPlan steps_plan(int nx, int ny, size_t elem, bool walls) {
   const long long nodes = (long long)nx * ny;
-  if (nodes <= kResidentNodes) return {kStepsResident, kResidentSteps, nx, ny};
+  if (nodes <= kResidentNodes) return {kStepsResident, kResidentSteps, kResidentSteps, nx, ny};
   const int block = kMarchWaves * 56;
   const long long covered = (long long)((nx + block - 1) / block) * block;
   const bool wide = 2LL * nx > covered && nx < (1 << 28);
   if (wide && nodes >= (elem == 4 ? 700000 : 500000)) {
-    if (elem == 8) return {kStepsMarch, walls ? 3 : 4, 0, 0};
-    return {kStepsMarch, walls || 2 * 9 * elem * nodes <= kCacheBytes ? 4 : 5, 0, 0};
+    const int k = elem == 8 ? (walls ? 3 : 4)
+                            : (walls || 2 * 9 * elem * nodes <= kCacheBytes ? 4 : 5);
+    return {kStepsMarch, k < ny + 1 ? k : ny + 1, k, 0, 0};
   }
-  if (nodes <= 8192) return {kStepsTile, 8, 32, 16};
-  if (nodes <= 32768) return {kStepsTile, 8, 24, 24};
-  return {kStepsTile, nodes <= 131072 ? 8 : 5, 32, 32};
+  const int k = nodes <= 131072 ? 8 : 5;
+  const int rx = nodes <= 8192 ? 32 : nodes <= 32768 ? 24 : 32;
+  const int ry = nodes <= 8192 ? 16 : nodes <= 32768 ? 24 : 32;
+  if (ny + 2 * (k - 1) < ry &&
+      tiles_of(nx, ny, rx, ry, k) * rx * ry > kTilesAtOnce * kRegionNodes) {
+    int best = k;
+    for (; best > 1; --best) {
+      int fx, fy;
+      flat_region(ny, best, fx, fy);
+      if (tiles_of(nx, ny, fx, fy, best) <= kTilesAtOnce) break;
+    }
+    if (best == 1 && ny > 1) best = k < ny + 1 ? k : ny + 1;
+    return {kStepsTile, best, k, 0, 0};
+  }
+  return {kStepsTile, k, k, rx, ry};
 }
 
 template <typename T, int K, bool WALLS>
@@ -393,7 +428,9 @@ static int launch_march(const T *src, T *dst, int nx, int ny, T omega, T gx, hip
 template <typename T, bool WALLS>
 static int launch_tiles(const T *src, T *dst, int nx, int ny, const StepsPlan &P, int nsteps,
                         T omega, T gx, hipStream_t s) {
-  const unsigned inv_rx = ((1u << 20) + P.rx - 1) / P.rx;
+  int rx = P.rx, ry = P.ry;
+  if (!ry) flat_region(ny, nsteps, rx, ry);
+  const unsigned inv_rx = ((1u << 20) + rx - 1) / rx;
   if (P.kind == kStepsResident) {
     const int nodes = nx * ny, threads = (nodes + 63) / 64 * 64;
     auto *kernel = threads <= 128   ? tile_kernel<T, WALLS, true, 128>
@@ -403,16 +440,16 @@ static int launch_tiles(const T *src, T *dst, int nx, int ny, const StepsPlan &P
                        nsteps, 1, omega, gx);
     return launch_check("tile_kernel");
   }
-  const int ox = P.rx - 2 * (nsteps - 1), oy = P.ry - 2 * (nsteps - 1);
+  const int ox = rx - 2 * (nsteps - 1);
   const int txn = (nx + ox - 1) / ox;
-  const long long blocks = (long long)txn * ((ny + oy - 1) / oy);
+  const long long blocks = tiles_of(nx, ny, rx, ry, nsteps);
   if (blocks > 0x7fffffffLL) return fail(LBM_EINVAL, "lbm_steps: lattice too large");
-  const int threads = P.rx * P.ry;
+  const int threads = P.ry ? rx * ry : kRegionNodes;
   auto *kernel = threads == 512   ? tile_kernel<T, WALLS, false, 512>
                  : threads == 576 ? tile_kernel<T, WALLS, false, 576>
                                   : tile_kernel<T, WALLS, false, 1024>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, s, src, dst, nx, ny, P.rx,
-                     P.ry, inv_rx, nsteps, txn, omega, gx);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, s, src, dst, nx, ny, rx, ry,
+                     inv_rx, nsteps, txn, omega, gx);
   return launch_check("tile_kernel");
 }
 
@@ -426,8 +463,8 @@ static int steps_impl(const T *src, T *dst, int nx, int ny, T tau, T gx, int nst
   if (overlap(src, dst, (size_t)9 * nx * ny * sizeof(T)))
     return fail(LBM_EINVAL, "%s: source and destination overlap", who);
   const StepsPlan P = steps_plan(nx, ny, sizeof(T), WALLS);
-  if (nsteps < 2 || nsteps > P.max_steps)
-    return fail(LBM_EINVAL, "%s: %d steps, not 2 to %d", who, nsteps, P.max_steps);
+  if (nsteps < 2 || nsteps > P.limit)
+    return fail(LBM_EINVAL, "%s: %d steps, not 2 to %d", who, nsteps, P.limit);
   if (int rc = check_device()) return rc;
   hipStream_t s = as_stream(stream);
   const T omega = T(1) / tau;

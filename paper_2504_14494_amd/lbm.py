@@ -132,8 +132,8 @@ def lbm_step_channel(src: torch.Tensor, dst: torch.Tensor, tau: float, gx: float
 
 
 def lbm_steps_max(nx: int, ny: int, dtype=torch.float32, walls: bool = False) -> int:
-    """The most steps that one call of lbm_steps_bgk (walls: lbm_steps_channel)
-    takes for this lattice."""
+    """The most steps that are worth taking in one call of lbm_steps_bgk (walls:
+    lbm_steps_channel) for this lattice."""
     return int(_lib.load().lbm_steps_max(nx, ny, int(dtype == torch.float64), int(walls)))
 
 
@@ -299,8 +299,9 @@ class Lattice:
         # Several steps of a larger lattice in one launch outlast the 9 us it takes
         # to issue one, and a capture costs 1 to 5 ms (640 steps, replayed and
         # eager: 534 and 719 us at 64^2 FP32, 661 and 700 at 128^2; 917 and 880 at
-        # 128^2 FP64, 972 and 922 at 256^2 FP32, 2455 and 2258 at 512^2 FP64).
-        if most > 1 and self.a.nbytes > 9 * self.GRAPH_BYTES:
+        # 128^2 FP64, 972 and 922 at 256^2 FP32, 2455 and 2258 at 512^2 FP64).  Two or
+        # three steps, as lattices of few rows take, fill those 9 us later.
+        if most > 1 and self.a.nbytes > 9 * self.GRAPH_BYTES * (16 if most < 4 else 1):
             graph = False
         if graph and n >= self.GRAPH_CHUNK and 2 * most <= self.GRAPH_CHUNK:
             k = (key, self.a.data_ptr())
