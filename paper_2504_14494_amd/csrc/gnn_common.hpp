@@ -205,6 +205,9 @@ int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, const
 // consecutive chunks: its first batch by its index in the part, every later
 // one from the part's counter, drawn by lane 0 in the first chunk of the
 // previous batch, so the atomic's latency hides behind that chunk's loads.
+// Fewer chunks than a batch per wave are dealt out in turn, without the counters: the
+// waves would all draw at once, and a part's draws, one after the other, took longer
+// than the chunks (ungated Fig. 2 steps: 1 x 8000 27.4 -> 20.4 us, 512^2 20.2 -> 16.1).
 // Every member is wave-uniform.  No result depends on which wave takes a
 // chunk.
 constexpr int kQueueParts = 8;
@@ -215,6 +218,7 @@ struct ChunkQueue {
   int c, xc, y, b;  // current chunk, c >= nchunks when done
   int cxn, ny, nchunks;
   int base, len, cur, end, first_dyn, batch;
+  int stride;  // 0, or a wave's next chunk without drawing
   unsigned *ctr;
   int nxt;     // first chunk (in the part) of the next batch, once taken
   bool fresh;  // the current chunk starts its batch: its draw is to be issued and taken
@@ -230,11 +234,11 @@ struct ChunkQueue {
     base = p * L;
     len = nchunks - base < L ? nchunks - base : L;
     const int part_waves = ((G - 1 - p) / parts + 1) * waves_per_block;
-    const int share = len / part_waves;
-    batch = share >= kQueueBatch ? kQueueBatch : (share > 1 ? share : 1);
+    const bool deal = len < part_waves * kQueueBatch;
+    batch = deal ? 1 : kQueueBatch;
+    stride = deal ? part_waves : 0;
     first_dyn = part_waves * batch;
     ctr = counters + p * kQueueStride;
-    nxt = len;
     cur = ((int)blockIdx.x / parts * waves_per_block + w) * batch;
     begin_batch();
   }
@@ -251,7 +255,8 @@ struct ChunkQueue {
     }
     end = cur + batch < len ? cur + batch : len;
     at(cur);
-    fresh = true;
+    nxt = cur + stride;
+    fresh = stride == 0;
   }
   // In the first chunk of a batch, lane 0 draws the next batch: draw() before
   // the chunk's loads, take() once they have been waited for (which waited for
