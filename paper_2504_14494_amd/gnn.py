@@ -326,13 +326,13 @@ class GnnLattice(Lattice):
 
         fb = self.fallback if gate else None
 
-        def warm():
+        def warm(k):
             # same code path on copies: the gate state of the lattice is untouched
             tmp = None
             if gate:
                 tmp = Fallback(0.0, self.fallback.threshold)
                 tmp.mass.copy_(self.fallback.mass)
-            step(self.a.clone(), torch.empty_like(self.a), tmp)
+            step(self.a.clone(), torch.empty_like(self.a), tmp, k)
         return self._run(("gnn", float(tau), bool(gate)) + self._graph_key(gate),
                          lambda s, d, k: step(s, d, fb, k), warm, n, graph,
                          self._most_simple if self.rounds == 0 else 1,
@@ -354,12 +354,12 @@ class GnnLattice(Lattice):
 
         fb = self.fallback if gate else None
 
-        def warm():
+        def warm(k):
             tmp = None
             if gate:
                 tmp = Fallback(0.0, self.fallback.threshold)
                 tmp.mass.copy_(self.fallback.mass)
-            step(self.a.clone(), torch.empty_like(self.a), tmp)
+            step(self.a.clone(), torch.empty_like(self.a), tmp, k)
         return self._run(("gnn_channel", float(tau), float(gx), bool(gate)) + self._graph_key(gate),
                          lambda s, d, k: step(s, d, fb, k), warm, n, graph, self._most_simple)
 

@@ -264,24 +264,27 @@ class Lattice:
     def _capture(self, advance, warmup, most, pair=False):
         """HIP graph of GRAPH_CHUNK steps from self.a, ping-ponging with
         self.b over an even number of launches, so that the state returns to
-        self.a.  `warmup()` runs one step on scratch copies first, on the
-        side stream, so that library state and workspaces exist before the
-        capture and the lattice itself does not advance."""
+        self.a.  `warmup(k)` makes the call for k steps that is captured on scratch
+        copies first, on the side stream, so that the kernels are loaded and
+        library state and workspaces exist before the capture, and the lattice
+        itself does not advance."""
+        launches = -(-self.GRAPH_CHUNK // most)
+        launches += launches % 2
+        shares = _shares(self.GRAPH_CHUNK, launches)
         side = torch.cuda.Stream()
         side.wait_stream(torch.cuda.current_stream())
         with torch.cuda.stream(side):
-            warmup()
+            for k in (2,) if pair else sorted(set(shares)):
+                warmup(k)
         torch.cuda.current_stream().wait_stream(side)
         torch.cuda.synchronize()
-        launches = -(-self.GRAPH_CHUNK // most)
-        launches += launches % 2
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g):
             src, dst = self.a, self.b
             if pair:
                 advance(src, dst, self.GRAPH_CHUNK)
                 return g
-            for k in _shares(self.GRAPH_CHUNK, launches):
+            for k in shares:
                 advance(src, dst, k)
                 src, dst = dst, src
         return g
@@ -355,8 +358,8 @@ class Lattice:
             else:
                 lbm_steps_bgk(src, dst, tau, k)
 
-        def warm():
-            advance(self.a.clone(), torch.empty_like(self.a), 1)
+        def warm(k):
+            advance(self.a.clone(), torch.empty_like(self.a), k)
         return self._run(("bgk", float(tau)), advance, warm, n, graph, self._most)
 
     def step_channel(self, tau: float, gx: float, n: int = 1, graph: bool = False):
@@ -366,8 +369,8 @@ class Lattice:
             else:
                 lbm_steps_channel(src, dst, tau, gx, k)
 
-        def warm():
-            advance(self.a.clone(), torch.empty_like(self.a), 1)
+        def warm(k):
+            advance(self.a.clone(), torch.empty_like(self.a), k)
         return self._run(("channel", float(tau), float(gx)), advance, warm, n, graph,
                          self._most_walls)
 
