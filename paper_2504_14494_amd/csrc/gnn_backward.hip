@@ -948,8 +948,8 @@ extern "C" int gnn_backward(const float *dL_dgpost, const float *g_pre, const vo
   auto asaved = [&](int r) { return (const uint16_t *)at(saved, SL.agg + (size_t)r * hstride); };
 
   if (R == 0) {  // the per-node network, one kernel
-    if (int rc = launch_simple_backward(dL_dgpost, g_pre, tau, (const float *)saved, batch,
-                                        nx, ny, params, part, s))
+    if (int rc = launch_simple_backward(dL_dgpost, g_pre, tau, (const float *)at(saved, SL.z),
+                                        batch, nx, ny, params, part, s))
       return rc;
   } else {
     int cur = 0;

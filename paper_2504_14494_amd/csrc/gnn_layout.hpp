@@ -51,6 +51,7 @@ constexpr size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 //   h_r [64]  BF16 node states r = 0..R
 //   a_r [64]  BF16 summed messages r = 1..R
 //   z   [10]  FP32 head outputs (stored with stride 12)
+// simple_forward (R = 0) keeps z_0 alone, stride 1.
 struct SavedLayout {
   size_t x, e1, h, agg, z, total;
   size_t nodes;
@@ -60,10 +61,14 @@ inline SavedLayout saved_layout(long long nodes, int R) {
   SavedLayout S{};
   size_t n = (size_t)nodes, o = 0;
   S.nodes = n;
+  if (R == 0) {
+    S.total = align256(n * 4);
+    return S;
+  }
   S.x = o; o += align256(n * 16 * 2);
   S.e1 = o; o += align256(n * HID * 2);
   S.h = o; o += align256(n * HID * 2) * (size_t)(R + 1);
-  S.agg = o; o += align256(n * HID * 2) * (size_t)(R > 0 ? R : 1);
+  S.agg = o; o += align256(n * HID * 2) * (size_t)R;
   S.z = o; o += align256(n * 12 * 4);
   S.total = o;
   return S;
@@ -136,7 +141,8 @@ inline size_t step_workspace_bytes(int nx, int ny, int R) {
 // Backward scratch: packed weights, two FP32 node-gradient buffers
 // (ping-pong over the rounds), FP32 gradients of the summed messages, BF16
 // per-edge gradients of the edge-layer pre-activations (8 x 64 per node), and one
-// FP32 partial parameter gradient per wave of the fixed backward grid.
+// FP32 partial parameter gradient per wave of the fixed backward grid.  The
+// backward pass of the per-node network (R = 0) needs the partials alone.
 constexpr int kBwdBlocks = 256;
 constexpr int kBwdWaves = kBwdBlocks * 4;
 struct BackwardScratch {
@@ -147,11 +153,13 @@ inline BackwardScratch backward_scratch(long long nodes, int R) {
   BackwardScratch B{};
   size_t n = (size_t)nodes, o = 0;
   size_t np = blob_layout(R).nparam;
-  B.pack = o; o += kPackBytes;
-  B.dhA = o; o += align256(n * HID * 4);
-  B.dhB = o; o += align256(n * HID * 4);
-  B.dagg = o; o += align256(n * HID * 4);
-  B.dq = o; o += align256(n * 8 * HID * 2);
+  if (R > 0) {
+    B.pack = o; o += kPackBytes;
+    B.dhA = o; o += align256(n * HID * 4);
+    B.dhB = o; o += align256(n * HID * 4);
+    B.dagg = o; o += align256(n * HID * 4);
+    B.dq = o; o += align256(n * 8 * HID * 2);
+  }
   B.part = o; o += align256((size_t)kBwdWaves * np * 4);
   B.total = o;
   return B;

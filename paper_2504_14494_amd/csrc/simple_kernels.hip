@@ -404,13 +404,14 @@ extern "C" int simple_forward(const float *g_pre, float *g_post, int batch, int 
   if (!workspace || ws_bytes < simple_scratch().total)
     return fail(LBM_EWORKSPACE, "simple_forward: workspace needs %zu bytes",
                 simple_scratch().total);
-  const size_t saved_need = gnn::saved_bytes(batch, nx, ny, 0);
-  if (saved && saved_bytes < saved_need)
-    return fail(LBM_EWORKSPACE, "simple_forward: saved buffer needs %zu bytes", saved_need);
+  const SavedLayout SL = saved_layout((long long)batch * nx * ny, 0);
+  if (saved && saved_bytes < SL.total)
+    return fail(LBM_EWORKSPACE, "simple_forward: saved buffer needs %zu bytes", SL.total);
   if (int rc = check_device()) return rc;
   int nparts;
   return launch_simple(false, false, 0.0f, g_pre, g_post, batch, nx, ny, tau, 0.0f, params,
-                       head_out, (float *)saved, workspace, nullptr, &nparts, (hipStream_t)stream);
+                       head_out, saved ? (float *)at_(saved, SL.z) : nullptr, workspace, nullptr,
+                       &nparts, (hipStream_t)stream);
 }
 
 // One step and its gate; turn: its number since the weights were packed (0 packs
