@@ -81,8 +81,8 @@ def bgk_single_leg(lat, tau32, steps):
 def simple_src_hash():
     """Hash of the sources of the fused per-node (Fig. 2) step."""
     return hashlib.sha256(_read("gnn_common.hpp") + _read("gnn_layout.hpp") +
-                          _read("simple_kernels.hip") + _read("lbm_common.hpp") +
-                          _read("channel_common.hpp")).hexdigest()[:16]
+                          _read("simple_kernels.hip") + _read("simple_common.hpp") +
+                          _read("lbm_common.hpp") + _read("channel_common.hpp")).hexdigest()[:16]
 
 
 def gnn_src_hash():
