@@ -19,7 +19,8 @@ __all__ = ["gnn_param_count", "gnn_blob_len", "saved_bytes", "gnn_forward", "lbm
            "lbm_step_gnn_noalloc",
            "Fallback", "GnnLattice", "gnn_backward", "gnn_mse", "gnn_adam", "GnnCollide",
            "GnnMse", "gnn_mse_weighted", "simple_forward", "lbm_step_simple", "lbm_step_simple_channel",
-           "lbm_steps_simple_max", "lbm_steps_simple", "lbm_steps_simple_channel", "gnn_gelu_rate", "collide"]
+           "lbm_steps_simple_max", "lbm_steps_simple", "lbm_steps_simple_channel",
+           "lbm_steps_gnn", "gnn_gelu_rate", "collide"]
 
 
 def gnn_param_count(rounds: int = 2) -> int:
@@ -123,11 +124,13 @@ def lbm_step_gnn(src: torch.Tensor, dst: torch.Tensor, tau: float, blob: torch.T
 
 def lbm_steps_gnn(a: torch.Tensor, b: torch.Tensor, tau: float, blob: torch.Tensor, nsteps: int,
                   rounds: int = 2, fallback: Fallback = None, ws: Workspace = None):
-    """nsteps steps of lbm_step_gnn (rounds = 0: lbm_step_simple) in one call, alternately from a into b and
-    back.  Returns the buffer of the last state: b if nsteps is odd, else a."""
+    """nsteps steps of lbm_step_gnn (rounds = 0: lbm_step_simple) in one call,
+    alternately from a into b and back.  Returns the buffer of the last state: b if
+    nsteps is odd, else a."""
+    nsteps = int(nsteps)
     nx, ny, fb, buf = _gnn_step_args(a, b, blob, rounds, fallback, ws)
     rc = _lib.load().lbm_steps_gnn(_ptr(a), _ptr(b), nx, ny, float(tau), _ptr(blob), rounds,
-                                   int(nsteps), fb, _ptr(buf), buf.numel(), _stream())
+                                   nsteps, fb, _ptr(buf), buf.numel(), _stream())
     check(rc, "lbm_steps_gnn")
     return b if nsteps % 2 else a
 
