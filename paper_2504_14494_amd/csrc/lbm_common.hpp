@@ -132,8 +132,8 @@ __device__ __forceinline__ void pull9(const T *__restrict__ src, int nx, int ny,
 
 // 1 / x.  FP32: the hardware reciprocal (1 ulp) and one Newton step, three
 // instructions for the eleven of an IEEE division; equal to 1.0f / x for every
-// x in [2^-20, 2^20] (checked over all of them), which is where a density
-// is.  An infinite or zero x gives NaN, as the collision that consumes it does.
+// x in [2^-20, 2^20], which is where a density is (the tests compare every
+// significand of [1/2, 4) and samples of the rest).  An infinite or zero x gives NaN, as the collision that consumes it does.
 __device__ __forceinline__ float recip(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return __builtin_fmaf(__builtin_fmaf(-x, r, 1.0f), r, r);
