@@ -251,13 +251,17 @@ int lbm_step_gnn(const float *g_src, float *g_dst, int nx, int ny, float tau,
 
 /* nsteps steps of lbm_step_gnn (n_rounds = 0: lbm_step_simple) in one call,
  * alternately from g_a into g_b and back: the states, flags, decisions and masses of
- * as many single calls, with the weights packed once.  The last state is in g_b if nsteps is odd, in
- * g_a if it is even; the other buffer holds the state before it.  nsteps >= 1;
- * other arguments and errors as for the single step. */
+ * as many single calls.  The last state is in g_b if nsteps is odd, in g_a if it is
+ * even; the other buffer holds the state before it.  nsteps >= 1; other arguments and
+ * errors as for the single step.  The weights are packed once if the steps are gated,
+ * and without a gate for message passing on small lattices (at most two 16 x 4 tiles per
+ * CU, n_rounds <= 2); otherwise before every step.  On lattices of one workgroup the
+ * per-node network packs before every step here; lbm_steps_simple packs once. */
 int lbm_steps_gnn(float *g_a, float *g_b, int nx, int ny, float tau,
                   const float *params, int n_rounds, int nsteps,
                   const lbm_fallback *fb, void *workspace, size_t ws_bytes,
                   void *stream);
+
 /* lbm_step_gnn without a workspace and without any allocation, for callers
  * that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  The step's scratch
@@ -342,7 +346,7 @@ int lbm_steps_simple_channel(const float *g_src, float *g_dst, int nx, int ny,
  * [batch][ny][9][nx], tau: device float[batch]; head_out NULL or
  * [batch][ny][nx][10].  saved: NULL for inference, else a device buffer of
  * >= lbm_workspace_bytes(LBM_WS_GNN_SAVED, batch, nx, ny, 0) bytes, to be handed
- * to gnn_backward (n_rounds = 0).  It receives z_0 per node; this network's
+ * to gnn_backward (n_rounds = 0).  It receives z_0 per node (4 bytes); this network's
  * activations are cheaper to recompute than to store, so the backward pass
  * forms them again from g_pre. */
 int simple_forward(const float *g_pre, float *g_post, int batch, int nx, int ny,

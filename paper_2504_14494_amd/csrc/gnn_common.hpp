@@ -334,11 +334,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_resource(void *base, size
 // between is what makes the partials visible: an arrival count in the
 // producing kernel, with the device-wide fences it needs across the XCDs, took
 // 7.6 us of a step.  Control words (in the caller's workspace), readied by
-// gnn_prep_kernel, which starts every step: ctrl[kCtrlFallback] = workgroups of
-// the gate kernel done with a fallback (0), ctrl[kCtrlMass ..] = the FP64 mass of
-// the previous state, the tile counters of the message-passing rounds (0),
-// ctrl[kCtrlTileQueue + r], and the chunk counters of the encoder or of the
-// fused per-node step (0), ctrl[kCtrlChunkQueue + 32 p].
+// gnn_prep_kernel before a step that packs the weights, else by the gate of the step
+// before: ctrl[kCtrlFallback] = workgroups of the gate kernel done with a fallback (0),
+// ctrl[kCtrlMass ..] = the FP64 mass of the previous state, the tile counters of the
+// message-passing rounds (0), ctrl[kCtrlTileQueue + r], and the chunk counters of the
+// encoder or of the fused per-node step (0), ctrl[kCtrlChunkQueue + 32 p].
 constexpr int kCtrlFallback = 2;
 constexpr int kCtrlTileQueue = 4;
 constexpr int kCtrlMass = 8;         // two doubles: the gate's reference mass of even and odd steps

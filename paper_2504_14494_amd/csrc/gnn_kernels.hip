@@ -887,8 +887,8 @@ __global__ __launch_bounds__(kRoundThreads, 2) void gnn_round_kernel(
 // there is one workgroup per CU (eight waves, two per SIMD), its GELUs
 // alone are 6 us (10, 7 and 4 groups of 16 nodes in the three phases of R = 2),
 // and it runs 16: 2.6 until the weights and populations are there, 2 in the
-// encoder, 7 and 4 in the rounds.  A gated step of 128^2 in a captured graph:
-// 46 us with encoder, rounds and gate arrival, 24 with this kernel.
+// encoder, 7 and 4 in the rounds.  Gated steps of 128^2, the weights packed once:
+// 35 us each with encoder and rounds on their own, 20 with this kernel.
 constexpr int kSmallThreads = 512;
 constexpr int kSmallWaves = kSmallThreads / 64;
 constexpr int kSmallY = 4;                 // tile rows (TILE_X columns)
@@ -1311,9 +1311,10 @@ int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, const
 }
 
 // Small lattices take one fused kernel, up to two workgroups per CU one after
-// the other: gated steps took 23 us at 128^2 (256 tiles; encoder and rounds
-// launched on their own 46), 39 at 160 x 160 (400 tiles; 43) and 55 at 192^2
-// (576 tiles; 54).
+// the other.  Gated steps, the weights packed once, with it and with encoder and
+// rounds on their own: two rounds 20.2 and 35.2 us at 128^2 (256 tiles), 35.2 and 36.8
+// at 160^2 (400), 50.5 and 49.1 at 192^2 (576); one round 13.1 and 23.7, 21.6 and
+// 24.9, 30.0 and 31.7, but 39.2 and 33.5 at 256^2 (1,024).
 static bool small_lattice(int batch, int nx, int ny, int R) {
   const long long tiles =
       (long long)batch * ((nx + TILE_X - 1) / TILE_X) * ((ny + kSmallY - 1) / kSmallY);
@@ -1542,9 +1543,11 @@ extern "C" int lbm_step_gnn(const float *g_src, float *g_dst, int nx, int ny, fl
 }
 
 // The packing of the weights takes as long as the gate, 4.5 us and a launch: several
-// steps pack once.  Gated steps one by one and so: message passing 22.6 and 19.2 us
-// at 128^2, 58.8 and 54.4 at 256^2; the Fig. 2 network 12.3 and 9.1 at 128^2, 22.9
-// and 19.5 at 512^2.
+// gated steps pack once, and so do ungated ones in the fused kernel, which draws no
+// work.  (Other ungated steps pack each time: packing is what zeroes the work
+// counters.)  Gated steps one by one and so: message passing 23.2 and 21.1 us at 128^2,
+// 57.8 and 53.6 at 256^2; the Fig. 2 network 12.8 and 9.6 at 128^2, 19.6 and 17.1 at
+// 512^2.
 extern "C" int lbm_steps_gnn(float *g_a, float *g_b, int nx, int ny, float tau,
                              const float *params, int n_rounds, int nsteps,
                              const lbm_fallback *fb, void *workspace, size_t ws_bytes,

@@ -82,7 +82,8 @@ inline size_t saved_bytes(int batch, int nx, int ny, int R) {
 // sizes the per-workgroup partial sums.
 constexpr int kMaxGnnBlocks = 2048;
 
-// Control words of a step (gate decision and arrival counts, work counters).
+// Control words of a step (the fallback's arrival count, the gate's reference masses,
+// work counters; see gnn_common.hpp).
 constexpr int kCtrlWords = 512;
 
 // Bytes of the packed weight fragments (see gnn_common.hpp); generous bound

@@ -22,10 +22,6 @@
 
 namespace gnn {
 
-// Shared with gnn_kernels.hip.
-int launch_prep(const float *params, int R, uint8_t *pack, unsigned *ctrl, const double *mass,
-                hipStream_t s);
-
 namespace simple {
 
 using lbm::cx;

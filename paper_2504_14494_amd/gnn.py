@@ -157,8 +157,8 @@ def simple_forward(g_pre: torch.Tensor, tau: torch.Tensor, blob: torch.Tensor,
                    want_z: bool = False, saved: torch.Tensor = None, ws: Workspace = None):
     """The per-node (Fig. 2) corrected collision of a batch of pre-collision
     states, no streaming.  blob: zero-round layout.  With `saved` (uint8,
-    saved_bytes(B, nx, ny, 0)) the activations gnn_backward(rounds=0) needs
-    are kept.  Returns (g_post, z)."""
+    saved_bytes(B, nx, ny, 0)) what gnn_backward(rounds=0) needs is kept.  Returns
+    (g_post, z)."""
     single = g_pre.dim() == 3
     if single:
         g_pre = g_pre.unsqueeze(0)
