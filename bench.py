@@ -40,7 +40,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 BGK_BYTES_PER_LU = 72           # 9 FP32 loads + 9 FP32 stores per node
-BGK_VALU_PER_LU = 82            # instructions of one node's BGK collision
+BGK_VALU_PER_LU = 84            # instructions of one node's BGK collision
 VALU_PEAK_TOPS = 39.3           # 256 CUs x 64 lanes x 2.4 GHz, no packed FP32
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bgk_pull_8192_traffic.json")
 

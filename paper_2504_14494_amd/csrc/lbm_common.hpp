@@ -77,7 +77,7 @@ struct Moments {
 
 // Shifted equilibrium of direction i, as geq_shifted.  Opposite directions
 // share e.u up to its sign and C (e.u)^2, and no product with a zero component
-// is formed (the compiler must keep one: it is NaN for an infinite factor): 82
+// is formed (the compiler must keep one: it is NaN for an infinite factor): 84
 // VALU instructions for the collision of a node, 108 when every direction
 // was written out.  The fused multiply-adds are explicit, so that every kernel
 // that inlines this rounds alike: steps of different kernels agree bitwise.
@@ -130,13 +130,16 @@ __device__ __forceinline__ void pull9(const T *__restrict__ src, int nx, int ny,
   g[8] = rp[(size_t)8 * nx + xm];
 }
 
-// 1 / x.  FP32: the hardware reciprocal (1 ulp) and one Newton step, three
+// 1 / x.  FP32: the hardware reciprocal (1 ulp) and one Newton step, five
 // instructions for the eleven of an IEEE division; equal to 1.0f / x for every
 // x in [2^-20, 2^20], which is where a density is (the tests compare every
-// significand of [1/2, 4) and samples of the rest).  An infinite or zero x gives NaN, as the collision that consumes it does.
+// significand of [1/2, 4) and samples of the rest).  Taken at x / 4: the hardware
+// flushes results below 2^-126, and a run that blows up through densities of 2^126
+// then lost its momentum there and could stay finite (0.8 % of a BGK step at
+// 8192^2).  An infinite or zero x gives NaN, as the collision that consumes it does.
 __device__ __forceinline__ float recip(float x) {
-  const float r = __builtin_amdgcn_rcpf(x);
-  return __builtin_fmaf(__builtin_fmaf(-x, r, 1.0f), r, r);
+  const float y = 0.25f * x, r = __builtin_amdgcn_rcpf(y);
+  return 0.25f * __builtin_fmaf(__builtin_fmaf(-y, r, 1.0f), r, r);
 }
 // FP64: two Newton steps from the hardware's estimate, to within an ulp.
 __device__ __forceinline__ double recip(double x) {

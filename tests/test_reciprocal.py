@@ -127,3 +127,17 @@ def test_fp64_is_within_one_unit_in_the_last_place():
     ref = 1.0 / (1.0 + g0.astype(np.float64))
     assert (np.abs(inv - ref) <= np.spacing(ref)).all()
     assert np.mean(inv != ref) < 0.01      # and the quotient itself nearly always
+
+
+@pytest.mark.gpu
+def test_densities_up_to_the_largest_keep_their_momentum():
+    """1 / rho is below the smallest normal number from 2^126 on."""
+    k = torch.arange(0, 4096, device="cuda", dtype=torch.float64)
+    rho = (2.0 ** (120 + 7.999 * k / 4096)).float()
+    half = (rho.double() / 16).float()
+    src = torch.zeros(1, 9, rho.numel(), device="cuda")
+    src[0, 0], src[0, 2], src[0, 4] = rho, half, -half
+    g = lbm.lbm_step_bgk(src, torch.empty_like(src), 1.0)[0].double()
+    j = (g[2] - g[4]) + (g[5] + g[6] - g[7] - g[8])
+    # (FP32 sums of nine terms of the size of rho, and 22 bits of 1 / rho)
+    assert float(((j - 2 * half.double()).abs() / rho.double()).max()) <= 1e-5
