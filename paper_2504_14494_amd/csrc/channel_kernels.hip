@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kChannelThreads) void channel_profile_kernel(
 #pragma unroll
     for (int i = 0; i < 9; ++i) f[i] = (double)r[(size_t)i * nx + x];
     const Moments<double> M = node_moments(f);
-    acc += M.u - 0.5 * (double)gx;
+    acc += fma_of(M.jx, M.inv, -0.5 * (double)gx);  // u rounded once
   }
   red[threadIdx.x] = acc;
   __syncthreads();
