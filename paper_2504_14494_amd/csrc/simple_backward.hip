@@ -35,6 +35,13 @@ struct BwdWave {
   uint16_t d_z[16 * kPitch], d_2[64 * kPitch], d_1[64 * kPitch];  // gradients, channel-major
   uint16_t a_h[64 * kPitch], a_e[64 * kPitch], a_x[16 * kPitch];  // activations
 };
+// A factor rather than a choice: a gradient that is not finite stays so in the units
+// that are off, too.
+__device__ __forceinline__ f32x4 relu_grad(f32x4 p) {
+  return f32x4{p.x > 0.0f ? 1.0f : 0.0f, p.y > 0.0f ? 1.0f : 0.0f, p.z > 0.0f ? 1.0f : 0.0f,
+               p.w > 0.0f ? 1.0f : 0.0f};
+}
+
 constexpr int kBwdFrags = 24;     // W1 4, W2 8, W2^T 8, Wh^T 4
 
 __global__ __launch_bounds__(kBT) void simple_backward_kernel(
@@ -207,9 +214,7 @@ __global__ __launch_bounds__(kBT) void simple_backward_kernel(
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             o[h][t] = mfma(wt, dzb[h], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
-            const f32x4 p = p2[h][t];
-            o[h][t] = f32x4{p.x > 0.0f ? o[h][t].x : 0.0f, p.y > 0.0f ? o[h][t].y : 0.0f,
-                            p.z > 0.0f ? o[h][t].z : 0.0f, p.w > 0.0f ? o[h][t].w : 0.0f};
+            o[h][t] *= relu_grad(p2[h][t]);
             s2[t] += o[h][t];
           }
         }
@@ -228,9 +233,7 @@ __global__ __launch_bounds__(kBT) void simple_backward_kernel(
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             o[h][t] = mfma(w1, dpb[h][1], mfma(w0, dpb[h][0], f32x4{0.0f, 0.0f, 0.0f, 0.0f}));
-            const f32x4 p = p1[h][t];
-            o[h][t] = f32x4{p.x > 0.0f ? o[h][t].x : 0.0f, p.y > 0.0f ? o[h][t].y : 0.0f,
-                            p.z > 0.0f ? o[h][t].z : 0.0f, p.w > 0.0f ? o[h][t].w : 0.0f};
+            o[h][t] *= relu_grad(p1[h][t]);
             s1[t] += o[h][t];
           }
         }
